@@ -57,13 +57,21 @@ aln_status_t make_params(const aln_scoring_t* sc, KParams* kp) {
   }
   kp->sigma_max = smax;
   kp->sigma_min = smin;
+  kp->fgo = (float)kp->go;
+  for (int k = 0; k < 20; ++k) kp->fc[k] = (float)(-k * kp->ge);
+  for (int a = 0; a < A; ++a)
+    for (int b = 0; b < A; ++b) {
+      const int8_t v = (int8_t)(kp->sig[a * kMaxAlphabet + b] - 2 * kp->ge);
+      kp->sig2[a * kMaxAlphabet + b] = v;
+      kp->sig2[kMaxAlphabet * kMaxAlphabet + b * kMaxAlphabet + a] = v;
+    }
   return ALN_OK;
 }
 
 // Every exact score of an n x m problem lies in [3*go + (n+m)*ge, min(n,m)*max(sigma_max, 0)];
 // the 32-bit lanes need both ends well inside +-2^29 (the pad letter scores -2^29).
-// The wavefront engine also adds a row bias of up to rows*|ge| to every value, and relaxes a pair
-// transposed when that puts the longer sequence along the rows.
+// The wavefront engine also adds a bias of up to (rows + columns)*|ge| to every value: with both bounds below
+// 2^28 that stays below 2^30, and the bias cancels in every comparison with the pad letter's 2^29.
 static bool fits_i32(const KParams& kp, int64_t max_n, int64_t max_m) {
   const int64_t mn = max_n < max_m ? max_n : max_m;
   const int64_t mx = max_n < max_m ? max_m : max_n;
@@ -236,8 +244,8 @@ aln_status_t aln_align_batch_ex(const aln_scoring_t* scoring, int64_t n_pairs, c
   launch_split(L.sp, n_pairs, q_off, s_off, max_n, max_m, out, split_ws, stream);
   if (!tb || L.sp.code_cap > 0) {
     WfWs W = wf_view(split_ws + L.sp.wf_base, L.sp.wf);
-    st = launch_wf_i32(kp, W, q, s, out, L.sp.wf_waves, L.sp.grouped, tb, !tb && L.sp.wf_p16, cigar, 0, stream,
-                       tb ? cigar_off : nullptr);
+    st = launch_wf_i32(kp, W, q, s, out, L.sp.wf_waves, L.sp.grouped, tb, !tb && L.sp.wf_p16,
+                       band_fits_fa(kp, max_n, max_m), cigar, 0, stream, tb ? cigar_off : nullptr);
     if (st != ALN_OK) return st;
   }
   const int* list = reinterpret_cast<const int*>(split_ws + L.sp.off_small_idx);

@@ -29,7 +29,11 @@ struct KParams {
   int32_t sigma_min;
   int64_t spin_dev;  // polls of device memory a bounded wait makes before giving up
   int64_t spin_lds;  // polls of LDS a bounded wait makes before giving up
+  float fgo;      // go
+  float fc[20];   // fc[k] = -k * ge
   int8_t sig[kMaxAlphabet * kMaxAlphabet];  // row-major sigma(q, s) over the real alphabet
+  // sigma - 2 ge (low bytes; exact where every one fits a byte): row-major by query letter, then by subject letter
+  alignas(4) int8_t sig2[2 * kMaxAlphabet * kMaxAlphabet];
 };
 
 // Traceback slabs of the one-pair-per-lane kernels hold every cell's code for the waves in flight; a batch
@@ -100,7 +104,6 @@ struct WfWs {
   int2* ckcols;      // checkpointed forward pass (one pair), else null: [k][row - 1] Hb and Fb of column
                      // (k + 1) * kTileCols; its row slots hold every group's bottom row
   int64_t ck_ld;     // rows of a checkpoint column (a multiple of the band height)
-  int one_pair;      // aln_align_long: one pair, its bands spread over the whole device
   int64_t* order;    // [n_items] per-band engine: the item handed out at each ticket (see wf_order_kernel)
   int* lv;           // [2 * n_lv - 1] per-band engine: level counts, positions and cursors of that order
   int n_lv;          // more than the largest band count of any pair
@@ -175,9 +178,14 @@ WfWs wf_view(void* base, const WfOffsets& o);
 // where the scoring's step bound keeps them exact
 // cigar_off: batches, each pair's CIGAR room (cigar[cigar_off[k] .. cigar_off[k + 1]]); else one pair with
 // cigar_cap words at cigar
+// fa: band_fits_fa of the largest pair
 aln_status_t launch_wf_i32(const KParams& kp, const WfWs& W, const uint8_t* q, const uint8_t* s, aln_result_t* out,
-                           int max_waves, bool grouped, bool tb, bool p16, uint32_t* cigar, int64_t cigar_cap,
-                           hipStream_t stream, const int64_t* cigar_off = nullptr);
+                           int max_waves, bool grouped, bool tb, bool p16, bool fa, uint32_t* cigar,
+                           int64_t cigar_cap, hipStream_t stream, const int64_t* cigar_off = nullptr);
+// Whether every lane value of pairs up to n x m stays in the 2^23 consecutive integers that lanes held as floats
+// cover (band.h): values are at least 2 go - 127 and at most min(n, m) max(sigma, 0) + (n + m) |ge|, taken here over
+// the padding rows and columns a band relaxes, with room for 2^20 below zero.
+bool band_fits_fa(const KParams& kp, int64_t n, int64_t m);
 aln_status_t plan_long(int64_t n, int64_t m, bool tb, LongPlan* plan);
 void launch_single_pair(const WfWs& W, int n, int m, hipStream_t stream);
 

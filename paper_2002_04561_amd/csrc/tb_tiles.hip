@@ -28,13 +28,6 @@ constexpr int kTbWinMargin = 2 * kTileCols;   // window columns beyond the rows 
 
 // Profile kinds of the band wavefront (band.h): register bytes for up to 4 letters, else the LDS table.
 
-__device__ __forceinline__ int t_dpp_shr1(int old, int src) {
-  return __builtin_amdgcn_update_dpp(old, src, 0x138, 0xf, 0xf, false);  // wave_shr:1, lane 0 keeps old
-}
-__device__ __forceinline__ int t_dpp_shl1(int old, int src) {
-  return __builtin_amdgcn_update_dpp(old, src, 0x130, 0xf, 0xf, false);  // wave_shl:1, lane 63 keeps old
-}
-
 struct TbView {
   int n, m;            // rows (query) and columns (subject) of the pair
   int seg_rows;        // rows of a segment, a multiple of kTileRows
@@ -55,23 +48,27 @@ __device__ __forceinline__ int tb_window_lo(int i, int j, int seg_r0) {
   return c > 0 ? c / kTileCols : 0;
 }
 
-// One tile of the segment `seg`, relaxed again with the codes stored.  Values carry the row bias of
-// the band wavefront (Hb = H - i*ge, likewise E and F), so they are the forward pass's own integers.
+// One tile of the segment `seg`, relaxed again with the codes stored.  Values are lane values of band.h, as in
+// the forward pass, so they are its own integers.
 // Phase 0 relaxes the tiles of the window, phase 1 (after a walk that stopped at the window's left
 // edge) those left of it.
-template <int MODE, bool AFFINE, int PROF>
+template <int MODE, bool AFFINE, int PROF, bool FA>
 __global__ __launch_bounds__(64 * kTWaves) void tb_tile_kernel(const KParams P, const uint8_t* __restrict__ Q,
                                                               const uint8_t* __restrict__ S, TbView V, int seg,
                                                               int phase) {
   constexpr int R = kWfR, BLK = kTBlk;
-  __shared__ int32_t tab[kTab * kTab];
+  __shared__ int32_t tab[PROF == kProfTable ? kTab * kTab : 1];
   __shared__ int4 stage[kTWaves][3][BLK / 4];  // lane-0 inputs of BLK steps: H, E, letter
   __shared__ int2 ring[kTWaves][kTRing];       // ring w carries band w-1's bottom row to band w
   __shared__ int pub[kTWaves], con[kTWaves];
   __shared__ int s_err;
-  for (int k = threadIdx.x; k < kTab * kTab; k += blockDim.x) {
-    const int a = k / kTab, b = k % kTab;
-    tab[k] = (a >= P.alphabet || b >= P.alphabet) ? -kBig32 : (int32_t)P.sig[a * kMaxAlphabet + b] - P.ge;
+  __shared__ uint32_t sig2[PROF == kProfTable ? 1 : kScoreWords];
+  if constexpr (PROF != kProfTable) fill_score_bytes(P, sig2);
+  if constexpr (PROF == kProfTable) {
+    for (int k = threadIdx.x; k < kTab * kTab; k += blockDim.x) {
+      const int a = k / kTab, b = k % kTab;
+      tab[k] = (a >= P.alphabet || b >= P.alphabet) ? -kBig32 : (int32_t)P.sig[a * kMaxAlphabet + b] - 2 * P.ge;
+    }
   }
   if (threadIdx.x < kTWaves) {
     pub[threadIdx.x] = 0;
@@ -95,7 +92,6 @@ __global__ __launch_bounds__(64 * kTWaves) void tb_tile_kernel(const KParams P, 
   const int i0 = R0 + wib * kWfBand;               // this band's rows i0+1 .. i0+kWfBand
   if (i0 >= rows_hi) return;                       // the bands below it return too; none waits on it
   const bool has_out = wib + 1 < kTWaves && i0 + kWfBand < rows_hi;
-  const int32_t go = P.go, ge = P.ge, goe = P.goe;
   int* st_h = reinterpret_cast<int*>(&stage[wib][0][0]);
   int* st_e = reinterpret_cast<int*>(&stage[wib][1][0]);
   int* st_c = reinterpret_cast<int*>(&stage[wib][2][0]);
@@ -117,58 +113,43 @@ __global__ __launch_bounds__(64 * kTWaves) void tb_tile_kernel(const KParams P, 
     return true;
   };
 
-  // rows of this lane, their letters and profile entries
-  int prof[R];
-  int32_t hl[R], f[R], nu[R];
+  // rows of this lane: their letters' profile entries, and the column left of the tile (the matrix border, or a
+  // checkpoint column) with the cell above-left of the first row
+  int prof[R], rowc[R];
+  BandLane<R> L;
   const int irow0 = i0 + lane * R;  // the row just above this lane's first row
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int i = irow0 + r + 1;
-    int c = kPad;
-    if (i <= n) {
-      c = Q[i - 1];
-      if (c >= P.alphabet) c = kPad;
-    }
-    if (PROF == kProfReg) {
-      uint32_t w = 0;
-      for (int a = 0; a < 4; ++a) {
-        const int v = (c < P.alphabet && a < P.alphabet) ? tab[c * kTab + a] : -128;
-        w |= ((uint32_t)(v & 0xff)) << (8 * a);
-      }
-      prof[r] = (int)w;
+    int c = i <= n ? (int)Q[i - 1] : kPad;
+    rowc[r] = c >= P.alphabet ? kPad : c;
+  }
+  band_profile<PROF, R>(P, sig2, rowc, false, prof, nullptr);
+  const int2* cc = C0 == 0 ? nullptr : V.ckcols + (int64_t)(C0 / kTileCols - 1) * V.ck_ld;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    if (C0 == 0) {
+      L.h[r] = border_h<MODE, FA>(P, irow0 + r + 1, 0);
+      L.f[r] = lane_neg<FA>();
     } else {
-      prof[r] = c * kTab;
-    }
-    nu[r] = -i * ge;  // local floor: H = 0
-  }
-  // the column left of the tile (the matrix border, or a checkpoint column), and the cell above-left
-  // of each lane's first row
-  int32_t diag;
-  if (C0 == 0) {
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int i = irow0 + r + 1;
-      hl[r] = (MODE == ALN_GLOBAL) ? go : -i * ge;  // Hb(i, 0)
-      f[r] = kNeg32;
-    }
-    diag = (MODE == ALN_GLOBAL) ? (irow0 > 0 ? go : 0) : -irow0 * ge;  // Hb(irow0, 0)
-  } else {
-    const int2* cc = V.ckcols + (int64_t)(C0 / kTileCols - 1) * V.ck_ld;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
       const int2 v = cc[irow0 + r];
-      hl[r] = v.x;
-      f[r] = v.y;
+      L.h[r] = v.x;
+      L.f[r] = v.y;
     }
-    if (irow0 > R0)
-      diag = cc[irow0 - 1].x;
-    else if (R0 == 0)
-      diag = (MODE == ALN_GLOBAL) ? go + C0 * ge : 0;  // H(0, C0)
-    else
-      diag = V.ckrows[(int64_t)(R0 / kTileRows - 1) * (m + 1) + C0].x;
+    L.g[r] = lane_add<FA>(L.h[r], P.go, P.fgo);
   }
+  if (C0 == 0 || (irow0 == 0 && R0 == 0))
+    L.diag = border_h<MODE, FA>(P, irow0, C0);
+  else if (irow0 > R0)
+    L.diag = cc[irow0 - 1].x;
+  else
+    L.diag = V.ckrows[(int64_t)(R0 / kTileRows - 1) * (m + 1) + C0].x;
+  L.bot_h = L.h[R - 1];
+  L.bot_e = lane_neg<FA>();
+  // the floor at the first step's column, C0 + 1 - lane
+  L.floor0 = lane_zero<FA>() - (irow0 + 1 + C0 + 1 - lane) * P.ge;
   uint16_t* __restrict__ codes = V.codes + (int64_t)((irow0 - seg_r0) / R) * m + C0;
-  int32_t bot_h = 0, bot_e = kNeg32, cur_c = 0, out_h = 0, out_e = 0;
+  int cur_c = 0, out_h = 0, out_e = 0;
   int2* __restrict__ rin = ring[wib];
   int2* __restrict__ rout = ring[has_out ? wib + 1 : wib];
   const uint8_t* __restrict__ s = S + C0;
@@ -176,7 +157,7 @@ __global__ __launch_bounds__(64 * kTWaves) void tb_tile_kernel(const KParams P, 
     if (col > cols) return 0;
     int c = s[col - 1];
     if (c >= P.alphabet) c = PROF == kProfTable ? kPad : 0;
-    return PROF == kProfReg ? c * 8 : c;
+    return PROF == kProfReg ? 1 << (8 * c) : c;
   };
 
   const int steps = cols + 63;
@@ -184,11 +165,11 @@ __global__ __launch_bounds__(64 * kTWaves) void tb_tile_kernel(const KParams P, 
     // lane-0 inputs for steps tb..tb+BLK-1 (tile columns tb+1..tb+BLK), held by lanes < BLK
     const int col_in = tb + 1 + lane;
     const int sreg = lane < BLK ? letter_idx(col_in) : 0;
-    int32_t th = 0, te = kNeg32;
+    int32_t th = lane_neg<FA>(), te = lane_neg<FA>();
     if (wib == 0) {
       if (lane < BLK && col_in <= cols) {
         if (R0 == 0) {
-          th = (MODE == ALN_GLOBAL) ? go + (C0 + col_in) * ge : 0;
+          th = border_h<MODE, FA>(P, 0, C0 + col_in);
         } else {
           const int2 v = V.ckrows[(int64_t)(R0 / kTileRows - 1) * (m + 1) + C0 + col_in];
           th = v.x;
@@ -212,44 +193,28 @@ __global__ __launch_bounds__(64 * kTWaves) void tb_tile_kernel(const KParams P, 
       st_e[lane] = te;
       st_c[lane] = sreg;
     }
-    // One step: lane l relaxes tile column jt = t - l + 1 for its R rows and stores their codes.
-    auto step = [&](int t, int in_top_h, int in_top_e, int in_top_c, auto checked) {
-      const int jt = t - lane + 1;
-      const int in_h = t_dpp_shr1(in_top_h, bot_h);
-      const int in_e = t_dpp_shr1(in_top_e, bot_e);
-      const int in_c = t_dpp_shr1(in_top_c, cur_c);
-      cur_c = in_c;
-      if (!decltype(checked)::value || (jt >= 1 && jt <= cols)) {
-        int32_t hup = in_h, eup = in_e, hn = 0, unused_bv[R];
-        int unused_bj[R];
-        uint32_t word = 0;
-        band_column<MODE, AFFINE, PROF, true, decltype(checked)::value, R, false>(
-            tab, prof, in_c, 0, go, ge, goe, nu, hl, f, unused_bv, unused_bj, nullptr, jt, -1, diag, hup, eup, hn,
-            word);
-        codes[jt - 1] = (uint16_t)word;
-        bot_h = hup;
-        bot_e = eup;
-        diag = in_h;
-      }
-      out_h = t_dpp_shl1(bot_h, out_h);
-      out_e = t_dpp_shl1(bot_e, out_e);
-    };
     for (int g4 = 0; g4 < BLK / 4; ++g4) {
       const int t0 = tb + 4 * g4;
-      const int4 vh = reinterpret_cast<const int4*>(st_h)[g4];
-      const int4 ve = reinterpret_cast<const int4*>(st_e)[g4];
-      const int4 vc = reinterpret_cast<const int4*>(st_c)[g4];
-      if (t0 >= 63 && t0 + 3 < cols) {
-        step(t0, vh.x, ve.x, vc.x, std::false_type());
-        step(t0 + 1, vh.y, ve.y, vc.y, std::false_type());
-        step(t0 + 2, vh.z, ve.z, vc.z, std::false_type());
-        step(t0 + 3, vh.w, ve.w, vc.w, std::false_type());
-      } else {
-        step(t0, vh.x, ve.x, vc.x, std::true_type());
-        step(t0 + 1, vh.y, ve.y, vc.y, std::true_type());
-        step(t0 + 2, vh.z, ve.z, vc.z, std::true_type());
-        step(t0 + 3, vh.w, ve.w, vc.w, std::true_type());
-      }
+      const int j0 = t0 - lane + 1;  // the lane's tile column at the first of the 4 steps
+      const int4 h4 = reinterpret_cast<const int4*>(st_h)[g4];
+      const int4 e4 = reinterpret_cast<const int4*>(st_e)[g4];
+      const int4 c4 = reinterpret_cast<const int4*>(st_c)[g4];
+      BandIn<R> I = {{h4.x, h4.y, h4.z, h4.w}, {e4.x, e4.y, e4.z, e4.w}, {}, {}};
+      const int v4[4] = {c4.x, c4.y, c4.z, c4.w};
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        I.vc[u] = cur_c = __builtin_amdgcn_update_dpp(v4[u], cur_c, 0x138, 0xf, 0xf, false);  // wave_shr:1
+      BandGroup<R> G;
+      const bool inside = t0 >= 63 && t0 + 3 < cols;
+      auto collect = [&](int) {  // lane 63's outputs (wave_shl:1)
+        out_h = __builtin_amdgcn_update_dpp(L.bot_h, out_h, 0x130, 0xf, 0xf, false);
+        out_e = __builtin_amdgcn_update_dpp(L.bot_e, out_e, 0x130, 0xf, 0xf, false);
+      };
+      if (inside)
+        band_group<MODE, AFFINE, PROF, true, FA, R, false>(P, tab, prof, I, j0, cols, L, G, collect);
+      else
+        band_group<MODE, AFFINE, PROF, true, FA, R, true>(P, tab, prof, I, j0, cols, L, G, collect);
+      store_codes<R>(G, codes, j0, cols, inside);
     }
     // lanes 64-BLK.. hold lane 63's outputs of steps tb..tb+BLK-1, i.e. tile columns tb-62..tb+BLK-63
     if (has_out) {
@@ -330,34 +295,37 @@ __global__ __launch_bounds__(64) void tb_final_kernel(aln_result_t* __restrict__
   }
 }
 
-template <int MODE, bool AFFINE, int PROF>
+template <int MODE, bool AFFINE, int PROF, bool FA>
 void launch_tiles(const KParams& kp, const uint8_t* q, const uint8_t* s, const TbView& V, int seg, int phase,
                   hipStream_t stream) {
   const int tiles = V.seg_rows / kTileRows * V.strips;
-  hipLaunchKernelGGL((tb_tile_kernel<MODE, AFFINE, PROF>), dim3(tiles), dim3(64 * kTWaves), 0, stream, kp, q, s, V,
+  hipLaunchKernelGGL((tb_tile_kernel<MODE, AFFINE, PROF, FA>), dim3(tiles), dim3(64 * kTWaves), 0, stream, kp, q, s, V,
                      seg, phase);
 }
 
 template <int MODE>
-void launch_rounds(const KParams& kp, const uint8_t* q, const uint8_t* s, const TbView& V, int nseg,
+void launch_rounds(const KParams& kp, const uint8_t* q, const uint8_t* s, const TbView& V, int nseg, bool fa,
                    aln_result_t* out, uint32_t* cigar, int64_t cap, hipStream_t stream) {
   hipLaunchKernelGGL((tb_init_kernel<MODE>), dim3(1), dim3(64), 0, stream, out, V, cigar, cap);
-  const bool bytes = kp.sigma_max - kp.ge <= 127 && kp.sigma_min - kp.ge >= -127;
+  const bool bytes = kp.sigma_max - 2 * kp.ge <= 127 && kp.sigma_min - 2 * kp.ge >= -127;
   for (int seg = nseg - 1; seg >= 0; --seg) {
     for (int phase = 0; phase < 2; ++phase) {
       {
         ProfScope prof("traceback_tiles", stream);
-        if (kp.go != 0) {
+        auto tiles = [&](auto affine, auto lanes) {
+          constexpr bool kAffine = decltype(affine)::value, kFa = decltype(lanes)::value;
           if (bytes && kp.alphabet <= 4)
-            launch_tiles<MODE, true, kProfReg>(kp, q, s, V, seg, phase, stream);
+            launch_tiles<MODE, kAffine, kProfReg, kFa>(kp, q, s, V, seg, phase, stream);
           else
-            launch_tiles<MODE, true, kProfTable>(kp, q, s, V, seg, phase, stream);
-        } else {
-          if (bytes && kp.alphabet <= 4)
-            launch_tiles<MODE, false, kProfReg>(kp, q, s, V, seg, phase, stream);
-          else
-            launch_tiles<MODE, false, kProfTable>(kp, q, s, V, seg, phase, stream);
-        }
+            launch_tiles<MODE, kAffine, kProfTable, kFa>(kp, q, s, V, seg, phase, stream);
+        };
+        // the lane values of the forward pass's checkpoints (launch_wf_m)
+        if (kp.go == 0)
+          tiles(std::false_type(), std::false_type());
+        else if (fa)
+          tiles(std::true_type(), std::true_type());
+        else
+          tiles(std::true_type(), std::false_type());
       }
       ProfScope prof("traceback_walk", stream);
       hipLaunchKernelGGL((tb_walk_kernel<MODE>), dim3(1), dim3(64), 0, stream, V, seg, phase, cigar, cap);
@@ -416,7 +384,8 @@ aln_status_t launch_long_ls(const KParams& kp, const LongLsPlan& pl, const uint8
   W.ck_ld = pl.ck_ld;
   launch_single_pair(W, (int)n, (int)m, stream);
   // the forward pass: score, end cell and the checkpoints (grouped bands)
-  aln_status_t st = launch_wf_i32(kp, W, q, s, out, pl.n_waves, true, false, false, nullptr, 0, stream);
+  const bool fa = band_fits_fa(kp, n, m);
+  aln_status_t st = launch_wf_i32(kp, W, q, s, out, pl.n_waves, true, false, false, fa, nullptr, 0, stream);
   if (st != ALN_OK) return st;
   TbView V;
   V.n = (int)n;
@@ -432,13 +401,13 @@ aln_status_t launch_long_ls(const KParams& kp, const LongLsPlan& pl, const uint8
   V.win_lo = reinterpret_cast<int*>(base + pl.off_walk + 192);
   switch (kp.mode) {
     case ALN_GLOBAL:
-      launch_rounds<ALN_GLOBAL>(kp, q, s, V, pl.nseg, out, cigar, cigar_cap, stream);
+      launch_rounds<ALN_GLOBAL>(kp, q, s, V, pl.nseg, fa, out, cigar, cigar_cap, stream);
       break;
     case ALN_LOCAL:
-      launch_rounds<ALN_LOCAL>(kp, q, s, V, pl.nseg, out, cigar, cigar_cap, stream);
+      launch_rounds<ALN_LOCAL>(kp, q, s, V, pl.nseg, fa, out, cigar, cigar_cap, stream);
       break;
     default:
-      launch_rounds<ALN_SEMIGLOBAL>(kp, q, s, V, pl.nseg, out, cigar, cigar_cap, stream);
+      launch_rounds<ALN_SEMIGLOBAL>(kp, q, s, V, pl.nseg, fa, out, cigar, cigar_cap, stream);
       break;
   }
   return hipGetLastError() == hipSuccess ? ALN_OK : ALN_E_DEVICE;

@@ -1,5 +1,9 @@
 // Canonical traceback walk by a whole wave over 4-bit predecessor codes held in device memory.
 //
+// A cell's code is a nibble of its row group's 16-bit word, row r of the group at bits 4 (3 - r): bit 0 "H is not
+// the diagonal", bit 1 "nor E", bit 2 "E extended a gap", bit 3 "F extended a gap"; a local cell with H = 0 has
+// bits 1..0 = 10 (elsewhere bit 1 means nothing while bit 0 is clear).
+//
 // The walk of walk.h (the canonical rule: diagonal, then E, then F in the no-gap state; inside a gap
 // the gap-open predecessor wins ties; local walks stop at a cell whose H is 0, semi-global ones on
 // row 0 or column 0, global ones finish along row 0 or column 0), taken by one wave: the codes are
@@ -94,8 +98,10 @@ __device__ void walk_core(const uint16_t* __restrict__ codes, int64_t ld, int r0
   auto code = [&](int ii, int jj) -> uint32_t {
     const unsigned r = (unsigned)(ii - r0 - 1);
     const uint32_t w = win[(g0 - (int)(r / kWfR)) * kWalkCols + (c0 - jj)];
-    return (w >> (4 * (r % kWfR))) & 15u;
+    return (w >> (4 * (kWfR - 1 - r % kWfR))) & 15u;
   };
+  // H came from the diagonal: bits 1..0 clear, or, without local zeros, bit 0
+  constexpr uint32_t kSrc = MODE == ALN_LOCAL ? 3u : 1u;
   auto push = [&](uint32_t op, uint32_t len) {
     if (op == cur_op) {
       cur_len += len;
@@ -131,7 +137,7 @@ __device__ void walk_core(const uint16_t* __restrict__ codes, int64_t ld, int r0
       const int t = in ? lane : 0;
       const uint32_t ct = code(i - t, j - t);
       const uint32_t pc = in ? ct : 3u;
-      const unsigned long long stop = __builtin_amdgcn_ballot_w64((pc & 3u) != 0u);
+      const unsigned long long stop = __builtin_amdgcn_ballot_w64((pc & kSrc) != 0u);
       const int k = stop ? __builtin_ctzll(stop) : 64;
       if (k > 0) {
         push(ALN_CIGAR_M, (uint32_t)k);
@@ -142,11 +148,11 @@ __device__ void walk_core(const uint16_t* __restrict__ codes, int64_t ld, int r0
       // lane 0 looked at (i, j) itself, which the window holds; its code also gives the first gap
       // step, taken below without reading the cell again
       const uint32_t c = (uint32_t)__builtin_amdgcn_readfirstlane((int)pc);
-      if ((c & 3u) == 3u) {
-        done = true;
+      if (MODE == ALN_LOCAL && (c & 3u) == 2u) {
+        done = true;  // H = 0
         break;
       }
-      state = (int)(c & 3u);
+      state = (c & 2u) ? 2 : 1;
       if (state == 1) {
         push(ALN_CIGAR_I, 1);
         if (!(c & 4u) || i == 1) state = 0;

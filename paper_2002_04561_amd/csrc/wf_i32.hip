@@ -3,9 +3,9 @@
 // A work item is one band (BH = 64*R rows) of one pair.  A wave relaxes a band: lane l owns R
 // consecutive rows and works on column j = t - l + 1 at step t, so the 64 lanes sweep the band as an
 // anti-diagonal front (cells on one anti-diagonal are independent, AnySeq Sec. III-A).  The lane
-// above hands its bottom-row H and E (and the subject letter) down with a DPP wave_shr:1 move each
-// step; lane 0 reads the band's top row from an LDS stage refilled every kBlk steps, and lane 63's
-// outputs collect in a DPP wave_shl:1 shift register that is written out every kBlk steps.
+// above hands its bottom-row H and E down with a DPP wave_shr:1 move each step; lane 0 takes the band's
+// top row from LDS, every lane reads its column letters from an LDS window, and lane 63 writes its bottom
+// row to LDS 4 columns at a time (a DPP shift register took two moves a step, a DPP chain for the letters one).
 //
 // Work is handed out in groups of kWfWavesPerBlock consecutive items from one atomic ticket, so
 // several pairs of different sizes share the device the way the paper's dynamic wavefront shares
@@ -50,29 +50,22 @@ __device__ __forceinline__ int dpp_shl1(int old, int src) {
   return __builtin_amdgcn_update_dpp(old, src, 0x130, 0xf, 0xf, false);  // wave_shl:1, lane 63 keeps old
 }
 
-// Local alignment: every row keeps the best biased score it has seen (bv) and the first column that
-// reached it.  The pair's optimum -- the first cell in (score, i, j) order -- scores at least as high
-// as every real cell, so once per block each row's running value is raised to the largest score seen
-// so far minus one (ties still pass, also for transposed pairs, whose caller rows run along the band):
-// the best of the band's top-row inputs, which are cells of an earlier row, and the best its own rows
-// have recorded.  Rows then record only cells that may still be the optimum.  On related sequences
-// the top row stays ahead of the values that climb towards the diagonal inside the band; on unrelated
-// ones the band's best over all its rows is rarely beaten; either way the exact per-cell update runs
-// in a small fraction of the 4-step groups.  A raised value never wins: it is below a real cell,
-// which some band records or beats.  top_h is the top-row Hb (row i0's bias) of the block's columns,
-// or 0 (at most H = 0) on lanes without one.  Rows past n need no mask: with gap scores <= 0 their
-// values come from row n's minus penalties, or from the floor H = 0, so they never exceed the
-// optimum either.  Every lane of the wave calls this.
-template <int R>
-__device__ __forceinline__ void raise_local_floors(int32_t (&bv)[R], const int32_t (&nu)[R], int32_t top_h, int i0,
-                                                   int32_t ge) {
-  static_assert(R % 2 == 0, "rows are folded in pairs");
-  int32_t v = top_h + i0 * ge;  // H of the top-row cell
-#pragma unroll
-  for (int r = 0; r < R; r += 2) v = max(max(v, bv[r] - nu[r]), bv[r + 1] - nu[r + 1]);
-  const int32_t fl = __ockl_wfred_max_i32(v) - 1;
-#pragma unroll
-  for (int r = 0; r < R; ++r) bv[r] = max(bv[r], fl + nu[r]);
+// Local alignment: every lane keeps the best score its rows have seen (bs) and the first cell, by row and then by
+// column, that reached it.  The pair's optimum -- the first cell in (score, i, j) order -- scores at least as high
+// as every real cell, so once per block each lane's running value is raised to the largest score seen so far minus
+// one (ties still pass, also for transposed pairs, whose caller rows run along the band): the best of the
+// band's top-row inputs, which are cells of an earlier row, and the best its own lanes have recorded.  Lanes then
+// record only cells that may still be the optimum.  On related sequences the top row stays ahead of the values
+// that climb towards the diagonal inside the band; on unrelated ones the band's best over all its rows is
+// rarely beaten.  A raised value never wins: it is below a real cell, which some band records or beats.  top_h
+// is the score of the lane's top-row input, or 0 (at most H = 0) on lanes without one.  Rows past n and columns
+// outside 1..m need no mask: with gap scores <= 0 and a negative pad letter their values come from real cells'
+// minus penalties, or from the floor H = 0, so they never reach the optimum.  Every lane of the wave calls
+// this; it returns the raised floor, which no lane's bs is below.
+__device__ __forceinline__ int raise_local_floor(int32_t& bs, int32_t top_h) {
+  const int32_t fl = __ockl_wfred_max_i32(max(bs, top_h)) - 1;
+  bs = max(bs, fl);
+  return fl;
 }
 
 // Per lane, a where the lane's bit of mask is set, else b: one v_cndmask, never a branch.
@@ -127,139 +120,370 @@ __device__ __forceinline__ bool better(int s1, int i1, int j1, int s2, int i2, i
   return s1 > s2 || (s1 == s2 && (i1 < i2 || (i1 == i2 && j1 < j2)));
 }
 
-// Bands on their own (one wave per band, hand-offs through HBM), handed out level by level (wf_order_kernel).
-//
-// Values are kept with a row bias: Hb(i,j) = H(i,j) - i*ge, and likewise E and F.  Then
-//   Eb(i,j) = max(Eb(i-1,j), Hb(i-1,j) + go)          (extension costs nothing: one add less)
-//   Fb(i,j) = max(Fb(i,j-1) + ge, Hb(i,j-1) + go + ge)
-//   Hb(i,j) = max(Hb(i-1,j-1) + sigma - ge, Eb, Fb [, -i*ge for local])
-// which is Eqs. (1), (4), (5) with every term shifted by the same per-row constant.
-template <int MODE, bool AFFINE, int PROF, bool TB, int R>
-__global__ __launch_bounds__(kWfBlockAlone) void wf_i32_kernel(const KParams P, const uint8_t* __restrict__ Q,
-                                                          const uint8_t* __restrict__ S, WfWs W) {
-  static_assert(PROF != kProfLane || R == 4, "a lane profile word holds 4 rows");
-  // sigma - ge by (query letter, subject letter); also the source of the byte profiles
-  __shared__ int32_t tab[kTab * kTab];
-  __shared__ int4 stage[kWfWavesPerBlock][3][16];  // lane-0 inputs of 64 steps: H, E, letter
-  extern __shared__ uint32_t lprof[];               // kProfLane: [wave][letter][lane], alphabet letters
+// Per wave, the letters of the columns in flight as profile indices: 64 columns before the block, then the block's
+// own (and the 8 columns that the last groups look ahead to, never used).  Step t of the block at tb has lane l
+// at column t - l + 1, so a lane reads 4 consecutive entries a group.
+template <int BLK>
+struct LetterWindow {
+  int v[64 + BLK + 12];
+  // old: the letter of column tb - 63 + lane; cur: lane < BLK, of column tb + 1 + lane
+  __device__ __forceinline__ void put(int lane, int old, int cur) {
+    v[lane] = old;
+    if (BLK >= 64 || lane < BLK) v[64 + lane] = cur;
+  }
+  __device__ __forceinline__ void get(int lane, int g4, int (&c)[4]) const {
+    const int* p = v + 64 - lane + 4 * g4;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) c[u] = p[u];
+  }
+  __device__ __forceinline__ void clear_tail(int lane) {
+    if (lane < 12) v[64 + BLK + lane] = 0;
+  }
+};
+
+// What a lane keeps of its best cells.  Local: the best score, the group of 4 steps that first reached it (its first
+// column and its cells' values), and the largest score known anywhere in the band minus one.  Semi-global: the best
+// of row n.
+template <int R>
+struct BandBest {
+  int32_t bs = kNeg32;
+  int floor = -1;
+  int kj = INT32_MIN;
+  int32_t kv[4][R];
+  int32_t brow = 0;  // H(n, 0) = 0
+  int browj = 0;
+};
+
+// The first cell that holds a group's largest value v(u, r) + (r + u) * ge: by row and then by column, or (BY_COL) by
+// column and then by row.
+template <int R, bool BY_COL>
+__device__ __forceinline__ void first_best(const KParams& P, const int32_t (&v)[4][R], int& br, int& bu) {
+  int32_t best = INT32_MIN;
+  br = bu = 0;
+#pragma unroll
+  for (int a = 0; a < (BY_COL ? 4 : R); ++a)
+#pragma unroll
+    for (int b = 0; b < (BY_COL ? R : 4); ++b) {
+      const int r = BY_COL ? b : a, u = BY_COL ? a : b;
+      const int32_t x = v[u][r] + (r + u) * P.ge;
+      if (x > best) {
+        best = x;
+        br = r;
+        bu = u;
+      }
+    }
+}
+
+// After 4 steps of a local band (columns j0 .. j0 + 3, floor0: the floor of the lane's first row at column j0).
+// A group matters only where some cell beats the floor, and no cell does unless the sums below do: g of every
+// cell flows down into E~ of the lane's last row or is that row's g, and that row's F~ holds the g of its earlier
+// columns, so their maximum is at least every g of the group; a cell that beats the floor has
+// g > floor0 + floor + go.  With a linear gap the last cell is itself at least every cell.  That costs 4 issue
+// slots for 16 cells; comparing each row's maximum took 12.
+// Where the test passes, the exact best of the group is the largest of the anti-diagonals' maxima (whose cells share
+// a bias).  A lane that improves keeps the group's values, 16 selects; its cell is looked up at the band's end.
+// One long pair's bands improve in a hundred groups or more where they meet the alignment's diagonal, and every step a
+// band spends there delays each band below it: looking the cell up at once took 45.5 ms on 262144^2 related DNA.
+template <bool AFFINE, int R>
+__device__ __forceinline__ void track_local(const KParams& P, const BandLane<R>& L, const BandGroup<R>& G, int floor0,
+                                            int j0, bool flip, BandBest<R>& B) {
+  static_assert(R == 4, "the anti-diagonals of a 4 x 4 group");
+  int x;
+  if (AFFINE)
+    x = max(max3i(max3i(G.oe[0], G.oe[1], G.oe[2]), G.oe[3], L.f[R - 1]), L.g[R - 1]);
+  else
+    x = G.v[3][R - 1];
+  if (__builtin_amdgcn_ballot_w64(x - floor0 > B.floor + P.go) == 0) return;
+  const auto& v = G.v;
+  const int t1 = max(v[0][1], v[1][0]), t2 = max3i(v[0][2], v[1][1], v[2][0]);
+  const int t3 = max(max3i(v[0][3], v[1][2], v[2][1]), v[3][0]);
+  const int t4 = max3i(v[1][3], v[2][2], v[3][1]), t5 = max(v[2][3], v[3][2]);
+  int32_t mk = max3i(v[0][0], t1 + P.ge, t2 + 2 * P.ge);
+  mk = max3i(mk, t3 + 3 * P.ge, t4 + 4 * P.ge);
+  mk = max3i(mk, t5 + 5 * P.ge, v[3][3] + 6 * P.ge);
+  mk -= floor0 + P.go;
+  const unsigned long long over = __builtin_amdgcn_ballot_w64(mk > B.floor);
+  if (over == 0) return;
+  unsigned long long up = over & __builtin_amdgcn_ballot_w64(mk > B.bs);
+  // an equal cell replaces the lane's where its row is smaller (of a flipped pair, whose rows are the call's columns,
+  // never: its column is larger)
+  unsigned long long tie = over & __builtin_amdgcn_ballot_w64(mk == B.bs);
+  if (tie && !flip) {
+    int r1, u1, r0, u0;
+    first_best<R, false>(P, v, r1, u1);
+    first_best<R, false>(P, B.kv, r0, u0);
+    up |= tie & __builtin_amdgcn_ballot_w64(r1 < r0);
+  }
+  if (up == 0) return;
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) B.kv[u][r] = mask_select(up, v[u][r], B.kv[u][r]);
+  B.kj = mask_select(up, j0, B.kj);
+  B.bs = mask_select(up, mk, B.bs);
+  // one lane's new best raises the floor of the whole band at once
+  B.floor = max(B.floor, __builtin_amdgcn_readlane(mk, (int)__builtin_ctzll(up)) - 1);
+}
+
+// The kept group's first best cell: its row among the lane's and its column (-1: none kept).
+template <int R>
+__device__ __forceinline__ void resolve_kept(const KParams& P, const BandBest<R>& B, bool flip, int& br, int& bj) {
+  br = bj = -1;
+  if (B.kj == INT32_MIN) return;
+  int u;
+  if (flip)
+    first_best<R, true>(P, B.kv, br, u);
+  else
+    first_best<R, false>(P, B.kv, br, u);
+  bj = B.kj + u;
+}
+
+// After 4 steps of the semi-global band that holds row n (rn: its index among the lane's rows, elsewhere outside
+// 0 .. R - 1): that row's cells in columns 1..m.  As above, the row's F~ and last g (linear: its last cell) bound the
+// group's cells, so most groups cost a maximum and a select per row.
+template <bool AFFINE, int R>
+__device__ __forceinline__ void track_last_row(const KParams& P, const BandLane<R>& L, const BandGroup<R>& G, int floor0,
+                                               int m, int rn, int j0, BandBest<R>& B) {
+  static_assert(R == 4, "a row is picked by two bits of its index");
+  const unsigned long long b0 = __builtin_amdgcn_ballot_w64(rn & 1), b1 = __builtin_amdgcn_ballot_w64(rn & 2);
+  auto pick = [&](int x0, int x1, int x2, int x3) {
+    return mask_select(b1, mask_select(b0, x3, x2), mask_select(b0, x1, x0));
+  };
+  int last[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) last[r] = AFFINE ? max(L.f[r], L.g[r]) : L.h[r];
+  const int y = pick(last[0], last[1], last[2], last[3]);
+  const bool mine = rn >= 0 && rn < R;
+  if (__builtin_amdgcn_ballot_w64(mine && y - floor0 + rn * P.ge > B.brow + P.go) == 0) return;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int hn = pick(G.v[u][0], G.v[u][1], G.v[u][2], G.v[u][3]);
+    const int j = j0 + u;
+    const int sc = hn - P.go - floor0 + (rn + u) * P.ge;
+    if (mine && j >= 1 && j <= m && sc > B.brow) {
+      B.brow = sc;
+      B.browj = j;
+    }
+  }
+}
+
+// The start of a band: a lane's row letters (kPad past the end), profile, column 0 and empty bests.
+template <int MODE, int PROF, bool FA, int R>
+__device__ __forceinline__ void band_start(const KParams& P, const uint32_t* sig2, const uint8_t* __restrict__ q, int n, bool flip, int irow0,
+                                           int lane, uint32_t* __restrict__ lp, int (&prof)[R], BandLane<R>& L,
+                                           BandBest<R>& B, bool& bad) {
+  int rowc[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int i = irow0 + r + 1;
+    int c = kPad;
+    if (i <= n) {
+      c = q[i - 1];
+      if (c >= P.alphabet) {
+        bad = true;
+        c = kPad;
+      }
+    }
+    rowc[r] = c;
+  }
+  band_profile<PROF, R>(P, sig2, rowc, flip, prof, lp);
+  // A local lane also runs its columns before the first: they hold the floor, which is column 0's value.
+  const int jstart = MODE == ALN_LOCAL ? -lane : 0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    L.h[r] = border_h<MODE, FA>(P, irow0 + r + 1, jstart);
+    L.g[r] = lane_add<FA>(L.h[r], P.go, P.fgo);
+    L.f[r] = lane_neg<FA>();
+    for (int u = 0; u < 4; ++u) B.kv[u][r] = 0;
+  }
+  L.diag = border_h<MODE, FA>(P, irow0, jstart);
+  L.bot_h = L.h[R - 1];
+  L.bot_e = lane_neg<FA>();
+  L.floor0 = lane_zero<FA>() - (irow0 + 1 + 1 - lane) * P.ge;
+}
+
+// The band's optimum in (score, i, j) order over the lane's rows, then across the wave.
+template <int MODE, bool FA, int R>
+__device__ __forceinline__ int4 band_optimum(const KParams& P, const BandLane<R>& L, const BandBest<R>& B, int n,
+                                             int m, bool flip, bool last_band, int irow0, bool bad, bool failed) {
+  int bs = kNeg32, bi = 0, bjj = 0;
+  const int rn = n - 1 - irow0;
+  int br = -1, bj = -1;
+  if (MODE == ALN_LOCAL) resolve_kept<R>(P, B, flip, br, bj);
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int i = irow0 + r + 1;
+    if (i > n) continue;
+    int sc = 0, jj = 0;
+    bool cand = false;
+    if (MODE == ALN_LOCAL) {
+      sc = B.bs;
+      jj = bj;
+      cand = sc > 0 && r == br;
+    } else {
+      sc = L.h[r] - lane_zero<FA>() + (i + m) * P.ge;  // H(i, m): last-column candidate; row n is handled below
+      jj = m;
+      cand = MODE == ALN_SEMIGLOBAL ? i < n : i == n;
+    }
+    // a flipped pair's cell (i, jj) is the call's cell (jj, i)
+    const int ci = flip ? jj : i, cj = flip ? i : jj;
+    if (cand && better(sc, ci, cj, bs, bi, bjj)) {
+      bs = sc;
+      bi = ci;
+      bjj = cj;
+    }
+  }
+  if (MODE == ALN_SEMIGLOBAL && last_band && rn >= 0 && rn < R) {
+    // row n: (n, 0) with H = 0 first, then its running maximum over j in column order
+    const int ci = flip ? B.browj : n, cj = flip ? n : B.browj;
+    if (better(B.brow, ci, cj, bs, bi, bjj)) {
+      bs = B.brow;
+      bi = ci;
+      bjj = cj;
+    }
+  }
+  for (int o = 32; o >= 1; o >>= 1) {
+    const int s2 = __shfl_xor(bs, o, 64), i2 = __shfl_xor(bi, o, 64), j2 = __shfl_xor(bjj, o, 64);
+    if (better(s2, i2, j2, bs, bi, bjj)) {
+      bs = s2;
+      bi = i2;
+      bjj = j2;
+    }
+  }
+  return make_int4(bs, bi, bjj, (__any(bad) ? 1 : 0) | (failed ? 2 : 0));
+}
+
+// Fills the substitution scores sigma - 2 ge in LDS: the byte table, or for kProfTable the 32-bit table by (query
+// letter, subject letter).
+template <int PROF>
+__device__ __forceinline__ void fill_table(const KParams& P, int32_t* tab, uint32_t* sig2) {
+  if (PROF != kProfTable) {
+    fill_score_bytes(P, sig2);
+    return;
+  }
   for (int k = threadIdx.x; k < kTab * kTab; k += blockDim.x) {
     const int a = k / kTab, b = k % kTab;
-    tab[k] = (a >= P.alphabet || b >= P.alphabet) ? -kBig32 : (int32_t)P.sig[a * kMaxAlphabet + b] - P.ge;
+    tab[k] = (a >= P.alphabet || b >= P.alphabet) ? -kBig32 : (int32_t)P.sig[a * kMaxAlphabet + b] - 2 * P.ge;
   }
+}
+
+// The first ng of a block's groups of 4 steps.  A group's inputs are read from LDS while the group before runs (its
+// letters one group earlier still where they lead to profile words), so that no group waits for LDS.
+template <int PROF, int R, int NG, typename Window, typename Rows, typename Run>
+__device__ __forceinline__ void run_block(const Window& lett, const uint32_t* lp, int lane, int ng, Rows load_rows,
+                                          Run run) {
+  BandIn<R> A, C;
+  lett.get(lane, 0, A.vc);
+  load_rows(0, A);
+  if (PROF == kProfLane) lett.get(lane, 1, C.vc);
+  load_words<PROF, R>(lp, A);
+  for (int g4 = 0; g4 < ng; g4 += 2) {
+    load_rows(g4 + 1, C);
+    if (PROF == kProfLane) {
+      load_words<PROF, R>(lp, C);
+      lett.get(lane, g4 + 2, A.vc);
+    } else {
+      lett.get(lane, g4 + 1, C.vc);
+    }
+    run(g4, A);
+    if (g4 + 1 >= ng) break;
+    load_rows(g4 + 2, A);
+    if (PROF == kProfLane) {
+      load_words<PROF, R>(lp, A);
+      lett.get(lane, g4 + 3, C.vc);
+    } else {
+      lett.get(lane, g4 + 2, A.vc);
+    }
+    run(g4 + 1, C);
+  }
+}
+
+// Bands on their own (one wave per band, hand-offs through HBM), handed out level by level (wf_order_kernel).
+// The recurrence is band.h's.  A wave's stage holds its top-row inputs of 64 steps, H~ and E~ of column j at
+// (j - 1) & 63; lane 63 writes its bottom row into the slots just consumed, a column late so that 4 columns are
+// one aligned store: after the block's step t the slots hold columns up to t - 62.
+template <int MODE, bool AFFINE, int PROF, bool TB, bool FA, int R>
+__global__ __launch_bounds__(kWfBlockAlone, 4) void wf_i32_kernel(const KParams P, const uint8_t* __restrict__ Q,
+                                                          const uint8_t* __restrict__ S, WfWs W) {
+  static_assert(PROF != kProfLane || R == 4, "a lane profile word holds 4 rows");
+  __shared__ int32_t tab[PROF == kProfTable ? kTab * kTab : 1];
+  __shared__ int4 stage[kWfWavesPerBlock][2][16];
+  __shared__ LetterWindow<64> letters[kWfWavesPerBlock];
+  extern __shared__ uint32_t lprof[];  // kProfLane: [wave][letter][lane], alphabet letters and the pad letter
+  __shared__ uint32_t sig2[PROF == kProfTable ? 1 : kScoreWords];
+  fill_table<PROF>(P, tab, sig2);
   __syncthreads();
   constexpr int BH = 64 * R;
   const int lane = threadIdx.x & 63;
   const int wib = threadIdx.x >> 6;
   int* st_h = reinterpret_cast<int*>(&stage[wib][0][0]);
   int* st_e = reinterpret_cast<int*>(&stage[wib][1][0]);
-  int* st_c = reinterpret_cast<int*>(&stage[wib][2][0]);
-  const int32_t go = P.go, ge = P.ge, goe = P.goe;
+  LetterWindow<64>& lett = letters[wib];
+  uint32_t* __restrict__ lp = lprof + (PROF == kProfLane ? wib * (P.alphabet + 1) * 64 + lane : 0);
   const int np = *W.n_pairs;
   const int64_t n_items = *W.n_items;
 
+  // A batch whose pairs all have one band needs no ticket: no band waits on another and they come largest first, so
+  // the waves take them in turn.  One ticket counter serves an atomic every 38 ns or so: 100,003 one-band pairs took
+  // 3.9 ms whatever the bands cost.
+  const bool in_turn = W.lv[0] <= 1;
+  int64_t turn = (int64_t)blockIdx.x * kWfWavesPerBlock + wib;
   for (;;) {
-    int64_t t = 0;
-    if (lane == 0) t = (int64_t)atomicAdd(reinterpret_cast<unsigned long long*>(W.ticket), 1ull);
-    t = __shfl(t, 0, 64);
+    // The whole wave comes back here before lane 0 takes the next ticket.  Without a convergent operation in this
+    // block the compiler may join lane 0's store at the end of a band with its atomic below and send the other
+    // lanes straight to the shuffle, which then reads an inactive lane: they relax item 0 for ever.
+    __builtin_amdgcn_wave_barrier();
+    int64_t t = turn;
+    if (!in_turn) {
+      t = 0;
+      if (lane == 0) t = (int64_t)atomicAdd(reinterpret_cast<unsigned long long*>(W.ticket), 1ull);
+      t = __shfl(t, 0, 64);
+    }
+    turn += (int64_t)gridDim.x * kWfWavesPerBlock;
     if (t >= n_items) break;
     if (__hip_atomic_load(W.error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
     t = W.order[t];  // the item (pair-major band index) this ticket hands out
     const WfPair pr = W.pairs[np == 1 ? 0 : W.item_pair[t]];
-    const int b = (int)(t - pr.item0);
-    const int n = pr.n, m = pr.m, nb = pr.nb;
+    const int b = __builtin_amdgcn_readfirstlane((int)(t - pr.item0));
+    const int n = __builtin_amdgcn_readfirstlane(pr.n), m = __builtin_amdgcn_readfirstlane(pr.m);
+    const int nb = __builtin_amdgcn_readfirstlane(pr.nb);
     // rows come from the query array, columns from the subject array, or the reverse when flipped
-    const bool flip = pr.flip != 0;
+    const bool flip = __builtin_amdgcn_readfirstlane(pr.flip) != 0;
     const uint8_t* __restrict__ q = (flip ? S : Q) + pr.q_off;
     const uint8_t* __restrict__ s = (flip ? Q : S) + pr.s_off;
     const int64_t ld = (int64_t)m + 1;
-    // sigma - ge of a (row letter, column letter) pair, taken in the call's (query, subject) order
-    auto sig_rc = [&](int cr, int cc) -> int { return flip ? tab[cc * kTab + cr] : tab[cr * kTab + cc]; };
 
-    const int i0 = b * BH;
-    int prof[R];  // kProfReg: 4 bytes sigma - ge against letters 0..3; kProfTable: table offset of the letter
-    int32_t hl[R], f[R], bv[R], nu[R];
-    int bj[R];
-    int rowc[R];
+    const int i0 = b * BH, irow0 = i0 + lane * R;
+    int prof[R];
+    BandLane<R> L;
+    BandBest<R> B;
     bool bad = false;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int i = i0 + lane * R + r + 1;
-      int c = kPad;
-      if (i <= n) {
-        c = q[i - 1];
-        if (c >= P.alphabet) {
-          bad = true;
-          c = kPad;
-        }
-      }
-      rowc[r] = c;
-      if (PROF == kProfReg) {
-        uint32_t w = 0;
-        for (int a = 0; a < 4; ++a) {
-          const int v = (c < P.alphabet && a < P.alphabet) ? sig_rc(c, a) : -128;
-          w |= ((uint32_t)(v & 0xff)) << (8 * a);
-        }
-        prof[r] = (int)w;
-      } else if (PROF == kProfTable) {
-        prof[r] = flip ? c : c * kTab;  // the table is indexed [query letter][subject letter]
-      } else {
-        prof[r] = 0;
-      }
-      hl[r] = (MODE == ALN_GLOBAL) ? go : -i * ge;  // Hb(i, 0)
-      f[r] = kNeg32;
-      nu[r] = -i * ge;                                // local floor: H = 0
-      bv[r] = kNeg32;
-      bj[r] = 0;
-    }
-    uint32_t* __restrict__ lp = lprof + (PROF == kProfLane ? wib * P.alphabet * 64 + lane : 0);
-    if (PROF == kProfLane) {
-      // this lane's word per column letter; each lane reads only its own words, so no barrier
-      for (int a = 0; a < P.alphabet; ++a) {
-        uint32_t w = 0;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const int v = rowc[r] < P.alphabet ? sig_rc(rowc[r], a) : -128;
-          w |= ((uint32_t)(v & 0xff)) << (8 * r);
-        }
-        lp[a * 64] = w;
-      }
-    }
-    const int irow0 = i0 + lane * R;  // the row just above this lane's first row
-    int32_t diag = (MODE == ALN_GLOBAL) ? (irow0 > 0 ? go : 0) : -irow0 * ge;  // Hb(irow0, 0)
+    band_start<MODE, PROF, FA, R>(P, sig2, q, n, flip, irow0, lane, lp, prof, L, B, bad);
     uint16_t* __restrict__ codes = TB ? W.codes + pr.code_off + (size_t)(b * 64 + lane) * (size_t)m : nullptr;
-    int32_t bot_h = 0, bot_e = kNeg32, cur_c = 0, out_h = 0, out_e = 0;
-    // semi-global: the band holding row n tracks row n's running maximum
     const bool last_band = (b == nb - 1);
-    int32_t brow = -n * ge;  // Hb(n, 0), i.e. H(n, 0) = 0
-    int browj = 0;
     const int rn = n - 1 - irow0;  // index of row n among this lane's rows
-
     int2* __restrict__ prev = W.rows + pr.row_off + (int64_t)((b + 1) & 1) * ld;
     int2* __restrict__ cur = W.rows + pr.row_off + (int64_t)(b & 1) * ld;
     bool failed = false;
 
     int seen = 0;  // columns of the previous band known to be published
     constexpr int BLK = 64;
+    // letters are loaded one block ahead; those of columns before the first are pad letters
+    int c_next = 1 + lane <= m ? (int)s[lane] : -1;
+    int c_idx = letter_index<PROF, R>(P, -1, flip, bad);
+    lett.clear_tail(lane);
 
-    const int steps = m + 63;
+    const int steps = m + 64;  // lane 63's column m leaves at step m + 63
     for (int tb = 0; tb < steps; tb += BLK) {
       // lane-0 inputs for steps tb..tb+63 (columns tb+1..tb+64)
       const int col_in = tb + 1 + lane;
-      int sreg = 0;
-      if (col_in <= m) {
-        sreg = s[col_in - 1];
-        if (sreg >= P.alphabet) {
-          bad = true;
-          sreg = PROF == kProfTable ? kPad : 0;
-        }
-      }
-      if (PROF == kProfReg) sreg *= 8;
-      if (PROF == kProfLane) sreg *= 64;
-      if (PROF == kProfTable && flip) sreg *= kTab;
-      int32_t th, te;
+      const int c_old = c_idx;
+      c_idx = letter_index<PROF, R>(P, c_next, flip, bad);
+      lett.put(lane, c_old, c_idx);
+      c_next = col_in + BLK <= m ? (int)s[col_in + BLK - 1] : -1;
+      int32_t th = lane_neg<FA>(), te = lane_neg<FA>();
       if (b == 0) {
-        th = (MODE == ALN_GLOBAL) ? go + col_in * ge : 0;
-        te = kNeg32;
+        if (col_in <= m) th = border_h<MODE, FA>(P, 0, col_in);
       } else {
         const int need = min(tb + BLK, m);
         if (seen < need) {
@@ -287,8 +511,6 @@ __global__ __launch_bounds__(kWfBlockAlone) void wf_i32_kernel(const KParams P, 
           asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
           seen = v;
         }
-        th = 0;
-        te = kNeg32;
         if (col_in <= m) {
           const long long pv = __hip_atomic_load(reinterpret_cast<long long*>(prev + col_in), __ATOMIC_RELAXED,
                                                  __HIP_MEMORY_SCOPE_AGENT);
@@ -296,87 +518,45 @@ __global__ __launch_bounds__(kWfBlockAlone) void wf_i32_kernel(const KParams P, 
           te = (int32_t)(pv >> 32);
         }
       }
-      if (MODE == ALN_LOCAL) raise_local_floors<R>(bv, nu, th, i0, ge);
+      if (MODE == ALN_LOCAL)
+        B.floor = raise_local_floor(B.bs, col_in <= m ? th - lane_zero<FA>() + (i0 + col_in) * P.ge : 0);
       st_h[lane] = th;
       st_e[lane] = te;
-      st_c[lane] = sreg;
-      // One step: lane l relaxes column j = t - l + 1 for its R rows.
-      auto step = [&](int t, int in_top_h, int in_top_e, int in_top_c, auto checked, int32_t* hk) {
-        const int j = t - lane + 1;
-        const int in_h = dpp_shr1(in_top_h, bot_h);
-        const int in_e = dpp_shr1(in_top_e, bot_e);
-        const int in_c = dpp_shr1(in_top_c, cur_c);
-        cur_c = in_c;
-        if (!decltype(checked)::value || (j >= 1 && j <= m)) {
-          int32_t hd = diag, hup = in_h, eup = in_e;
-          int32_t hn = 0;
-          uint32_t word = 0;
-          const int pw = PROF == kProfLane ? (int)lp[in_c] : 0;
-          // local affine score-only bands fold the floor into E (band.h)
-          constexpr bool kFloorE = MODE == ALN_LOCAL && AFFINE && !TB;
-          band_column<MODE, AFFINE, PROF, TB, decltype(checked)::value, R, true, kFloorE>(
-              tab, prof, in_c, pw, go, ge, goe, nu, hl, f, bv, bj, hk, j, rn, hd, hup, eup, hn, word);
-          if (TB) codes[j - 1] = (uint16_t)word;
-          if (MODE == ALN_SEMIGLOBAL && last_band && rn >= 0 && rn < R && hn > brow) {
-            brow = hn;
-            browj = j;
-          }
-          bot_h = hup;
-          bot_e = eup;
-          diag = in_h;
-        }
-        out_h = dpp_shl1(bot_h, out_h);
-        out_e = dpp_shl1(bot_e, out_e);
+      auto load_rows = [&](int g4, BandIn<R>& I) __attribute__((always_inline)) {
+        const int4 h4 = reinterpret_cast<const int4*>(st_h)[g4 & 15];
+        const int4 e4 = reinterpret_cast<const int4*>(st_e)[g4 & 15];
+        I.vh[0] = h4.x, I.vh[1] = h4.y, I.vh[2] = h4.z, I.vh[3] = h4.w;
+        I.ve[0] = e4.x, I.ve[1] = e4.y, I.ve[2] = e4.z, I.ve[3] = e4.w;
       };
-      for (int g4 = 0; g4 < BLK / 4; ++g4) {
+      auto run = [&](int g4, const BandIn<R>& I) __attribute__((always_inline)) {
         const int t0 = tb + 4 * g4;
-        const int4 vh = reinterpret_cast<const int4*>(st_h)[g4];
-        const int4 ve = reinterpret_cast<const int4*>(st_e)[g4];
-        const int4 vc = reinterpret_cast<const int4*>(st_c)[g4];
-        if (t0 >= 63 && t0 + 3 < m) {
-          // every lane is inside the matrix: no range test; local optima are tracked per 4 steps
-          int32_t hk[4][R];
-          step(t0, vh.x, ve.x, vc.x, std::false_type(), hk[0]);
-          step(t0 + 1, vh.y, ve.y, vc.y, std::false_type(), hk[1]);
-          step(t0 + 2, vh.z, ve.z, vc.z, std::false_type(), hk[2]);
-          step(t0 + 3, vh.w, ve.w, vc.w, std::false_type(), hk[3]);
-          if (MODE == ALN_LOCAL) {
-            int32_t mk[R];
-            bool imp = false;
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-              mk[r] = max(max(hk[0][r], hk[1][r]), max(hk[2][r], hk[3][r]));
-              imp |= mk[r] > bv[r];
-            }
-            if (imp) {
-              // a row that beat its best takes the group's maximum at the first of the 4 steps that
-              // reached it, as a cell-by-cell strict update would
-#pragma unroll
-              for (int r = 0; r < R; ++r) {
-                int k = hk[2][r] == mk[r] ? 2 : 3;
-                k = hk[1][r] == mk[r] ? 1 : k;
-                k = hk[0][r] == mk[r] ? 0 : k;
-                bj[r] = lane_select(mk[r] > bv[r], t0 - lane + 1 + k, bj[r]);
-                bv[r] = max(bv[r], mk[r]);
-              }
-            }
-          }
-        } else {
-          step(t0, vh.x, ve.x, vc.x, std::true_type(), nullptr);
-          step(t0 + 1, vh.y, ve.y, vc.y, std::true_type(), nullptr);
-          step(t0 + 2, vh.z, ve.z, vc.z, std::true_type(), nullptr);
-          step(t0 + 3, vh.w, ve.w, vc.w, std::true_type(), nullptr);
+        const int j0 = t0 - lane + 1;
+        const int ph = L.bot_h, pe = L.bot_e, floor0 = L.floor0;
+        BandGroup<R> G;
+        const bool inside = t0 >= 63 && t0 + 3 < m;
+        // local cells outside the matrix are harmless (raise_local_floor); the others keep their state there
+        if (MODE == ALN_LOCAL || inside)
+          band_group<MODE, AFFINE, PROF, TB, FA, R, false>(P, tab, prof, I, j0, m, L, G, [](int) {});
+        else
+          band_group<MODE, AFFINE, PROF, TB, FA, R, true>(P, tab, prof, I, j0, m, L, G, [](int) {});
+        if (TB) store_codes<R>(G, codes, j0, m, inside);
+        if constexpr (MODE == ALN_LOCAL) track_local<AFFINE, R>(P, L, G, floor0, j0, flip, B);
+        if (MODE == ALN_SEMIGLOBAL && last_band) track_last_row<AFFINE, R>(P, L, G, floor0, m, rn, j0, B);
+        if (lane == 63) {
+          reinterpret_cast<int4*>(st_h)[g4] = make_int4(ph, G.oh[0], G.oh[1], G.oh[2]);
+          reinterpret_cast<int4*>(st_e)[g4] = make_int4(pe, G.oe[0], G.oe[1], G.oe[2]);
         }
-      }
-      // lane u now holds lane 63's outputs of step tb+u, i.e. column tb+u-62
+      };
+      run_block<PROF, R, BLK / 4>(lett, lp, lane, min(BLK / 4, (steps - tb + 3) / 4), load_rows, run);
+      // slot u now holds lane 63's column tb + u - 63
       if (b + 1 < nb) {
-        const int col_out = tb + lane - 62;
+        const int col_out = tb + lane - 63;
         if (col_out >= 1 && col_out <= m) {
-          const long long pv = ((long long)(uint32_t)out_h) | ((long long)out_e << 32);
+          const long long pv = ((long long)(uint32_t)st_h[lane]) | ((long long)st_e[lane] << 32);
           __hip_atomic_store(reinterpret_cast<long long*>(cur + col_out), pv, __ATOMIC_RELAXED,
                              __HIP_MEMORY_SCOPE_AGENT);
         }
-        const int published = min(tb + 1, m);
+        const int published = min(tb, m);
         // Publication: the row stores above are device-coherent (sc1) atomics; waiting for their
         // completion before the sc1 flag store orders them without an L2 write-back (an agent-scope
         // release fence would emit buffer_wbl2 on every publication).
@@ -385,103 +565,57 @@ __global__ __launch_bounds__(kWfBlockAlone) void wf_i32_kernel(const KParams P, 
           __hip_atomic_store(W.flags + t, published, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     }
-    // band optimum: (score, i, j) over this lane's rows, then across the wave
-    int bs = kNeg32, bi = 0, bjj = 0;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int i = irow0 + r + 1;
-      if (i > n) continue;
-      int sc = 0, jj = 0;
-      bool cand = false;
-      if (MODE == ALN_LOCAL) {
-        sc = bv[r] + i * ge;
-        jj = bj[r];
-        cand = sc > 0;
-      } else if (MODE == ALN_SEMIGLOBAL) {
-        sc = hl[r] + i * ge;  // H(i, m): last-column candidate; row n is handled below
-        jj = m;
-        cand = (i < n);
-      } else {
-        sc = hl[r] + i * ge;
-        jj = m;
-        cand = (i == n);
-      }
-      // a flipped pair's cell (i, jj) is the call's cell (jj, i)
-      const int ci = flip ? jj : i, cj = flip ? i : jj;
-      if (cand && better(sc, ci, cj, bs, bi, bjj)) {
-        bs = sc;
-        bi = ci;
-        bjj = cj;
-      }
-    }
-    if (MODE == ALN_SEMIGLOBAL && last_band && rn >= 0 && rn < R) {
-      // row n: (n, 0) with H = 0 first, then its running maximum over j in column order
-      const int rowv = (browj > 0) ? brow + n * ge : 0;
-      const int ci = flip ? browj : n, cj = flip ? n : browj;
-      if (better(rowv, ci, cj, bs, bi, bjj)) {
-        bs = rowv;
-        bi = ci;
-        bjj = cj;
-      }
-    }
-    for (int o = 32; o >= 1; o >>= 1) {
-      const int s2 = __shfl_xor(bs, o, 64), i2 = __shfl_xor(bi, o, 64), j2 = __shfl_xor(bjj, o, 64);
-      if (better(s2, i2, j2, bs, bi, bjj)) {
-        bs = s2;
-        bi = i2;
-        bjj = j2;
-      }
-    }
-    const bool anybad = __any(bad);
-    if (lane == 0) W.band_res[t] = make_int4(bs, bi, bjj, (anybad ? 1 : 0) | (failed ? 2 : 0));
+    const int4 opt = band_optimum<MODE, FA, R>(P, L, B, n, m, flip, last_band, irow0, bad, failed);
+    if (lane == 0) W.band_res[t] = opt;
   }
 }
 
-// Bands in groups (workgroups of kWfWavesPerBlock bands and a courier), same recurrence.
-// Values are kept with a row bias: Hb(i,j) = H(i,j) - i*ge, and likewise E and F.  Then
-//   Eb(i,j) = max(Eb(i-1,j), Hb(i-1,j) + go)          (extension costs nothing: one add less)
-//   Fb(i,j) = max(Fb(i,j-1) + ge, Hb(i,j-1) + go + ge)
-//   Hb(i,j) = max(Hb(i-1,j-1) + sigma - ge, Eb, Fb [, -i*ge for local])
-// which is Eqs. (1), (4), (5) with every term shifted by the same per-row constant.
+// Bands in groups (workgroups of kWfWavesPerBlock bands and a courier), same recurrence.  A ring holds H~ and E~
+// of column j at (j - 1) mod kRing; a band reads its top row straight from its ring, 4 columns at a time, and lane
+// 63 writes the bottom row into the next ring as it goes, a column late so that 4 columns are one aligned store.
 // CKPT: also store checkpoints for a linear-space traceback (one pair, groups aligned with its bands):
 // every group's bottom row stays in its own row slot instead of two rotating ones, and every
-// kTileCols-th column's H and F of all rows go to W.ckcols.
-template <int MODE, bool AFFINE, int PROF, bool TB, int R, bool P16, bool CKPT, bool LAZY>
-__global__ __launch_bounds__(kWfBlock) void wf_i32_group_kernel(const KParams P, const uint8_t* __restrict__ Q,
+// kTileCols-th column's H~ and F~ of all rows go to W.ckcols.
+template <int MODE, bool AFFINE, int PROF, bool TB, bool FA, int R, bool P16, bool CKPT>
+__global__ __launch_bounds__(kWfBlock, CKPT ? 3 : 4) void wf_i32_group_kernel(const KParams P, const uint8_t* __restrict__ Q,
                                                           const uint8_t* __restrict__ S, WfWs W) {
   static_assert(PROF != kProfLane || R == 4, "a lane profile word holds 4 rows");
-  // sigma - ge by (query letter, subject letter); also the source of the byte profiles
-  __shared__ int32_t tab[kTab * kTab];
   constexpr int BLK = kBlkGrouped;
-  __shared__ int4 stage[kWfWavesPerBlock][3][BLK / 4];  // lane-0 inputs of BLK steps: H, E, letter
+  // packed bands: sigma - ge by (query letter, subject letter), the source of their profiles; kProfTable: sigma - 2 ge
+  __shared__ int32_t tab[P16 || PROF == kProfTable ? kTab * kTab : 1];
+  __shared__ uint32_t sig2[P16 || PROF == kProfTable ? 1 : kScoreWords];
+  __shared__ int4 stage[P16 ? kWfWavesPerBlock : 1][3][BLK / 4];  // packed bands: lane-0 inputs of BLK steps
+  __shared__ LetterWindow<BLK> letters[P16 ? 1 : kWfWavesPerBlock];
   // ring k carries the rows feeding compute wave k; ring kWfWavesPerBlock feeds the courier
-  __shared__ int2 ring[kWfWavesPerBlock + 1][kRing];
+  __shared__ int4 ring4[kWfWavesPerBlock + 1][2][kRing / 4];
   __shared__ int pub[kWfWavesPerBlock + 1];  // columns written into each ring
   __shared__ int con[kWfWavesPerBlock + 1];  // columns read out of each ring
   __shared__ long long s_t0;                 // first item of the group
   __shared__ int s_err;
-  extern __shared__ uint32_t lprof[];        // kProfLane: [wave][letter][lane], alphabet letters
+  extern __shared__ uint32_t lprof[];        // kProfLane: [wave][letter][lane], alphabet letters and the pad letter
   static_assert(!P16 || (MODE == ALN_LOCAL && (PROF == kProfReg || PROF == kProfLane) && !TB && R == 4),
                 "packed bands: local, score only, register or per-lane profiles");
   static_assert(!CKPT || (!TB && !P16 && R == 4), "checkpoints: 32-bit score-only bands");
-  static_assert(!LAZY || (MODE == ALN_LOCAL && !TB && !P16 && !CKPT), "kept groups: local 32-bit score-only bands");
   // packed bands: the upper half's bottom row (absolute H, E) on its way to the lower half
   __shared__ int2 dline[P16 ? kWfWavesPerBlock : 1][P16 ? kDelayRing : 1];
-  for (int k = threadIdx.x; k < kTab * kTab; k += blockDim.x) {
-    const int a = k / kTab, b = k % kTab;
-    tab[k] = (a >= P.alphabet || b >= P.alphabet) ? -kBig32 : (int32_t)P.sig[a * kMaxAlphabet + b] - P.ge;
+  if constexpr (P16) {
+    for (int k = threadIdx.x; k < kTab * kTab; k += blockDim.x) {
+      const int a = k / kTab, b = k % kTab;
+      tab[k] = (a >= P.alphabet || b >= P.alphabet) ? -kBig32 : (int32_t)P.sig[a * kMaxAlphabet + b] - P.ge;
+    }
+  } else {
+    fill_table<PROF>(P, tab, sig2);
   }
   __syncthreads();
   constexpr int BH = 64 * R;
   const int lane = threadIdx.x & 63;
   const int wib = threadIdx.x >> 6;
-  const int cw = wib < kWfWavesPerBlock ? wib : 0;  // the courier borrows wave 0's stage pointers
-  int* st_h = reinterpret_cast<int*>(&stage[cw][0][0]);
-  int* st_e = reinterpret_cast<int*>(&stage[cw][1][0]);
-  int* st_c = reinterpret_cast<int*>(&stage[cw][2][0]);
-  const int32_t go = P.go, ge = P.ge, goe = P.goe;
+  const int cw = wib < kWfWavesPerBlock ? wib : 0;  // the courier borrows wave 0's pointers
+  [[maybe_unused]] const int32_t go = P.go, ge = P.ge, goe = P.goe;
   const int np = *W.n_pairs;
   const int64_t n_items = *W.n_items;
+  auto ring_h = [&](int k) -> int* { return reinterpret_cast<int*>(&ring4[k][0][0]); };
+  auto ring_e = [&](int k) -> int* { return reinterpret_cast<int*>(&ring4[k][1][0]); };
 
   // Bounded waits.  A wave that gives up raises the group's and the launch's error flags and leaves
   // its band; every wave still meets the group's barriers, so the grid drains.
@@ -548,7 +682,8 @@ __global__ __launch_bounds__(kWfBlock) void wf_i32_group_kernel(const KParams P,
           if (col <= want) {
             const long long v = __hip_atomic_load(reinterpret_cast<const long long*>(src + col), __ATOMIC_RELAXED,
                                                   __HIP_MEMORY_SCOPE_AGENT);
-            ring[0][col % kRing] = make_int2((int32_t)(v & 0xffffffffll), (int32_t)(v >> 32));
+            ring_h(0)[(col - 1) % kRing] = (int32_t)(v & 0xffffffffll);
+            ring_e(0)[(col - 1) % kRing] = (int32_t)(v >> 32);
           }
           asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
           if (lane == 0) __hip_atomic_store(&pub[0], want, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -561,8 +696,8 @@ __global__ __launch_bounds__(kWfBlock) void wf_i32_group_kernel(const KParams P,
         if (__hip_atomic_load(&pub[kWfWavesPerBlock], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >= want) {
           const int col = out_done + 1 + lane;
           if (col <= want) {
-            const int2 v = ring[kWfWavesPerBlock][col % kRing];
-            const long long pv = ((long long)(uint32_t)v.x) | ((long long)v.y << 32);
+            const int vh = ring_h(kWfWavesPerBlock)[(col - 1) % kRing], ve = ring_e(kWfWavesPerBlock)[(col - 1) % kRing];
+            const long long pv = ((long long)(uint32_t)vh) | ((long long)ve << 32);
             __hip_atomic_store(reinterpret_cast<long long*>(dst + col), pv, __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
           }
@@ -598,8 +733,11 @@ __global__ __launch_bounds__(kWfBlock) void wf_i32_group_kernel(const KParams P,
   // scores at the block's first column, so every value of a block stays within a few thousand of its
   // offset (adjacent cells differ by at most max|sigma| + |go| + 2|ge|, which the host bounds).  The
   // band's inputs and outputs are absolute 32-bit rows, as for the 32-bit bands.
-  auto p16_band = [&](auto t_) {
+  [[maybe_unused]] auto p16_band = [&](auto t_) {
     const int64_t t = t_;
+    int* st_h = reinterpret_cast<int*>(&stage[cw][0][0]);
+    int* st_e = reinterpret_cast<int*>(&stage[cw][1][0]);
+    int* st_c = reinterpret_cast<int*>(&stage[cw][2][0]);
     const WfPair pr = W.pairs[np == 1 ? 0 : W.item_pair[t]];
     const int b = (int)(t - pr.item0);
     const int n = pr.n, m = pr.m, nb = pr.nb;
@@ -673,8 +811,7 @@ __global__ __launch_bounds__(kWfBlock) void wf_i32_group_kernel(const KParams P,
     int bot_h = 0, bot_e = pack16(kNeg16, kNeg16), cur_c = 0, out_h = 0, out_e = 0;
     const int go2 = pack16(go, go), ge2 = pack16(ge, ge), goe2 = pack16(goe, goe);
     bool failed = false;
-    int2* __restrict__ rin = ring[wib];
-    int2* __restrict__ rout = ring[wib + 1];
+    int *rin_h = ring_h(wib), *rin_e = ring_e(wib), *rout_h = ring_h(wib + 1), *rout_e = ring_e(wib + 1);
     int2* __restrict__ dl = dline[wib];
     const bool has_out = b + 1 < nb;
     auto letter_raw = [&](int col) -> int { return (col >= 1 && col <= m) ? (int)s[col - 1] : -1; };
@@ -704,9 +841,8 @@ __global__ __launch_bounds__(kWfBlock) void wf_i32_group_kernel(const KParams P,
           break;
         }
         if (lane < BLK && col0 <= m) {
-          const int2 v = rin[col0 % kRing];
-          th0 = v.x;
-          te0 = v.y;
+          th0 = rin_h[(col0 - 1) % kRing];
+          te0 = rin_e[(col0 - 1) % kRing];
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         if (lane == 0) __hip_atomic_store(&con[wib], need, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -733,7 +869,7 @@ __global__ __launch_bounds__(kWfBlock) void wf_i32_group_kernel(const KParams P,
         B1 = nB1;
       }
       {
-        // floors (see raise_local_floors): the best of both halves' top-row inputs and recorded optima
+        // floors (see raise_local_floor): the best of both halves' top-row inputs and recorded optima
         int v = max(th0 + i0 * ge, th1 + (i0 + HB) * ge);
 #pragma unroll
         for (int h = 0; h < 2; ++h)
@@ -871,8 +1007,10 @@ __global__ __launch_bounds__(kWfBlock) void wf_i32_group_kernel(const KParams P,
             failed = true;
             break;
           }
-          if (inw && cl >= 1 && cl <= m)
-            rout[cl % kRing] = make_int2(unrel16(hi16(out_h), B1), unrel16(hi16(out_e), B1));
+          if (inw && cl >= 1 && cl <= m) {
+            rout_h[(cl - 1) % kRing] = unrel16(hi16(out_h), B1);
+            rout_e[(cl - 1) % kRing] = unrel16(hi16(out_e), B1);
+          }
           asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
           if (lane == 0) __hip_atomic_store(&pub[wib + 1], hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
@@ -929,328 +1067,182 @@ __global__ __launch_bounds__(kWfBlock) void wf_i32_group_kernel(const KParams P,
     } else {
     const int64_t t = t0g + wib;
     const WfPair pr = W.pairs[np == 1 ? 0 : W.item_pair[t]];
-    const int b = (int)(t - pr.item0);
-    const int n = pr.n, m = pr.m, nb = pr.nb;
+    const int b = __builtin_amdgcn_readfirstlane((int)(t - pr.item0));
+    const int n = __builtin_amdgcn_readfirstlane(pr.n), m = __builtin_amdgcn_readfirstlane(pr.m);
+    const int nb = __builtin_amdgcn_readfirstlane(pr.nb);
     // rows come from the query array, columns from the subject array, or the reverse when flipped
-    const bool flip = pr.flip != 0;
+    const bool flip = __builtin_amdgcn_readfirstlane(pr.flip) != 0;
     const uint8_t* __restrict__ q = (flip ? S : Q) + pr.q_off;
     const uint8_t* __restrict__ s = (flip ? Q : S) + pr.s_off;
-    // sigma - ge of a (row letter, column letter) pair, taken in the call's (query, subject) order
-    auto sig_rc = [&](int cr, int cc) -> int { return flip ? tab[cc * kTab + cr] : tab[cr * kTab + cc]; };
 
-    const int i0 = b * BH;
-    int prof[R];  // kProfReg: 4 bytes sigma - ge against letters 0..3; kProfTable: table offset of the letter
-    int32_t hl[R], f[R], bv[R], nu[R];
-    int bj[R];
-    int rowc[R];
+    const int i0 = b * BH, irow0 = i0 + lane * R;
+    uint32_t* __restrict__ lp = lprof + (PROF == kProfLane ? cw * (P.alphabet + 1) * 64 + lane : 0);
+    LetterWindow<BLK>& lett = letters[cw];
+    int prof[R];
+    BandLane<R> L;
+    BandBest<R> B;
     bool bad = false;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int i = i0 + lane * R + r + 1;
-      int c = kPad;
-      if (i <= n) {
-        c = q[i - 1];
-        if (c >= P.alphabet) {
-          bad = true;
-          c = kPad;
-        }
-      }
-      rowc[r] = c;
-      if (PROF == kProfReg) {
-        uint32_t w = 0;
-        for (int a = 0; a < 4; ++a) {
-          const int v = (c < P.alphabet && a < P.alphabet) ? sig_rc(c, a) : -128;
-          w |= ((uint32_t)(v & 0xff)) << (8 * a);
-        }
-        prof[r] = (int)w;
-      } else if (PROF == kProfTable) {
-        prof[r] = flip ? c : c * kTab;  // the table is indexed [query letter][subject letter]
-      } else {
-        prof[r] = 0;
-      }
-      hl[r] = (MODE == ALN_GLOBAL) ? go : -i * ge;  // Hb(i, 0)
-      f[r] = kNeg32;
-      nu[r] = -i * ge;                                // local floor: H = 0
-      bv[r] = kNeg32;
-      bj[r] = 0;
-    }
-    uint32_t* __restrict__ lp = lprof + (PROF == kProfLane ? wib * P.alphabet * 64 + lane : 0);
-    if (PROF == kProfLane) {
-      // this lane's word per column letter; each lane reads only its own words, so no barrier
-      for (int a = 0; a < P.alphabet; ++a) {
-        uint32_t w = 0;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const int v = rowc[r] < P.alphabet ? sig_rc(rowc[r], a) : -128;
-          w |= ((uint32_t)(v & 0xff)) << (8 * r);
-        }
-        lp[a * 64] = w;
-      }
-    }
-    const int irow0 = i0 + lane * R;  // the row just above this lane's first row
-    int32_t diag = (MODE == ALN_GLOBAL) ? (irow0 > 0 ? go : 0) : -irow0 * ge;  // Hb(irow0, 0)
+    band_start<MODE, PROF, FA, R>(P, sig2, q, n, flip, irow0, lane, lp, prof, L, B, bad);
     uint16_t* __restrict__ codes = TB ? W.codes + pr.code_off + (size_t)(b * 64 + lane) * (size_t)m : nullptr;
-    int32_t bot_h = 0, bot_e = kNeg32, cur_c = 0, out_h = 0, out_e = 0;
-    // semi-global: the band holding row n tracks row n's running maximum
     const bool last_band = (b == nb - 1);
-    int32_t brow = -n * ge;  // Hb(n, 0), i.e. H(n, 0) = 0
-    int browj = 0;
     const int rn = n - 1 - irow0;  // index of row n among this lane's rows
-
     bool failed = false;
-    int2* __restrict__ rin = ring[wib];       // rows of the band above (b > 0)
-    int2* __restrict__ rout = ring[wib + 1];  // this band's bottom row, for the band below
+    int *rin_h = ring_h(cw), *rin_e = ring_e(cw);           // row of the band above (b > 0)
+    int *rout_h = ring_h(cw + 1), *rout_e = ring_e(cw + 1);  // this band's bottom row, for the band below
     const bool has_out = b + 1 < nb;
-    // Subject letters are loaded one block ahead and turned into profile indices only when their block
-    // starts, so the load's latency hides behind a block of steps: the raw letter of column col (-1 past
-    // the end), then the index the profile kind uses (0 past the end).
-    auto letter_raw = [&](int col) -> int { return col <= m ? (int)s[col - 1] : -1; };
-    auto letter_idx = [&](int c) -> int {
-      if (c < 0) return 0;
-      if (c >= P.alphabet) {
-        bad = true;
-        c = PROF == kProfTable ? kPad : 0;
-      }
-      if (PROF == kProfReg) c *= 8;
-      if (PROF == kProfLane) c *= 64;
-      if (PROF == kProfTable && flip) c *= kTab;
-      return c;
-    };
-    int c_next = lane < BLK ? letter_raw(1 + lane) : -1;
+    // The letters of columns tb - 31 .. tb + 32 are loaded one block ahead and turned into profile indices only when
+    // their block starts, so the load's latency hides behind a block of steps; -1 outside the subject.
+    auto letter_at = [&](int col) -> int { return col >= 1 && col <= m ? (int)s[col - 1] : -1; };
+    int c_next = letter_at(lane - 31);
+    int c_idx = letter_index<PROF, R>(P, -1, flip, bad);
+    lett.clear_tail(lane);
 
-    // LAZY (local, score-only): a row that beats its best in a group of 4 steps keeps that group (its
-    // first step sg and its 4 H values sv) instead of finding the first maximal step at once; resolve()
-    // turns the kept group into the row's column before any cell-by-cell update and after the band's
-    // last step.  The result is the same (a later strict improvement replaces the kept group, as it
-    // would replace the column), and the improving groups -- hundreds per band where the bands meet
-    // the alignment's diagonal -- cost 20 selects instead of a search.  Every step a band spends there
-    // also delays each band below it, which is what the selects save.
-    int32_t sv[4][R];
-    int sg[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      sg[r] = -1;
-      sv[0][r] = sv[1][r] = sv[2][r] = sv[3][r] = 0;
-    }
-    auto resolve = [&]() {
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        if (sg[r] >= 0) {
-          const int32_t mx = max(max(sv[0][r], sv[1][r]), max(sv[2][r], sv[3][r]));
-          int k = sv[2][r] == mx ? 2 : 3;
-          k = sv[1][r] == mx ? 1 : k;
-          k = sv[0][r] == mx ? 0 : k;
-          bj[r] = sg[r] - lane + 1 + k;
-          sg[r] = -1;
-        }
-      }
-    };
-
-    const int steps = m + 63;
+    const int steps = m + 64;  // lane 63's column m leaves at step m + 63
     for (int tb = 0; tb < steps; tb += BLK) {
-      // lane-0 inputs for steps tb..tb+BLK-1 (columns tb+1..tb+BLK), held by lanes < BLK
       const int col_in = tb + 1 + lane;
-      const int sreg = letter_idx(c_next);
+      static_assert(BLK == 32, "a wave's lanes hold the letters of two blocks");
+      const int c_old = c_idx;  // columns tb - 63 .. tb
+      c_idx = letter_index<PROF, R>(P, c_next, flip, bad);
       // consume the previous block's load before issuing the next one: memory counters drain in order,
       // so waiting for the old letter must not also wait for the new load
-      asm volatile("" ::"v"(sreg) : "memory");
-      c_next = lane < BLK ? letter_raw(col_in + BLK) : -1;
-      // The band below's consumption, read together with the input counter: it only grows, so a value
-      // that already allows this block's output spares the wait at the block's end.
-      const int con_seen =
-          has_out ? __hip_atomic_load(&con[wib + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) : 0;
-      int32_t th = 0, te = kNeg32;
+      asm volatile("" ::"v"(c_idx) : "memory");
+      c_next = letter_at(tb + 1 + lane);  // columns (tb + 32) - 31 ..
+      lett.v[lane] = c_old;
+      if (lane >= 32) lett.v[32 + lane] = c_idx;  // columns tb + 1 .. tb + 32
+      const int hi = tb + BLK - 64;  // columns the block's outputs complete (the last ones may lie past m)
+      // the band below has read what this block's outputs overwrite
+      if (has_out && !lds_wait_ge(&con[cw + 1], hi - kRing)) {
+        failed = true;
+        break;
+      }
+      const int need = min(tb + BLK, m);
+      int32_t th = lane_neg<FA>();
       if (b == 0) {
-        th = (MODE == ALN_GLOBAL) ? go + col_in * ge : 0;
+        // the ring above is nobody's: this band writes row 0 there itself
+        if (lane < BLK) {
+          th = border_h<MODE, FA>(P, 0, col_in);
+          rin_h[(col_in - 1) % kRing] = th;
+          rin_e[(col_in - 1) % kRing] = lane_neg<FA>();
+        }
       } else {
-        const int need = min(tb + BLK, m);
-        if (!lds_wait_ge(&pub[wib], need)) {
+        if (!lds_wait_ge(&pub[cw], need)) {
           failed = true;
           break;
         }
-        if (lane < BLK && col_in <= m) {
-          const int2 v = rin[col_in % kRing];
-          th = v.x;
-          te = v.y;
-        }
-        // the ring reads are complete before their slots are released to the band above
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        if (lane == 0) __hip_atomic_store(&con[wib], need, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (lane < BLK && col_in <= m) th = rin_h[(col_in - 1) % kRing];
       }
-      if (MODE == ALN_LOCAL) raise_local_floors<R>(bv, nu, th, i0, ge);
-      if (lane < BLK) {
-        st_h[lane] = th;
-        st_e[lane] = te;
-        st_c[lane] = sreg;
-      }
-      // One step: lane l relaxes column j = t - l + 1 for its R rows.  With ckc (checkpointing, wave-uniform)
-      // a lane whose column is a multiple of kTileCols also stores its rows' H and F there.
-      auto step = [&](int t, int in_top_h, int in_top_e, int in_top_c, auto checked, int32_t* hk, bool ckc) {
-        const int j = t - lane + 1;
-        const int in_h = dpp_shr1(in_top_h, bot_h);
-        const int in_e = dpp_shr1(in_top_e, bot_e);
-        const int in_c = dpp_shr1(in_top_c, cur_c);
-        cur_c = in_c;
-        if (!decltype(checked)::value || (j >= 1 && j <= m)) {
-          int32_t hd = diag, hup = in_h, eup = in_e;
-          int32_t hn = 0;
-          uint32_t word = 0;
-          const int pw = PROF == kProfLane ? (int)lp[in_c] : 0;
-          // local affine score-only bands fold the floor into E (band.h).  Checkpoint rows then hold the
-          // raised E too; the tiles relaxed again from them reproduce every H, and every E on the alignment's
-          // path (a local path's E is at least 0, the floor), so the walk reads the same codes.
-          constexpr bool kFloorE = MODE == ALN_LOCAL && AFFINE && !TB;
-          band_column<MODE, AFFINE, PROF, TB, decltype(checked)::value, R, true, kFloorE>(
-              tab, prof, in_c, pw, go, ge, goe, nu, hl, f, bv, bj, hk, j, rn, hd, hup, eup, hn, word);
-          if (TB) codes[j - 1] = (uint16_t)word;
-          if (MODE == ALN_SEMIGLOBAL && last_band && rn >= 0 && rn < R && hn > brow) {
-            brow = hn;
-            browj = j;
-          }
-          if (CKPT && ckc && (j & (kTileCols - 1)) == 0 && j >= kTileCols && j < m) {
-            // rows irow0+1..irow0+4 of column j: Hb and Fb, 32 contiguous bytes
-            int4* dst = reinterpret_cast<int4*>(W.ckcols + (int64_t)(j / kTileCols - 1) * W.ck_ld + irow0);
-            dst[0] = make_int4(hl[0], f[0], hl[1], f[1]);
-            dst[1] = make_int4(hl[2], f[2], hl[3], f[3]);
-          }
-          bot_h = hup;
-          bot_e = eup;
-          diag = in_h;
-        }
-        out_h = dpp_shl1(bot_h, out_h);
-        out_e = dpp_shl1(bot_e, out_e);
+      if (MODE == ALN_LOCAL)
+        B.floor = raise_local_floor(B.bs, lane < BLK && col_in <= m ? th - lane_zero<FA>() + (i0 + col_in) * P.ge : 0);
+      auto load_rows = [&](int g4, BandIn<R>& I) __attribute__((always_inline)) {
+        const int k = ((tb + 4 * g4) & (kRing - 1)) / 4;
+        const int4 h4 = reinterpret_cast<const int4*>(rin_h)[k];
+        const int4 e4 = reinterpret_cast<const int4*>(rin_e)[k];
+        I.vh[0] = h4.x, I.vh[1] = h4.y, I.vh[2] = h4.z, I.vh[3] = h4.w;
+        I.ve[0] = e4.x, I.ve[1] = e4.y, I.ve[2] = e4.z, I.ve[3] = e4.w;
       };
-      for (int g4 = 0; g4 < BLK / 4; ++g4) {
+      auto run = [&](int g4, BandIn<R>& I) __attribute__((always_inline)) {
         const int t0 = tb + 4 * g4;
-        const int4 vh = reinterpret_cast<const int4*>(st_h)[g4];
-        const int4 ve = reinterpret_cast<const int4*>(st_e)[g4];
-        const int4 vc = reinterpret_cast<const int4*>(st_c)[g4];
+        const int j0 = t0 - lane + 1;
+        if (t0 + 4 > m) {
+          // past the last column the ring holds whatever it held: nothing above lane 0 there
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            I.vh[u] = t0 + u + 1 > m ? lane_neg<FA>() : I.vh[u];
+            I.ve[u] = t0 + u + 1 > m ? lane_neg<FA>() : I.ve[u];
+          }
+        }
+        const int ph = L.bot_h, pe = L.bot_e, floor0 = L.floor0;
+        BandGroup<R> G;
+        const bool inside = t0 >= 63 && t0 + 3 < m;
         // With checkpoints, some lane's column in these 4 steps is a multiple of kTileCols only when
-        // (t0 + 1) mod kTileCols is below 64 or within 3 of kTileCols (a wave-uniform test); such
-        // groups take the checked path, which stores the checkpoints, and the fast path stays as is.
-        const int u = (t0 + 1) & (kTileCols - 1);
-        const bool ck_group = CKPT && (u < 64 || u > kTileCols - 4);
-        if (t0 >= 63 && t0 + 3 < m && !ck_group) {
-          // every lane is inside the matrix: no range test; local optima are tracked per 4 steps
-          int32_t hk[4][R];
-          step(t0, vh.x, ve.x, vc.x, std::false_type(), hk[0], false);
-          step(t0 + 1, vh.y, ve.y, vc.y, std::false_type(), hk[1], false);
-          step(t0 + 2, vh.z, ve.z, vc.z, std::false_type(), hk[2], false);
-          step(t0 + 3, vh.w, ve.w, vc.w, std::false_type(), hk[3], false);
-          if (MODE == ALN_LOCAL) {
-            int32_t mk[R];
-            bool imp = false;
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-              mk[r] = max(max(hk[0][r], hk[1][r]), max(hk[2][r], hk[3][r]));
-              imp |= mk[r] > bv[r];
+        // (t0 + 1) mod kTileCols is below 64 or within 3 of kTileCols (a wave-uniform test).
+        const int cu = (t0 + 1) & (kTileCols - 1);
+        if (CKPT && (cu < 64 || cu > kTileCols - 4)) {
+          auto checkpoint = [&](int u) {
+            const int j = j0 + u;
+            if ((j & (kTileCols - 1)) == 0 && j >= kTileCols && j < m) {
+              // rows irow0+1..irow0+4 of column j: H~ and F~, 32 contiguous bytes
+              int4* dst = reinterpret_cast<int4*>(W.ckcols + (int64_t)(j / kTileCols - 1) * W.ck_ld + irow0);
+              dst[0] = make_int4(L.h[0], L.f[0], L.h[1], L.f[1]);
+              dst[1] = make_int4(L.h[2], L.f[2], L.h[3], L.f[3]);
             }
-            if (LAZY && imp) {
-              // a row that beat its best keeps the group (resolved later, see resolve)
-#pragma unroll
-              for (int r = 0; r < R; ++r) {
-                const unsigned long long up = __builtin_amdgcn_ballot_w64(mk[r] > bv[r]);
-#pragma unroll
-                for (int x = 0; x < 4; ++x) sv[x][r] = mask_select(up, hk[x][r], sv[x][r]);
-                sg[r] = mask_select(up, t0, sg[r]);
-                bv[r] = max(bv[r], mk[r]);
-              }
-            } else if (imp) {
-              // a row that beat its best takes the group's maximum at the first of the 4 steps that
-              // reached it, as a cell-by-cell strict update would
-#pragma unroll
-              for (int r = 0; r < R; ++r) {
-                int k = hk[2][r] == mk[r] ? 2 : 3;
-                k = hk[1][r] == mk[r] ? 1 : k;
-                k = hk[0][r] == mk[r] ? 0 : k;
-                bj[r] = lane_select(mk[r] > bv[r], t0 - lane + 1 + k, bj[r]);
-                bv[r] = max(bv[r], mk[r]);
-              }
-            }
-          }
+          };
+          if (MODE == ALN_LOCAL || inside)
+            band_group<MODE, AFFINE, PROF, TB, FA, R, false>(P, tab, prof, I, j0, m, L, G, checkpoint);
+          else
+            band_group<MODE, AFFINE, PROF, TB, FA, R, true>(P, tab, prof, I, j0, m, L, G, checkpoint);
+        } else if (MODE == ALN_LOCAL || inside) {
+          // local cells outside the matrix are harmless (raise_local_floor); the others keep their state there
+          band_group<MODE, AFFINE, PROF, TB, FA, R, false>(P, tab, prof, I, j0, m, L, G, [](int) {});
         } else {
-          if (LAZY) resolve();
-          step(t0, vh.x, ve.x, vc.x, std::true_type(), nullptr, CKPT);
-          step(t0 + 1, vh.y, ve.y, vc.y, std::true_type(), nullptr, CKPT);
-          step(t0 + 2, vh.z, ve.z, vc.z, std::true_type(), nullptr, CKPT);
-          step(t0 + 3, vh.w, ve.w, vc.w, std::true_type(), nullptr, CKPT);
+          band_group<MODE, AFFINE, PROF, TB, FA, R, true>(P, tab, prof, I, j0, m, L, G, [](int) {});
         }
-      }
-      // lanes 64-BLK.. hold lane 63's outputs of steps tb..tb+BLK-1, i.e. columns tb-62..tb+BLK-63
-      if (has_out) {
-        const int hi = min(tb + BLK - 63, m);
-        const int col_out = tb + (lane - (64 - BLK)) - 62;
-        const bool mine = lane >= 64 - BLK && col_out >= 1 && col_out <= m;
-        if (hi >= 1) {
-          // the band below has read what this overwrites
-          if (con_seen < hi - kRing && !lds_wait_ge(&con[wib + 1], hi - kRing)) {
-            failed = true;
-            break;
-          }
-          if (mine) rout[col_out % kRing] = make_int2(out_h, out_e);
-          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-          if (lane == 0) __hip_atomic_store(&pub[wib + 1], hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (TB) store_codes<R>(G, codes, j0, m, inside);
+        if constexpr (MODE == ALN_LOCAL) track_local<AFFINE, R>(P, L, G, floor0, j0, flip, B);
+        if (MODE == ALN_SEMIGLOBAL && last_band) track_last_row<AFFINE, R>(P, L, G, floor0, m, rn, j0, B);
+        if (has_out && lane == 63) {
+          reinterpret_cast<int4*>(rout_h)[((t0 - 64) & (kRing - 1)) / 4] = make_int4(ph, G.oh[0], G.oh[1], G.oh[2]);
+          reinterpret_cast<int4*>(rout_e)[((t0 - 64) & (kRing - 1)) / 4] = make_int4(pe, G.oe[0], G.oe[1], G.oe[2]);
         }
+      };
+      run_block<PROF, R, BLK / 4>(lett, lp, lane, min(BLK / 4, (steps - tb + 3) / 4), load_rows, run);
+      // the block's ring reads are complete and its outputs written before either is announced
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      if (lane == 0) {
+        if (b > 0) __hip_atomic_store(&con[cw], need, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (has_out && hi >= 1)
+          __hip_atomic_store(&pub[cw + 1], min(hi, m), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       }
     }
-
-    if (LAZY) resolve();
-    // band optimum: (score, i, j) over this lane's rows, then across the wave
-    int bs = kNeg32, bi = 0, bjj = 0;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int i = irow0 + r + 1;
-      if (i > n) continue;
-      int sc = 0, jj = 0;
-      bool cand = false;
-      if (MODE == ALN_LOCAL) {
-        sc = bv[r] + i * ge;
-        jj = bj[r];
-        cand = sc > 0;
-      } else if (MODE == ALN_SEMIGLOBAL) {
-        sc = hl[r] + i * ge;  // H(i, m): last-column candidate; row n is handled below
-        jj = m;
-        cand = (i < n);
-      } else {
-        sc = hl[r] + i * ge;
-        jj = m;
-        cand = (i == n);
-      }
-      // a flipped pair's cell (i, jj) is the call's cell (jj, i)
-      const int ci = flip ? jj : i, cj = flip ? i : jj;
-      if (cand && better(sc, ci, cj, bs, bi, bjj)) {
-        bs = sc;
-        bi = ci;
-        bjj = cj;
-      }
-    }
-    if (MODE == ALN_SEMIGLOBAL && last_band && rn >= 0 && rn < R) {
-      // row n: (n, 0) with H = 0 first, then its running maximum over j in column order
-      const int rowv = (browj > 0) ? brow + n * ge : 0;
-      const int ci = flip ? browj : n, cj = flip ? n : browj;
-      if (better(rowv, ci, cj, bs, bi, bjj)) {
-        bs = rowv;
-        bi = ci;
-        bjj = cj;
-      }
-    }
-    for (int o = 32; o >= 1; o >>= 1) {
-      const int s2 = __shfl_xor(bs, o, 64), i2 = __shfl_xor(bi, o, 64), j2 = __shfl_xor(bjj, o, 64);
-      if (better(s2, i2, j2, bs, bi, bjj)) {
-        bs = s2;
-        bi = i2;
-        bjj = j2;
-      }
-    }
-    const bool anybad = __any(bad);
-    if (lane == 0) W.band_res[t] = make_int4(bs, bi, bjj, (anybad ? 1 : 0) | (failed ? 2 : 0));
+    const int4 opt = band_optimum<MODE, FA, R>(P, L, B, n, m, flip, last_band, irow0, bad, failed);
+    if (lane == 0) W.band_res[t] = opt;
     }
     }
     __syncthreads();  // the group's rings and ticket are reused by the next group
   }
 }
 
-// One wave per pair: reduces the pair's band optima into its aln_result_t.
+// A pair's result from its bands' optimum (bs at bi, bj) and flags, without the traceback's part.
+__device__ __forceinline__ aln_result_t pair_result(const KParams& P, const WfPair& pr, int bs, int bi, int bj, int flag,
+                                                    bool err) {
+  const int n = pr.flip ? pr.m : pr.n, m = pr.flip ? pr.n : pr.m;  // the call's query and subject lengths
+  aln_result_t r;
+  r.q_begin = -1;
+  r.s_begin = -1;
+  r.cigar_len = 0;
+  r.reserved = 0;
+  r.flags = 0;
+  if (P.mode == ALN_GLOBAL) {
+    r.q_end = n;
+    r.s_end = m;
+    r.score = (n == 0 || m == 0) ? ((n + m > 0) ? P.go + (n + m) * P.ge : 0) : bs;
+  } else if (n == 0 || m == 0 || bs < 0 || (bs == 0 && P.mode == ALN_LOCAL)) {
+    // local: the empty alignment at (0,0); semi-global: the first candidate (0, m), or (0, 0) if a side is empty
+    r.score = 0;
+    r.q_end = 0;
+    r.s_end = (P.mode == ALN_SEMIGLOBAL && n > 0) ? m : 0;
+  } else if (P.mode == ALN_SEMIGLOBAL && bs == 0) {
+    r.score = 0;  // (0, m) precedes every other candidate in row-major order
+    r.q_end = 0;
+    r.s_end = m;
+  } else {
+    r.score = bs;
+    r.q_end = bi;
+    r.s_end = bj;
+  }
+  if (err || (flag & 2)) r.flags |= ALN_RES_DEVICE_ERROR;
+  if (flag & 1) {
+    r.flags |= ALN_RES_BAD_CODE;
+    r.score = 0;
+    r.q_end = 0;
+    r.s_end = 0;
+  }
+  return r;
+}
+
+// Reduces every pair's band optima into its aln_result_t.  A wave takes as many consecutive pairs as spread the batch
+// over the launch's waves, up to 64: its lanes finish one pair with one band each (100,003 of them took 113 us with a
+// wave each), and the whole wave takes the other pairs one at a time.
 // cigar_off, when given, is a batch call's: pair out_idx owns cigar[cigar_off[out_idx] .. cigar_off[out_idx + 1]];
 // otherwise the single pair owns cigar_cap words at cigar.
 template <int MODE, bool TB>
@@ -1262,91 +1254,78 @@ __global__ __launch_bounds__(256) void wf_finish_kernel(const KParams P, WfWs W,
   __shared__ uint16_t walk_win[TB ? 4 : 1][TB ? kWalkGroups * kWalkCols : 1];
   const int lane = threadIdx.x & 63;
   const int np = *W.n_pairs;
+  const int waves = (int)gridDim.x * 4;
+  const int per = TB ? 1 : min(64, max(1, np / waves));
   const bool err = __hip_atomic_load(W.error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-  for (int k = blockIdx.x * 4 + (threadIdx.x >> 6); k < np; k += gridDim.x * 4) {
-    const WfPair pr = W.pairs[k];
-    int bs = kNeg32, bi = 0, bj = 0, flag = 0;
-    for (int b = lane; b < pr.nb; b += 64) {
-      const int4 v = W.band_res[pr.item0 + b];
-      flag |= v.w;
-      if (better(v.x, v.y, v.z, bs, bi, bj)) {
-        bs = v.x;
-        bi = v.y;
-        bj = v.z;
+  for (int64_t k0 = (int64_t)(blockIdx.x * 4 + (threadIdx.x >> 6)) * per; k0 < np; k0 += (int64_t)waves * per) {
+    unsigned long long rest = per == 64 ? ~0ull : (1ull << per) - 1;  // pairs left to the whole wave
+    if (per > 1) {
+      bool left = false;
+      if (lane < per && k0 + lane < np) {
+        const WfPair pr = W.pairs[k0 + lane];
+        left = pr.nb != 1;
+        if (!left) {
+          const int4 v = W.band_res[pr.item0];
+          out[pr.out_idx] = pair_result(P, pr, v.x, v.y, v.z, v.w, err);
+        }
       }
+      rest = __builtin_amdgcn_ballot_w64(left);
     }
-    if (pr.nb == 0) {
-      // a pair with an empty side has no bands, whose relaxation checks the letters: check them here
-      const uint8_t* rq = (pr.flip ? s : q) + pr.q_off;  // the pair's row and column letters
-      const uint8_t* rs = (pr.flip ? q : s) + pr.s_off;
-      for (int k = lane; k < pr.n; k += 64)
-        if (rq[k] >= P.alphabet) flag |= 1;
-      for (int k = lane; k < pr.m; k += 64)
-        if (rs[k] >= P.alphabet) flag |= 1;
-    }
-    for (int o = 32; o >= 1; o >>= 1) {
-      const int s2 = __shfl_xor(bs, o, 64), i2 = __shfl_xor(bi, o, 64), j2 = __shfl_xor(bj, o, 64);
-      flag |= __shfl_xor(flag, o, 64);
-      if (better(s2, i2, j2, bs, bi, bj)) {
-        bs = s2;
-        bi = i2;
-        bj = j2;
+    for (; rest; rest &= rest - 1) {
+      const int64_t k = k0 + __builtin_ctzll(rest);
+      const WfPair pr = W.pairs[k];
+      int bs = kNeg32, bi = 0, bj = 0, flag = 0;
+      for (int b = lane; b < pr.nb; b += 64) {
+        const int4 v = W.band_res[pr.item0 + b];
+        flag |= v.w;
+        if (better(v.x, v.y, v.z, bs, bi, bj)) {
+          bs = v.x;
+          bi = v.y;
+          bj = v.z;
+        }
       }
-    }
-    // every lane now holds the same optimum; the result is computed by all and written by lane 0
-    const int n = pr.flip ? pr.m : pr.n, m = pr.flip ? pr.n : pr.m;  // the call's query and subject lengths
-    aln_result_t r;
-    r.q_begin = -1;
-    r.s_begin = -1;
-    r.cigar_len = 0;
-    r.reserved = 0;
-    r.flags = 0;
-    if (P.mode == ALN_GLOBAL) {
-      r.q_end = n;
-      r.s_end = m;
-      r.score = (n == 0 || m == 0) ? ((n + m > 0) ? P.go + (n + m) * P.ge : 0) : bs;
-    } else if (n == 0 || m == 0 || bs < 0 || (bs == 0 && P.mode == ALN_LOCAL)) {
-      // local: the empty alignment at (0,0); semi-global: the first candidate (0, m), or (0, 0) if a side is empty
-      r.score = 0;
-      r.q_end = 0;
-      r.s_end = (P.mode == ALN_SEMIGLOBAL && n > 0) ? m : 0;
-    } else if (P.mode == ALN_SEMIGLOBAL && bs == 0) {
-      r.score = 0;  // (0, m) precedes every other candidate in row-major order
-      r.q_end = 0;
-      r.s_end = m;
-    } else {
-      r.score = bs;
-      r.q_end = bi;
-      r.s_end = bj;
-    }
-    if (err || (flag & 2)) r.flags |= ALN_RES_DEVICE_ERROR;
-    if (flag & 1) {
-      r.flags |= ALN_RES_BAD_CODE;
-      r.score = 0;
-      r.q_end = 0;
-      r.s_end = 0;
-    }
-    if (TB && r.flags == 0) {
-      // The codes form a [row group][column] array of 16-bit words, 4 rows per word (band bb, lane L
-      // is row group bb * 64 + L); walk_core walks them with the whole wave.
-      uint32_t* cg = cigar;
-      int64_t cap = cigar_cap;
-      if (cigar_off) {
-        const int64_t c0 = cigar_off[pr.out_idx];
-        cg = cigar + c0;
-        cap = cigar_off[pr.out_idx + 1] - c0;
+      if (pr.nb == 0) {
+        // a pair with an empty side has no bands, whose relaxation checks the letters: check them here
+        const uint8_t* rq = (pr.flip ? s : q) + pr.q_off;  // the pair's row and column letters
+        const uint8_t* rs = (pr.flip ? q : s) + pr.s_off;
+        for (int c = lane; c < pr.n; c += 64)
+          if (rq[c] >= P.alphabet) flag |= 1;
+        for (int c = lane; c < pr.m; c += 64)
+          if (rs[c] >= P.alphabet) flag |= 1;
       }
-      WalkState S;
-      walk_start(S, r.q_end, r.s_end);
-      walk_core<MODE>(W.codes + pr.code_off, m, 0, 0, S, walk_win[threadIdx.x >> 6], lane, cg, cap);
-      const int64_t runs = walk_finish(S, lane, cg, cap);
-      r.q_begin = S.i;
-      r.s_begin = S.j;
-      r.cigar_len = (int)runs;
-      if (runs > cap) r.flags |= ALN_RES_CIGAR_TRUNC;
-      if (S.stuck) r.flags |= ALN_RES_DEVICE_ERROR;
+      for (int o = 32; o >= 1; o >>= 1) {
+        const int s2 = __shfl_xor(bs, o, 64), i2 = __shfl_xor(bi, o, 64), j2 = __shfl_xor(bj, o, 64);
+        flag |= __shfl_xor(flag, o, 64);
+        if (better(s2, i2, j2, bs, bi, bj)) {
+          bs = s2;
+          bi = i2;
+          bj = j2;
+        }
+      }
+      // every lane now holds the same optimum; the result is computed by all and written by lane 0
+      aln_result_t r = pair_result(P, pr, bs, bi, bj, flag, err);
+      if (TB && r.flags == 0) {
+        // The codes form a [row group][column] array of 16-bit words, 4 rows per word (band bb, lane L
+        // is row group bb * 64 + L); walk_core walks them with the whole wave.
+        uint32_t* cg = cigar;
+        int64_t cap = cigar_cap;
+        if (cigar_off) {
+          const int64_t c0 = cigar_off[pr.out_idx];
+          cg = cigar + c0;
+          cap = cigar_off[pr.out_idx + 1] - c0;
+        }
+        WalkState S;
+        walk_start(S, r.q_end, r.s_end);
+        walk_core<MODE>(W.codes + pr.code_off, pr.m, 0, 0, S, walk_win[threadIdx.x >> 6], lane, cg, cap);
+        const int64_t runs = walk_finish(S, lane, cg, cap);
+        r.q_begin = S.i;
+        r.s_begin = S.j;
+        r.cigar_len = (int)runs;
+        if (runs > cap) r.flags |= ALN_RES_CIGAR_TRUNC;
+        if (S.stuck) r.flags |= ALN_RES_DEVICE_ERROR;
+      }
+      if (lane == 0) out[pr.out_idx] = r;
     }
-    if (lane == 0) out[pr.out_idx] = r;
   }
 }
 
@@ -1532,70 +1511,68 @@ bool p16_exact(const KParams& kp) {
   return step <= 32;
 }
 
-template <int MODE, bool AFFINE, int PROF, bool TB>
+template <int MODE, bool AFFINE, int PROF, bool TB, bool FA>
 void launch_wf_t(const KParams& kp, const uint8_t* q, const uint8_t* s, const WfWs& W, int n_waves, bool grouped,
                  bool p16, hipStream_t stream) {
   const int blocks = (n_waves + kWfWavesPerBlock - 1) / kWfWavesPerBlock;
-  const size_t lds = PROF == kProfLane ? (size_t)kWfWavesPerBlock * kp.alphabet * 64 * sizeof(uint32_t) : 0;
+  const size_t lds = PROF == kProfLane ? (size_t)kWfWavesPerBlock * (kp.alphabet + 1) * 64 * sizeof(uint32_t) : 0;
   constexpr bool kCanPack = MODE == ALN_LOCAL && (PROF == kProfReg || PROF == kProfLane) && !TB;
   if (kCanPack && grouped && p16 && p16_exact(kp)) {
     // packed bands keep two 16-bit rows of each half per letter and lane: twice the words
     ProfScope prof("wavefront_p16", stream);
-    hipLaunchKernelGGL((wf_i32_group_kernel<MODE, AFFINE, PROF, TB, kWfR, kCanPack, false, false>), dim3(blocks),
+    hipLaunchKernelGGL((wf_i32_group_kernel<MODE, AFFINE, PROF, TB, false, kWfR, kCanPack, false>), dim3(blocks),
                        dim3(kWfBlock), 2 * lds, stream, kp, q, s, W);
     return;
   }
   if (!TB && W.ckcols) {
     ProfScope prof("wavefront_i32_checkpoints", stream);
-    hipLaunchKernelGGL((wf_i32_group_kernel<MODE, AFFINE, PROF, false, kWfR, false, !TB, false>), dim3(blocks),
+    hipLaunchKernelGGL((wf_i32_group_kernel<MODE, AFFINE, PROF, false, FA, kWfR, false, !TB>), dim3(blocks),
                        dim3(kWfBlock), lds, stream, kp, q, s, W);
     return;
   }
   ProfScope prof(TB ? "wavefront_i32_traceback" : "wavefront_i32", stream);
-  // one long pair, local and score-only: improving groups are kept and resolved later (LAZY)
-  constexpr bool kLazy = MODE == ALN_LOCAL && !TB;
-  if (grouped && kLazy && W.one_pair)
-    hipLaunchKernelGGL((wf_i32_group_kernel<MODE, AFFINE, PROF, TB, kWfR, false, false, kLazy>), dim3(blocks),
-                       dim3(kWfBlock), lds, stream, kp, q, s, W);
-  else if (grouped)
-    hipLaunchKernelGGL((wf_i32_group_kernel<MODE, AFFINE, PROF, TB, kWfR, false, false, false>), dim3(blocks),
+  if (grouped)
+    hipLaunchKernelGGL((wf_i32_group_kernel<MODE, AFFINE, PROF, TB, FA, kWfR, false, false>), dim3(blocks),
                        dim3(kWfBlock), lds, stream, kp, q, s, W);
   else
-    hipLaunchKernelGGL((wf_i32_kernel<MODE, AFFINE, PROF, TB, kWfR>), dim3(blocks), dim3(kWfBlockAlone), lds,
+    hipLaunchKernelGGL((wf_i32_kernel<MODE, AFFINE, PROF, TB, FA, kWfR>), dim3(blocks), dim3(kWfBlockAlone), lds,
                        stream, kp, q, s, W);
 }
 
-template <int MODE, bool AFFINE, bool TB>
+template <int MODE, bool AFFINE, bool TB, bool FA>
 void launch_wf_p(const KParams& kp, const uint8_t* q, const uint8_t* s, const WfWs& W, int nw, bool grouped, bool p16,
                  hipStream_t st) {
-  const bool bytes = kp.sigma_max - kp.ge <= 127 && kp.sigma_min - kp.ge >= -127;
+  const bool bytes = kp.sigma_max - 2 * kp.ge <= 127 && kp.sigma_min - 2 * kp.ge >= -127;
   if (bytes && kp.alphabet <= 4)
-    launch_wf_t<MODE, AFFINE, kProfReg, TB>(kp, q, s, W, nw, grouped, p16, st);
+    launch_wf_t<MODE, AFFINE, kProfReg, TB, FA>(kp, q, s, W, nw, grouped, p16, st);
   else if (bytes)
-    launch_wf_t<MODE, AFFINE, kProfLane, TB>(kp, q, s, W, nw, grouped, p16, st);
+    launch_wf_t<MODE, AFFINE, kProfLane, TB, FA>(kp, q, s, W, nw, grouped, p16, st);
   else
-    launch_wf_t<MODE, AFFINE, kProfTable, TB>(kp, q, s, W, nw, grouped, false, st);
+    launch_wf_t<MODE, AFFINE, kProfTable, TB, FA>(kp, q, s, W, nw, grouped, false, st);
 }
 
+// fa: float lanes (band.h).  Only affine gaps add a constant per cell; linear ones always use integer lanes.
 template <int MODE, bool TB>
 void launch_wf_m(const KParams& kp, const uint8_t* q, const uint8_t* s, const WfWs& W, int nw, bool grouped, bool p16,
-                 hipStream_t st) {
-  if (kp.go != 0)
-    launch_wf_p<MODE, true, TB>(kp, q, s, W, nw, grouped, p16, st);
+                 bool fa, hipStream_t st) {
+  if (kp.go == 0)
+    launch_wf_p<MODE, false, TB, false>(kp, q, s, W, nw, grouped, p16, st);
+  else if (fa)
+    launch_wf_p<MODE, true, TB, true>(kp, q, s, W, nw, grouped, p16, st);
   else
-    launch_wf_p<MODE, false, TB>(kp, q, s, W, nw, grouped, p16, st);
+    launch_wf_p<MODE, true, TB, false>(kp, q, s, W, nw, grouped, p16, st);
 }
 
 template <int MODE>
 void launch_wf_mode(const KParams& kp, const uint8_t* q, const uint8_t* s, const WfWs& W, int nw, bool grouped, bool tb,
-                    bool p16, aln_result_t* out, uint32_t* cigar, int64_t cap, const int64_t* cigar_off,
+                    bool p16, bool fa, aln_result_t* out, uint32_t* cigar, int64_t cap, const int64_t* cigar_off,
                     hipStream_t st) {
   if (tb) {
-    launch_wf_m<MODE, true>(kp, q, s, W, nw, grouped, false, st);
+    launch_wf_m<MODE, true>(kp, q, s, W, nw, grouped, false, fa, st);
     hipLaunchKernelGGL((wf_finish_kernel<MODE, true>), dim3(256), dim3(256), 0, st, kp, W, q, s, out, cigar, cap,
                        cigar_off);
   } else {
-    launch_wf_m<MODE, false>(kp, q, s, W, nw, grouped, p16, st);
+    launch_wf_m<MODE, false>(kp, q, s, W, nw, grouped, p16, fa, st);
     hipLaunchKernelGGL((wf_finish_kernel<MODE, false>), dim3(256), dim3(256), 0, st, kp, W, q, s, out, cigar, cap,
                        cigar_off);
   }
@@ -1604,6 +1581,13 @@ void launch_wf_mode(const KParams& kp, const uint8_t* q, const uint8_t* s, const
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 }  // namespace
+
+bool band_fits_fa(const KParams& kp, int64_t n, int64_t m) {
+  const int64_t c = -(int64_t)kp.ge, mn = n < m ? n : m;
+  const int64_t up = mn * (kp.sigma_max > 0 ? kp.sigma_max : 0) + (n + m + 2 * kWfBand) * c + 256;
+  const int64_t down = 64 * c - 4 * (int64_t)kp.go + 256;  // columns before the first; gaps opened from there
+  return up < (1 << 23) - (1 << 20) && down < (1 << 20);
+}
 
 int wf_waves(int per_cu) {
   const int cus = device_cu_count();
@@ -1651,7 +1635,6 @@ WfWs wf_view(void* base_, const WfOffsets& o) {
   W.codes = reinterpret_cast<uint16_t*>(base + o.codes);
   W.ckcols = nullptr;
   W.ck_ld = 0;
-  W.one_pair = 0;
   W.order = reinterpret_cast<int64_t*>(base + o.order);
   W.lv = reinterpret_cast<int*>(base + o.lv);
   W.n_lv = (int)o.n_lv;
@@ -1659,7 +1642,7 @@ WfWs wf_view(void* base_, const WfOffsets& o) {
 }
 
 aln_status_t launch_wf_i32(const KParams& kp, const WfWs& W, const uint8_t* q, const uint8_t* s,
-                           aln_result_t* out, int max_waves, bool grouped, bool tb, bool p16, uint32_t* cigar,
+                           aln_result_t* out, int max_waves, bool grouped, bool tb, bool p16, bool fa, uint32_t* cigar,
                            int64_t cigar_cap, hipStream_t stream, const int64_t* cigar_off) {
   hipLaunchKernelGGL(wf_reset_kernel, dim3(256), dim3(256), 0, stream, W);
   if (!grouped) {
@@ -1669,13 +1652,13 @@ aln_status_t launch_wf_i32(const KParams& kp, const WfWs& W, const uint8_t* q, c
   }
   switch (kp.mode) {
     case ALN_GLOBAL:
-      launch_wf_mode<ALN_GLOBAL>(kp, q, s, W, max_waves, grouped, tb, p16, out, cigar, cigar_cap, cigar_off, stream);
+      launch_wf_mode<ALN_GLOBAL>(kp, q, s, W, max_waves, grouped, tb, p16, fa, out, cigar, cigar_cap, cigar_off, stream);
       break;
     case ALN_LOCAL:
-      launch_wf_mode<ALN_LOCAL>(kp, q, s, W, max_waves, grouped, tb, p16, out, cigar, cigar_cap, cigar_off, stream);
+      launch_wf_mode<ALN_LOCAL>(kp, q, s, W, max_waves, grouped, tb, p16, fa, out, cigar, cigar_cap, cigar_off, stream);
       break;
     default:
-      launch_wf_mode<ALN_SEMIGLOBAL>(kp, q, s, W, max_waves, grouped, tb, p16, out, cigar, cigar_cap, cigar_off,
+      launch_wf_mode<ALN_SEMIGLOBAL>(kp, q, s, W, max_waves, grouped, tb, p16, fa, out, cigar, cigar_cap, cigar_off,
                                      stream);
       break;
   }
@@ -1708,11 +1691,11 @@ aln_status_t launch_long(const KParams& kp, const LongPlan& pl, const uint8_t* q
                          int64_t m, aln_result_t* out, uint32_t* cigar, int64_t cigar_cap, void* ws,
                          hipStream_t stream) {
   WfWs W = wf_view(ws, pl.off);
-  W.one_pair = 1;
   hipLaunchKernelGGL(wf_single_pair_kernel, dim3(1), dim3(64), 0, stream, W, (int)n, (int)m, kWfBand);
   // one pair: its bands are few per SIMD, so the grouped engine (no device-memory stalls in the
   // compute waves) is the faster one
-  return launch_wf_i32(kp, W, q, s, out, pl.n_waves, true, pl.tb, false, cigar, cigar_cap, stream);
+  return launch_wf_i32(kp, W, q, s, out, pl.n_waves, true, pl.tb, false, band_fits_fa(kp, n, m), cigar,
+                       cigar_cap, stream);
 }
 
 }  // namespace mialign
