@@ -126,7 +126,8 @@ aln_status_t aln_batch_workspace_size(const aln_scoring_t* scoring, int64_t n_pa
  * In traceback calls the rule is fixed: pairs with n*m >= 2^18, or longer than 1024 on either side,
  * run on the band wavefront and store their 4-bit predecessor codes in an arena of the workspace (about
  * n*m/2 bytes each); the one-pair-per-lane kernels then hold code slabs for pairs up to 1024 x 1024
- * only.  The arena is sized by a bound from max_n, max_m, total_q and total_s; where that bound exceeds
+ * only.  Where the batch is too short to fill those kernels (a rule on its pair count and largest sides), the
+ * pairs they would take run one per wave, in 32-bit lanes.  The arena is sized by a bound from max_n, max_m, total_q and total_s; where that bound exceeds
  * the arena budget (aln_set_batch_code_arena, 16 GiB by default) the arena is the budget, pairs take
  * room in the order they reach it, those that find none run one pair per lane, and the lanes' slabs are
  * sized for max_n x max_m (fewer waves in flight, at most 16 GiB of slabs).  Results are identical
@@ -244,7 +245,7 @@ aln_status_t aln_traceback_workspace_size(const aln_scoring_t* scoring, int64_t 
  *                         outside the matrix or H there is not fwd's score.
  *   cigar, cigar_off  DEVICE  as for aln_align_batch; ALN_RES_CIGAR_TRUNC when a pair's room is short
  *   workspace     DEVICE  at least aln_traceback_workspace_size(...) bytes, 256-byte aligned
- * Pairs run one per lane in 32-bit lanes, in the order given. */
+ * Pairs run in 32-bit lanes, in the order given: one per wave, or one per lane where the pairs are small and many. */
 aln_status_t aln_traceback(const aln_scoring_t* scoring, int64_t n_pairs, const uint8_t* q, const int64_t* q_off,
                            const uint8_t* s, const int64_t* s_off, int64_t max_n, int64_t max_m,
                            const aln_result_t* fwd, aln_result_t* out, uint32_t* cigar, const int64_t* cigar_off,

@@ -1,4 +1,5 @@
 // C-ABI entry points of mialign: argument validation, workspace sizing and dispatch.
+#include <algorithm>
 #include <cstring>
 #include <mutex>
 
@@ -131,6 +132,8 @@ struct BatchLayout {
   BatchPlan16 bp16;
   SplitPlan sp;
   bool use16;
+  bool lanes_bounded;      // every pair left to the small-pair kernels is within lane_n x lane_m
+  int64_t lane_n, lane_m;  // largest sides they are sized for
   size_t off_redo, off_redo_cnt, off_split, total;
 };
 
@@ -141,9 +144,9 @@ static aln_status_t batch_layout(const KParams& kp, int64_t n_pairs, int64_t max
   if (st != ALN_OK) return st;
   // The one-pair-per-lane kernels of a traceback call meet pairs up to kTbLaneDim on each side when the
   // wavefront's code arena takes every longer pair; their slabs are sized for that.
-  const bool lanes_bounded = tb && L->sp.code_exact;
-  const int64_t lane_n = lanes_bounded ? std::min(max_n, kTbLaneDim) : max_n;
-  const int64_t lane_m = lanes_bounded ? std::min(max_m, kTbLaneDim) : max_m;
+  L->lanes_bounded = tb && L->sp.code_exact;
+  const int64_t lane_n = L->lane_n = L->lanes_bounded ? std::min(max_n, kTbLaneDim) : max_n;
+  const int64_t lane_m = L->lane_m = L->lanes_bounded ? std::min(max_m, kTbLaneDim) : max_m;
   st = plan_batch_i32(kp, n_pairs, lane_n, lane_m, tb, &L->bp);
   if (st != ALN_OK) return st;
   L->use16 = !(flags & ALN_FORCE_INT32) && cfg.small16 && lane_m < 32767;
@@ -250,6 +253,28 @@ aln_status_t aln_align_batch_ex(const aln_scoring_t* scoring, int64_t n_pairs, c
   }
   const int* list = reinterpret_cast<const int*>(split_ws + L.sp.off_small_idx);
   const int* list_cnt = reinterpret_cast<const int*>(split_ws + L.sp.off_small_cnt);
+  // a traceback batch too short to fill the one-pair-per-lane kernels runs one pair per wave
+  const int waves = tb && L.lanes_bounded ? wave_pair_waves(n_pairs, L.lane_n, L.lane_m, L.off_redo, L.use16) : 0;
+  if (waves > 0) {
+    WaveArgs a{};
+    a.q = q;
+    a.q_off = q_off;
+    a.s = s;
+    a.s_off = s_off;
+    a.n_pairs = n_pairs;
+    a.max_n = max_n;
+    a.max_m = max_m;
+    a.lane_n = L.lane_n;
+    a.lane_m = L.lane_m;
+    a.idx = list;
+    a.idx_count = list_cnt;
+    a.use16 = L.use16;
+    a.out = out;
+    a.cigar = cigar;
+    a.cigar_off = cigar_off;
+    a.ws = workspace;
+    return launch_batch_wave(kp, a, waves, stream);
+  }
   // the redo counter and the group tickets of the 16- and 32-bit launches start at zero
   int* ticket16 = redo_cnt + 16;
   int* ticket32 = redo_cnt + 32;
@@ -362,6 +387,23 @@ aln_status_t aln_traceback(const aln_scoring_t* scoring, int64_t n_pairs, const 
   st = tb_layout(kp, n_pairs, max_n, max_m, &bp, &off_ticket, &total);
   if (st != ALN_OK) return st;
   if (!workspace || workspace_bytes < total) return ALN_E_WORKSPACE;
+  const int waves = wave_pair_waves(n_pairs, max_n, max_m, off_ticket, false);
+  if (waves > 0) {
+    WaveArgs a{};
+    a.q = q;
+    a.q_off = q_off;
+    a.s = s;
+    a.s_off = s_off;
+    a.n_pairs = n_pairs;
+    a.max_n = a.lane_n = max_n;
+    a.max_m = a.lane_m = max_m;
+    a.fwd = fwd;
+    a.out = out;
+    a.cigar = cigar;
+    a.cigar_off = cigar_off;
+    a.ws = workspace;
+    return launch_batch_wave(kp, a, waves, stream);
+  }
   int* ticket = reinterpret_cast<int*>(static_cast<char*>(workspace) + off_ticket);
   hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(64), 0, stream, ticket, 1, 0);
   return launch_batch_i32(kp, bp, q, q_off, s, s_off, true, out, cigar, cigar_off, workspace, nullptr, nullptr, 0u,

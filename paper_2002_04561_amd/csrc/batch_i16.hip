@@ -32,7 +32,6 @@ constexpr int kI16WavesPerBlock = 2;
 constexpr int kI16Block = 64 * kI16WavesPerBlock;
 constexpr int kI16WavesPerCU = 8;
 constexpr int kPadSigma16 = -16384;
-constexpr int kBound16 = 32000;
 
 __device__ __forceinline__ s2 adds(s2 a, s2 b) { return __builtin_elementwise_add_sat(a, b); }
 __device__ __forceinline__ s2 subs(s2 a, s2 b) { return __builtin_elementwise_sub_sat(a, b); }
@@ -91,15 +90,6 @@ constexpr int kI16ProfBase = (kTab * kTab * 4 + 255) & ~255;
 __host__ __device__ constexpr int i16_chunk_words(int R) { return R / 2 < 4 ? R / 2 : 4; }
 __host__ __device__ constexpr int i16_wave_prof_words(int AP, int R) { return AP * 128 * (R / 2) + 64; }
 static_assert(kI16ProfBase % 256 == 0, "profiles start on a bank sweep");
-
-// biased: values carry the row bias of the global and semi-global recurrence (Hb = H - i*ge), which
-// lifts them by at most n*|ge|
-__device__ __forceinline__ bool fits16(const KParams& P, int n, int m, bool biased) {
-  const int mn = n < m ? n : m;
-  const long long up = (long long)mn * (P.sigma_max > 0 ? P.sigma_max : 0) - (biased ? (long long)n * P.ge : 0);
-  const long long lo = 3ll * P.go + (long long)(n + m) * P.ge;
-  return up <= kBound16 && lo >= -kBound16 && m < 32767;
-}
 
 // Persistent waves take groups of pairs from a device ticket; the groups come in the planner's
 // order (largest shapes first), so the waves drain the list evenly whatever number of them is

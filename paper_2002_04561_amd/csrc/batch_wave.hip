@@ -1,0 +1,324 @@
+// One wave per pair: traceback batches too short to fill the one-pair-per-lane kernels, and aln_traceback.
+//
+// A lane of batch_i16.hip takes a whole pair, so a wave's time is that of its largest pair whatever the batch holds: 4.5 ms
+// for reads of 100..250 letters against windows 64 longer, be it 400 pairs or 262,144.  Here a wave relaxes its pair
+// band by band (256 rows: 64 lanes x 4) with the recurrence of band.h, in 32-bit lanes, keeps the bottom row of a band in a
+// row buffer of its own for the next, and walks the codes back with the whole wave (walk_wave.h).  Bound by VALU issue:
+// a read's band takes (m + 64) steps of about 55 instructions, 70 % of its rows and columns padding.
+// Pairs come in the planner's order, largest first, and the waves take them in turn.
+#include "band.h"
+#include "band_wave.h"
+#include "internal.h"
+#include "walk_wave.h"
+
+#include <algorithm>
+#include <type_traits>
+
+namespace mialign {
+namespace {
+
+constexpr int kPWavesPerBlock = 4;
+constexpr int kPWavesPerCU = 16;
+constexpr int kPBand = 64 * kWfR;
+
+// LDS of one wave: while it relaxes, the stage of top-row inputs and outputs (H~ and E~ of 64 columns), the letter window and
+// the profile words; then the window of its walk.
+constexpr int kPStageBytes = 2 * 64 * 4;
+constexpr int kPLettersBytes = (int)((sizeof(LetterWindow<64>) + 15) / 16 * 16);
+__host__ __device__ constexpr int pair_lds_bytes(int alphabet, bool lane_profile) {
+  const int relax = kPStageBytes + kPLettersBytes + (lane_profile ? (alphabet + 1) * 256 : 0);
+  const int walk = kWalkGroups * kWalkCols * 2;
+  return relax > walk ? relax : walk;
+}
+
+// Relaxes a pair (n, m > 0) and stores its codes ([row group][column]); returns its optimum (score, i, j), or with FIXED the
+// score of cell (n, m) alone.
+template <int MODE, bool AFFINE, int PROF, bool FA, bool FIXED>
+__device__ __forceinline__ int4 relax_pair(const KParams& P, const int32_t* tab, const uint32_t* sig2, char* lds,
+                                           const uint8_t* __restrict__ q, int n, const uint8_t* __restrict__ s, int m,
+                                           int lane, int2* __restrict__ row, uint16_t* __restrict__ codes0, bool& bad) {
+  constexpr int R = kWfR, BLK = 64;
+  int* st_h = reinterpret_cast<int*>(lds);
+  int* st_e = st_h + 64;
+  LetterWindow<64>& lett = *reinterpret_cast<LetterWindow<64>*>(lds + kPStageBytes);
+  uint32_t* lp = reinterpret_cast<uint32_t*>(lds + kPStageBytes + kPLettersBytes) + lane;
+  const int nb = (n + kPBand - 1) / kPBand;
+  const int steps = m + 64;
+  int4 best = make_int4(kNeg32, 0, 0, 0);
+  for (int b = 0; b < nb; ++b) {
+    const int i0 = b * kPBand, irow0 = i0 + lane * R;
+    int prof[R];
+    BandLane<R> L;
+    BandBest<R> B;
+    band_start<MODE, PROF, FA, R>(P, sig2, q, n, false, irow0, lane, lp, prof, L, B, bad);
+    uint16_t* __restrict__ codes = codes0 + (size_t)(b * 64 + lane) * (size_t)m;
+    const bool last_band = b == nb - 1;
+    const int rn = n - 1 - irow0;
+    int cap[R] = {};  // FIXED, local: the lane's values of column m (the others keep their state there)
+    int c_next = 1 + lane <= m ? (int)s[lane] : -1;
+    int c_idx = letter_index<PROF, R>(P, -1, false, bad);
+    lett.clear_tail(lane);
+    for (int tb = 0; tb < steps; tb += BLK) {
+      const int col_in = tb + 1 + lane;
+      const int c_old = c_idx;
+      c_idx = letter_index<PROF, R>(P, c_next, false, bad);
+      lett.put(lane, c_old, c_idx);
+      c_next = col_in + BLK <= m ? (int)s[col_in + BLK - 1] : -1;
+      int32_t th = lane_neg<FA>(), te = lane_neg<FA>();
+      if (col_in <= m) {
+        if (b == 0) {
+          th = border_h<MODE, FA>(P, 0, col_in);
+        } else {
+          const int2 v = row[col_in];
+          th = v.x;
+          te = v.y;
+        }
+      }
+      if (MODE == ALN_LOCAL && !FIXED)
+        B.floor = raise_local_floor(B.bs, col_in <= m ? th - lane_zero<FA>() + (i0 + col_in) * P.ge : 0);
+      st_h[lane] = th;
+      st_e[lane] = te;
+      auto load_rows = [&](int g4, BandIn<R>& I) __attribute__((always_inline)) {
+        const int4 h4 = reinterpret_cast<const int4*>(st_h)[g4 & 15];
+        const int4 e4 = reinterpret_cast<const int4*>(st_e)[g4 & 15];
+        I.vh[0] = h4.x, I.vh[1] = h4.y, I.vh[2] = h4.z, I.vh[3] = h4.w;
+        I.ve[0] = e4.x, I.ve[1] = e4.y, I.ve[2] = e4.z, I.ve[3] = e4.w;
+      };
+      auto run = [&](int g4, const BandIn<R>& I) __attribute__((always_inline)) {
+        const int t0 = tb + 4 * g4;
+        const int j0 = t0 - lane + 1;
+        const int ph = L.bot_h, pe = L.bot_e, floor0 = L.floor0;
+        BandGroup<R> G;
+        const bool inside = t0 >= 63 && t0 + 3 < m;
+        if (MODE == ALN_LOCAL || inside)
+          band_group<MODE, AFFINE, PROF, true, FA, R, false>(P, tab, prof, I, j0, m, L, G, [](int) {});
+        else
+          band_group<MODE, AFFINE, PROF, true, FA, R, true>(P, tab, prof, I, j0, m, L, G, [](int) {});
+        if (irow0 < n) store_codes<R>(G, codes, j0, m, inside);  // row groups past n have no room
+        if constexpr (FIXED) {
+          if (MODE == ALN_LOCAL && last_band && t0 + 3 >= m - 1) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+              for (int r = 0; r < R; ++r) cap[r] = j0 + u == m ? G.v[u][r] - P.go : cap[r];
+          }
+        } else {
+          if constexpr (MODE == ALN_LOCAL) track_local<AFFINE, R>(P, L, G, floor0, j0, false, B);
+          if (MODE == ALN_SEMIGLOBAL && last_band) track_last_row<AFFINE, R>(P, L, G, floor0, m, rn, j0, B);
+        }
+        if (lane == 63) {
+          reinterpret_cast<int4*>(st_h)[g4] = make_int4(ph, G.oh[0], G.oh[1], G.oh[2]);
+          reinterpret_cast<int4*>(st_e)[g4] = make_int4(pe, G.oe[0], G.oe[1], G.oe[2]);
+        }
+      };
+      run_block<PROF, R, BLK / 4>(lett, lp, lane, min(BLK / 4, (steps - tb + 3) / 4), load_rows, run);
+      // slot u now holds lane 63's column tb + u - 63, whose entry of the row above has been read
+      if (!last_band) {
+        const int col_out = tb + lane - 63;
+        if (col_out >= 1 && col_out <= m) row[col_out] = make_int2(st_h[lane], st_e[lane]);
+      }
+    }
+    // the row buffer's stores are complete before the next band's lanes read other lanes' columns
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if constexpr (FIXED) {
+      if (last_band) {
+        int h = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) h = r == rn ? (MODE == ALN_LOCAL ? cap[r] : L.h[r]) : h;
+        const int hn = __builtin_amdgcn_readlane(h, (n - 1 - i0) / R);
+        best = make_int4(hn - lane_zero<FA>() + (n + m) * P.ge, n, m, 0);
+      }
+    } else {
+      const int4 o = band_optimum<MODE, FA, R>(P, L, B, n, m, false, last_band, irow0, false, false);
+      if (better(o.x, o.y, o.z, best.x, best.y, best.z)) best = o;
+    }
+  }
+  return best;
+}
+
+// FIXED: trace back from the end cell a forward pass found (fwd[p].q_end, fwd[p].s_end); the pair is relaxed only up to that
+// cell, whose H must equal fwd[p].score.
+template <int MODE, bool AFFINE, int PROF, bool FA, bool FIXED>
+__global__ __launch_bounds__(64 * kPWavesPerBlock, 4) void batch_wave_kernel(const KParams P, const WaveArgs A, int n_waves,
+                                                                             size_t wave_bytes, size_t row_bytes) {
+  // FIXED falls back to the 32-bit table, whose pad letter no alignment takes, where a letter is invalid: its H must be
+  // the one of aln_traceback's other kernel
+  constexpr bool kTable = PROF == kProfTable || FIXED;
+  __shared__ int32_t tab[kTable ? kTab * kTab : 1];
+  __shared__ uint32_t sig2[PROF == kProfTable ? 1 : kScoreWords];
+  extern __shared__ char smem[];
+  if constexpr (kTable) fill_table<kProfTable>(P, tab, nullptr);
+  if constexpr (PROF != kProfTable) fill_score_bytes(P, sig2);
+  __syncthreads();
+  const int lane = threadIdx.x & 63;
+  const int wib = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  char* lds = smem + wib * pair_lds_bytes(P.alphabet, PROF == kProfLane);
+  const int64_t wave = (int64_t)blockIdx.x * kPWavesPerBlock + wib;
+  if (wave >= n_waves) return;
+  char* slab = static_cast<char*>(A.ws) + wave * wave_bytes;
+  int2* row = reinterpret_cast<int2*>(slab);
+  uint16_t* codes = reinterpret_cast<uint16_t*>(slab + row_bytes);
+  const int64_t count = A.idx ? (int64_t)*A.idx_count : A.n_pairs;
+  for (int64_t slot = wave; slot < count; slot += n_waves) {
+    const int64_t p = A.idx ? (int64_t)A.idx[slot] : slot;
+    const int64_t qb = A.q_off[p], sb = A.s_off[p];
+    const int64_t nn = A.q_off[p + 1] - qb, mm = A.s_off[p + 1] - sb;
+    int n = 0, m = 0;
+    uint32_t flags = 0;
+    aln_result_t fw{};
+    if (nn > A.max_n || mm > A.max_m || nn < 0 || mm < 0) {
+      flags |= ALN_RES_TOO_LONG;
+    } else {
+      n = (int)nn;
+      m = (int)mm;
+    }
+    // the 16-bit kernel redoes these pairs in 32 bits (and no pair that it flags)
+    bool redo = !FIXED && A.use16 && flags == 0 && MODE != ALN_LOCAL && !fits16(P, n, m, true);
+    if (FIXED) {
+      fw = A.fwd[p];
+      flags |= fw.flags & (ALN_RES_BAD_CODE | ALN_RES_TOO_LONG | ALN_RES_DEVICE_ERROR);
+      if (!flags && (fw.q_end < 0 || fw.q_end > n || fw.s_end < 0 || fw.s_end > m)) flags |= ALN_RES_BAD_END;
+      n = flags ? 0 : fw.q_end;
+      m = flags ? 0 : fw.s_end;
+    }
+    const uint8_t* __restrict__ q = A.q + qb;
+    const uint8_t* __restrict__ s = A.s + sb;
+    bool bad = false;
+    int best = (MODE == ALN_GLOBAL && n + m > 0) ? P.go + (n + m) * P.ge : 0, bi = n, bj = m;
+    if (n > 0 && m > 0) {
+      int4 o = relax_pair<MODE, AFFINE, PROF, FA, FIXED>(P, tab, sig2, lds, q, n, s, m, lane, row, codes, bad);
+      if constexpr (FIXED && PROF != kProfTable) {
+        if (__any(bad))
+          o = relax_pair<MODE, AFFINE, kProfTable, FA, FIXED>(P, tab, sig2, lds, q, n, s, m, lane, row, codes, bad);
+      }
+      best = o.x;
+      if (!FIXED) {
+        bi = o.y;
+        bj = o.z;
+        if (MODE == ALN_LOCAL && best <= 0) {
+          best = bi = bj = 0;  // the empty alignment
+        } else if (MODE == ALN_SEMIGLOBAL && best <= 0) {
+          best = bi = 0;  // (0, m) precedes every other candidate in row-major order
+          bj = m;
+        }
+      }
+    } else {
+      // an empty side: no cell is relaxed, so the other side's letters are checked here (its border is not a cell)
+      for (int c = lane; c < n; c += 64) bad |= q[c] >= P.alphabet;
+      for (int c = lane; c < m; c += 64) bad |= s[c] >= P.alphabet;
+      if (!FIXED && MODE != ALN_GLOBAL) bi = bj = 0;
+    }
+    if (FIXED && !flags && best != fw.score) flags |= ALN_RES_BAD_END;
+    if (__any(bad)) {
+      flags |= ALN_RES_BAD_CODE;
+      redo = false;
+    }
+    if (!FIXED && A.use16 && flags == 0 && MODE == ALN_LOCAL && best >= 32767) redo = true;
+    aln_result_t res;
+    res.score = flags ? 0 : best;
+    res.q_begin = -1;
+    res.q_end = flags ? 0 : bi;
+    res.s_begin = -1;
+    res.s_end = flags ? 0 : bj;
+    res.cigar_len = 0;
+    res.reserved = 0;
+    if (!flags) {
+      const int64_t c0 = A.cigar_off[p];
+      const int64_t cap = A.cigar_off[p + 1] - c0;
+      WalkState S;
+      walk_start(S, bi, bj);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the codes are written before they are read
+      walk_core<MODE>(codes, m, 0, 0, S, reinterpret_cast<uint16_t*>(lds), lane, A.cigar + c0, cap);
+      const int64_t runs = walk_finish(S, lane, A.cigar + c0, cap);
+      res.q_begin = S.i;
+      res.s_begin = S.j;
+      res.cigar_len = (int)runs;
+      if (runs > cap) flags |= ALN_RES_CIGAR_TRUNC;
+      if (S.stuck) flags |= ALN_RES_DEVICE_ERROR;
+    }
+    res.flags = flags | (redo ? ALN_RES_INT32_REDO : 0u);
+    if (lane == 0) A.out[p] = res;
+    __builtin_amdgcn_wave_barrier();  // the wave stays together from pair to pair
+  }
+}
+
+size_t row_bytes(int64_t m) { return ((size_t)(m + 1) * sizeof(int2) + 255) & ~(size_t)255; }
+size_t code_bytes(int64_t n, int64_t m) {
+  return ((size_t)((n + kWfR - 1) / kWfR) * (size_t)m * sizeof(uint16_t) + 255) & ~(size_t)255;
+}
+
+template <int MODE, bool AFFINE, int PROF, bool FA>
+void launch_f(const KParams& kp, const WaveArgs& a, int waves, hipStream_t stream) {
+  const int blocks = (waves + kPWavesPerBlock - 1) / kPWavesPerBlock;
+  const size_t lds = (size_t)kPWavesPerBlock * pair_lds_bytes(kp.alphabet, PROF == kProfLane);
+  const size_t rb = row_bytes(a.lane_m), wb = rb + code_bytes(a.lane_n, a.lane_m);
+  if (a.fwd)
+    hipLaunchKernelGGL((batch_wave_kernel<MODE, AFFINE, PROF, FA, true>), dim3(blocks), dim3(64 * kPWavesPerBlock), lds,
+                       stream, kp, a, waves, wb, rb);
+  else
+    hipLaunchKernelGGL((batch_wave_kernel<MODE, AFFINE, PROF, FA, false>), dim3(blocks), dim3(64 * kPWavesPerBlock), lds,
+                       stream, kp, a, waves, wb, rb);
+}
+
+template <int MODE>
+void launch_m(const KParams& kp, const WaveArgs& a, int waves, hipStream_t stream) {
+  const bool bytes = kp.sigma_max - 2 * kp.ge <= 127 && kp.sigma_min - 2 * kp.ge >= -127;
+  const bool fa = band_fits_fa(kp, a.lane_n, a.lane_m);
+  auto go = [&](auto affine, auto lanes) {
+    constexpr bool kAffine = decltype(affine)::value, kFa = decltype(lanes)::value;
+    if (kAffine && !kFa)
+      launch_f<MODE, kAffine, kProfTable, kFa>(kp, a, waves, stream);  // gap scores in the thousands
+    else if (bytes && kp.alphabet <= 4)
+      launch_f<MODE, kAffine, kAffine && !kFa ? kProfTable : kProfReg, kFa>(kp, a, waves, stream);
+    else if (bytes)
+      launch_f<MODE, kAffine, kAffine && !kFa ? kProfTable : kProfLane, kFa>(kp, a, waves, stream);
+    else
+      launch_f<MODE, kAffine, kProfTable, kFa>(kp, a, waves, stream);
+  };
+  if (kp.go == 0)
+    go(std::false_type(), std::false_type());
+  else if (fa)
+    go(std::true_type(), std::true_type());
+  else
+    go(std::true_type(), std::false_type());
+}
+
+}  // namespace
+
+// The rule compares both kernels' times, from what they measured (picoseconds, 256 compute units).  One pair per wave:
+// 128 ps for every step of every band and pair, 105 steps a band beyond its columns (65,536 reads of 100..250 letters
+// 2.9 ms, of 20..30 letters 1.6 ms).  One pair per lane: a wave's largest pair alone, 56 ns a cell of it in 16 bits and 87 ns
+// in 32, 1.65 times that once two waves share a SIMD (reads of 100..250 letters 4.5 and 7.0 ms for up to 65,536 pairs,
+// 8.1 ms for 262,144 in 16 bits); a batch that more than fills those waves stays with them.  So reads of 100..250
+// letters go one per wave up to about 80,000 pairs (2.9 against 4.7 ms at 65,536), of 20..30 up to 5,000.
+int wave_pair_waves(int64_t n_pairs, int64_t lane_n, int64_t lane_m, size_t ws_bytes, bool use16) {
+  const int cus = device_cu_count();
+  if (cus <= 0 || n_pairs < 1 || lane_n < 1 || lane_m < 1) return 0;
+  const int64_t lane_waves = (n_pairs + (use16 ? 127 : 63)) / (use16 ? 128 : 64);
+  if (use16 && lane_waves > (int64_t)8 * cus) return 0;
+  const double t_wave = (double)n_pairs * (double)((lane_n + kPBand - 1) / kPBand) * (double)(lane_m + 105) * 0.128 * 256 / cus;
+  const double t_lane = (double)((lane_n + 15) / 16 * 16) * (double)lane_m * (use16 ? 56.0 : 87.0) *
+                        (lane_waves > (int64_t)4 * cus ? 1.65 * std::max(1.0, (double)lane_waves / (8 * cus)) : 1.0);
+  if (t_wave > t_lane) return 0;
+  const int64_t want = std::min<int64_t>(n_pairs, (int64_t)cus * kPWavesPerCU);
+  const int64_t fit = (int64_t)(ws_bytes / (row_bytes(lane_m) + code_bytes(lane_n, lane_m)));
+  return (int)std::min(want, fit);
+}
+
+aln_status_t launch_batch_wave(const KParams& kp, const WaveArgs& a, int waves, hipStream_t stream) {
+  ProfScope prof(a.fwd ? "batch_wave_traceback_from_end" : "batch_wave_traceback", stream);
+  switch (kp.mode) {
+    case ALN_GLOBAL:
+      launch_m<ALN_GLOBAL>(kp, a, waves, stream);
+      break;
+    case ALN_LOCAL:
+      launch_m<ALN_LOCAL>(kp, a, waves, stream);
+      break;
+    default:
+      launch_m<ALN_SEMIGLOBAL>(kp, a, waves, stream);
+      break;
+  }
+  return hipGetLastError() == hipSuccess ? ALN_OK : ALN_E_DEVICE;
+}
+
+}  // namespace mialign

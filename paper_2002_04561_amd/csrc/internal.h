@@ -166,6 +166,40 @@ aln_status_t plan_batch_i16(const KParams& kp, int64_t n_pairs, int64_t max_n, i
 aln_status_t launch_batch_i16(const KParams& kp, const BatchPlan16& plan, const I16Args& args, bool tb,
                               hipStream_t stream);
 
+// Whether the 16-bit kernel keeps an n x m pair's result without a 32-bit pass: every value lies in [3*go + (n+m)*ge,
+// min(n,m)*max(sigma_max,0)].
+constexpr int kBound16 = 32000;
+// biased: values carry the row bias of the global and semi-global recurrence (Hb = H - i*ge), which
+// lifts them by at most n*|ge|
+__host__ __device__ __forceinline__ bool fits16(const KParams& P, int n, int m, bool biased) {
+  const int mn = n < m ? n : m;
+  const long long up = (long long)mn * (P.sigma_max > 0 ? P.sigma_max : 0) - (biased ? (long long)n * P.ge : 0);
+  const long long lo = 3ll * P.go + (long long)(n + m) * P.ge;
+  return up <= kBound16 && lo >= -kBound16 && m < 32767;
+}
+
+// batch_wave.hip: one wave per pair
+struct WaveArgs {
+  const uint8_t* q;
+  const int64_t* q_off;
+  const uint8_t* s;
+  const int64_t* s_off;
+  int64_t n_pairs, max_n, max_m;  // pairs beyond the bounds are flagged
+  int64_t lane_n, lane_m;         // the largest sides a listed pair may have
+  const int* idx;                 // the pairs (null: all n_pairs in order), their number at *idx_count
+  const int* idx_count;
+  bool use16;                     // flag the pairs that the 16-bit kernel would leave to a 32-bit pass
+  const aln_result_t* fwd;        // aln_traceback: forward results, traced back from their end cells
+  aln_result_t* out;
+  uint32_t* cigar;
+  const int64_t* cigar_off;
+  void* ws;
+};
+// Waves of a one-wave-per-pair launch over at most n_pairs pairs of at most lane_n x lane_m, within ws_bytes of
+// workspace; 0 where the one-pair-per-lane kernels (16- or 32-bit) are the better choice.
+int wave_pair_waves(int64_t n_pairs, int64_t lane_n, int64_t lane_m, size_t ws_bytes, bool use16);
+aln_status_t launch_batch_wave(const KParams& kp, const WaveArgs& a, int waves, hipStream_t stream);
+
 // wf_i32.hip
 constexpr int kWfWavesPerCUDefault = 16;
 constexpr int kWfGroupBands = 4;  // bands (compute waves) of a workgroup of the grouped wavefront engine
