@@ -228,7 +228,7 @@ __global__ __launch_bounds__(64 * kPWavesPerBlock, 4) void batch_wave_kernel(con
       WalkState S;
       walk_start(S, bi, bj);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the codes are written before they are read
-      walk_core<MODE>(codes, m, 0, 0, S, reinterpret_cast<uint16_t*>(lds), lane, A.cigar + c0, cap);
+      walk_core<MODE>(codes, m, 0, 0, 0, S, reinterpret_cast<uint16_t*>(lds), lane, A.cigar + c0, cap);
       const int64_t runs = walk_finish(S, lane, A.cigar + c0, cap);
       res.q_begin = S.i;
       res.s_begin = S.j;

@@ -6,14 +6,15 @@
 // (H, F) of every kTileCols-th column, all rows.  Any tile of kTileRows x kTileCols cells can then be
 // relaxed again on its own from the row above it and the column left of it, replaying exactly the
 // forward pass's integers.  The walk goes back through segments of rows, bottom first.  For each
-// segment, the tiles at or above the walk's row and left of its column, within a window as wide as the
-// rows the walk has left in the segment plus kTbWinMargin columns, are relaxed again in parallel (one
-// workgroup of 4 band waves per tile), storing the 4-bit predecessor codes of walk.h for the segment
-// only; then one wave walks the segment (walk_wave.h).  A near-diagonal path crosses the segment inside
-// the window; a walk that reaches the window's left edge first stops there, the tiles left of the
-// window are relaxed again, and the walk goes on.  The walk then hands its position to the next
-// segment up.  Each cell is relaxed again at most once, so the whole traceback relaxes at most twice
-// the cells of the matrix; memory is one segment of codes plus the checkpoints, not a code per cell.
+// segment, the tiles that a path along the diagonal through the walk's cell crosses, kTbBandMargin columns
+// to either side, are relaxed again in parallel (one workgroup of 4 band waves per tile), storing the 4-bit
+// predecessor codes of walk.h for the segment only; then one wave walks the segment (walk_wave.h) as far as
+// those tiles reach.  Most walks end the segment so.  One that leaves the band is given a band around the cell
+// where it left, and after that, should it leave again, every tile above and left of it.  The walk then hands its
+// position to the next segment up.  Memory is one segment of codes plus the checkpoints, not a code per cell.
+//
+// Bound by the latency of a tile: 2048 columns and the lag of its 4 bands, 0.35 ms whatever runs beside it.  Relaxing every
+// tile left of the walk and above it took 4.9 ms on a 65536 x 65011 pair (2048 tiles), its band of 160 tiles 0.6.
 #include "band.h"
 #include "internal.h"
 #include "walk_wave.h"
@@ -24,7 +25,8 @@ namespace {
 constexpr int kTBlk = 32;      // steps between lane-0 input refills
 constexpr int kTRing = 256;    // columns held by the ring between two bands of a tile
 constexpr int kTWaves = kTileRows / kWfBand;  // bands (waves) of a tile
-constexpr int kTbWinMargin = 2 * kTileCols;   // window columns beyond the rows the walk has left
+constexpr int kTbBandMargin = kTileCols / 2;   // columns of a band to either side of the walk's diagonal
+constexpr int kTbPhases = 3;                   // two bands, then every tile
 
 // Profile kinds of the band wavefront (band.h): register bytes for up to 4 letters, else the LDS table.
 
@@ -38,25 +40,36 @@ struct TbView {
   uint16_t* codes;     // the current segment's codes: [row group][column - 1], stride m
   WalkState* walk;
   int* error;          // set when a bounded wait gives up
-  int* win_lo;         // the current segment's window: its first tile column
 };
 
-// First tile column of the window of a segment whose tiles are relaxed again from the walk at (i, j):
-// the walk's column minus the rows it has left in the segment and a margin.
-__device__ __forceinline__ int tb_window_lo(int i, int j, int seg_r0) {
-  const int c = j - (i - seg_r0) - kTbWinMargin;
-  return c > 0 ? c / kTileCols : 0;
+// The columns of a tile row (rows R0 + 1 .. R0 + kTileRows) that the band of a walk at (i, j) covers, in tiles lo .. hi:
+// the diagonal through (i, j) crosses the rows above it, up to row i, in columns j - (i - R0 - 1) .. j.
+__device__ __forceinline__ void tb_band(int i, int j, int R0, int* lo, int* hi) {
+  const int c_lo = j - (i - R0 - 1) - kTbBandMargin, c_hi = j - max(i - R0 - kTileRows, 0) + kTbBandMargin;
+  *lo = c_lo > 1 ? (c_lo - 1) / kTileCols : 0;
+  *hi = c_hi > 1 ? (min(c_hi, j) - 1) / kTileCols : -1;
 }
 
 // One tile of the segment `seg`, relaxed again with the codes stored.  Values are lane values of band.h, as in
 // the forward pass, so they are its own integers.
-// Phase 0 relaxes the tiles of the window, phase 1 (after a walk that stopped at the window's left
-// edge) those left of it.
+// Phases 0 and 1 relax the tiles of the walk's band, the last phase every tile above and left of the walk.
 template <int MODE, bool AFFINE, int PROF, bool FA>
 __global__ __launch_bounds__(64 * kTWaves) void tb_tile_kernel(const KParams P, const uint8_t* __restrict__ Q,
                                                               const uint8_t* __restrict__ S, TbView V, int seg,
                                                               int phase) {
   constexpr int R = kWfR, BLK = kTBlk;
+  const int n = V.n, m = V.m;
+  const int i_w = V.walk->i, j_w = V.walk->j, w_done = V.walk->done;
+  const int seg_r0 = seg * V.seg_rows;
+  const int tr = blockIdx.x / V.strips, sc = blockIdx.x % V.strips;
+  const int R0 = seg_r0 + tr * kTileRows, C0 = sc * kTileCols;
+  // only tiles at or above the walk's row and left of its column, in the segment it is in
+  if (w_done || i_w <= seg_r0 || R0 >= i_w || C0 >= j_w) return;
+  if (phase < kTbPhases - 1) {
+    int lo, hi;
+    tb_band(i_w, j_w, R0, &lo, &hi);
+    if (sc < lo || sc > hi) return;
+  }
   __shared__ int32_t tab[PROF == kProfTable ? kTab * kTab : 1];
   __shared__ int4 stage[kTWaves][3][BLK / 4];  // lane-0 inputs of BLK steps: H, E, letter
   __shared__ int2 ring[kTWaves][kTRing];       // ring w carries band w-1's bottom row to band w
@@ -77,16 +90,6 @@ __global__ __launch_bounds__(64 * kTWaves) void tb_tile_kernel(const KParams P, 
   if (threadIdx.x == 0) s_err = 0;
   __syncthreads();
   const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
-  const int n = V.n, m = V.m;
-  const int i_w = V.walk->i, j_w = V.walk->j, w_done = V.walk->done;
-  const int seg_r0 = seg * V.seg_rows;
-  const int tr = blockIdx.x / V.strips, sc = blockIdx.x % V.strips;
-  const int R0 = seg_r0 + tr * kTileRows, C0 = sc * kTileCols;
-  // only tiles at or above the walk's row and left of its column, in the segment it is in, and in
-  // (phase 0) or left of (phase 1) the segment's window
-  if (w_done || i_w <= seg_r0 || R0 >= i_w || C0 >= j_w) return;
-  const int lo = phase == 0 ? tb_window_lo(i_w, j_w, seg_r0) : *V.win_lo;
-  if (phase == 0 ? sc < lo : sc >= lo) return;
   const int rows_hi = min(n, i_w);
   const int cols = min(C0 + kTileCols, j_w) - C0;  // tile columns C0+1 .. C0+cols
   const int i0 = R0 + wib * kWfBand;               // this band's rows i0+1 .. i0+kWfBand
@@ -232,8 +235,8 @@ __global__ __launch_bounds__(64 * kTWaves) void tb_tile_kernel(const KParams P, 
   }
 }
 
-// One wave walks the codes of segment `seg` from where the walk stands, if it stands in it: in phase 0
-// up to the window's left edge (recorded for phase 1's tiles), in phase 1 on from there.
+// One wave walks the codes of segment `seg` from where the walk stands, if it stands in it, as far as the phase's tiles reach:
+// tile row by tile row through the band, or to the segment's top row.
 template <int MODE>
 __global__ __launch_bounds__(64) void tb_walk_kernel(TbView V, int seg, int phase, uint32_t* __restrict__ cig,
                                                      int64_t cap) {
@@ -242,13 +245,18 @@ __global__ __launch_bounds__(64) void tb_walk_kernel(TbView V, int seg, int phas
   WalkState S = *V.walk;
   const int seg_r0 = seg * V.seg_rows;
   if (S.done || S.i <= seg_r0) return;
-  int cb = 0;
-  if (phase == 0) {
-    const int lo = tb_window_lo(S.i, S.j, seg_r0);
-    cb = lo * kTileCols;
-    if (lane == 0) *V.win_lo = lo;
+  if (phase < kTbPhases - 1) {
+    const int ia = S.i, ja = S.j;
+    for (int R0 = seg_r0 + (ia - seg_r0 - 1) / kTileRows * kTileRows; R0 >= seg_r0 && !S.done && S.i > R0; R0 -= kTileRows) {
+      int lo, hi;
+      tb_band(ia, ja, R0, &lo, &hi);
+      if (S.j > 0 && (S.j <= lo * kTileCols || S.j > (hi + 1) * kTileCols)) break;  // the walk has left the band
+      walk_core<MODE>(V.codes, V.m, seg_r0, R0, lo * kTileCols, S, win, lane, cig, cap);
+      if (S.i > R0) break;  // done, or at the band's left edge
+    }
+  } else {
+    walk_core<MODE>(V.codes, V.m, seg_r0, seg_r0, 0, S, win, lane, cig, cap);
   }
-  walk_core<MODE>(V.codes, V.m, seg_r0, cb, S, win, lane, cig, cap);
   __syncthreads();  // every lane has read the state before lane 0 writes it
   if (lane == 0) *V.walk = S;
 }
@@ -266,7 +274,7 @@ __global__ __launch_bounds__(64) void tb_init_kernel(const aln_result_t* __restr
   if (r.flags) {
     S.done = 1;  // no CIGAR for a failed forward pass
   } else if (r.q_end == 0 || r.s_end == 0) {
-    walk_core<MODE>(nullptr, 0, 0, 0, S, win, lane, cig, cap);
+    walk_core<MODE>(nullptr, 0, 0, 0, 0, S, win, lane, cig, cap);
   }
   if (lane == 0) {
     *V.walk = S;
@@ -309,7 +317,7 @@ void launch_rounds(const KParams& kp, const uint8_t* q, const uint8_t* s, const 
   hipLaunchKernelGGL((tb_init_kernel<MODE>), dim3(1), dim3(64), 0, stream, out, V, cigar, cap);
   const bool bytes = kp.sigma_max - 2 * kp.ge <= 127 && kp.sigma_min - 2 * kp.ge >= -127;
   for (int seg = nseg - 1; seg >= 0; --seg) {
-    for (int phase = 0; phase < 2; ++phase) {
+    for (int phase = 0; phase < kTbPhases; ++phase) {
       {
         ProfScope prof("traceback_tiles", stream);
         auto tiles = [&](auto affine, auto lanes) {
@@ -357,10 +365,8 @@ aln_status_t plan_long_ls(int64_t n, int64_t m, int64_t code_budget, LongLsPlan*
   const int64_t ncols = pl->strips > 0 ? pl->strips - 1 : 0;
   pl->off_ckcols = off;
   off += a256((size_t)ncols * (size_t)pl->ck_ld * sizeof(int2));
-  // rows per segment: as many tile rows as the code budget allows, at least one.  A segment's window
-  // is about as wide as its rows, so shorter segments would relax fewer cells, but a tile takes its
-  // 2048 steps whatever the number of tiles beside it: taller segments keep more tiles in flight per
-  // launch (at 262144^2, segments of 8192 rows took 48.8 ms of tiles per traceback, of 32768 rows 20.1)
+  // rows per segment: as many tile rows as the code budget allows, at least one.  A tile takes its 2048 steps
+  // whatever the number of tiles beside it, so taller segments keep more tiles in flight per launch
   const int64_t rows_all = groups * kTileRows;
   int64_t seg = m > 0 ? code_budget * 2 / m / kTileRows * kTileRows : rows_all;
   if (seg < kTileRows) seg = kTileRows;
@@ -398,7 +404,6 @@ aln_status_t launch_long_ls(const KParams& kp, const LongLsPlan& pl, const uint8
   V.codes = reinterpret_cast<uint16_t*>(base + pl.off_codes);
   V.walk = reinterpret_cast<WalkState*>(base + pl.off_walk);
   V.error = reinterpret_cast<int*>(base + pl.off_walk + 128);
-  V.win_lo = reinterpret_cast<int*>(base + pl.off_walk + 192);
   switch (kp.mode) {
     case ALN_GLOBAL:
       launch_rounds<ALN_GLOBAL>(kp, q, s, V, pl.nseg, fa, out, cigar, cigar_cap, stream);
