@@ -9,8 +9,8 @@
 // segment, the tiles that a path along the diagonal through the walk's cell crosses, kTbBandMargin columns
 // to either side, are relaxed again in parallel (one workgroup of 4 band waves per tile), storing the 4-bit
 // predecessor codes of walk.h for the segment only; then one wave walks the segment (walk_wave.h) as far as
-// those tiles reach.  Most walks end the segment so.  One that leaves the band is given a band around the cell
-// where it left, and after that, should it leave again, every tile above and left of it.  The walk then hands its
+// those tiles reach.  Most walks end the segment so.  One that leaves the band is given a band 4 times as wide
+// around the cell where it left, then one 16 times as wide, then every tile above and left of it.  The walk then hands its
 // position to the next segment up.  Memory is one segment of codes plus the checkpoints, not a code per cell.
 //
 // Bound by the latency of a tile: 2048 columns and the lag of its 4 bands, 0.35 ms whatever runs beside it.  Relaxing every
@@ -25,8 +25,8 @@ namespace {
 constexpr int kTBlk = 32;      // steps between lane-0 input refills
 constexpr int kTRing = 256;    // columns held by the ring between two bands of a tile
 constexpr int kTWaves = kTileRows / kWfBand;  // bands (waves) of a tile
-constexpr int kTbBandMargin = kTileCols / 2;   // columns of a band to either side of the walk's diagonal
-constexpr int kTbPhases = 3;                   // two bands, then every tile
+constexpr int kTbBandMargin = kTileCols / 2;   // columns of the first band to either side of the walk's diagonal
+constexpr int kTbPhases = 4;                   // three bands, each 4 times as wide as the one before, then every tile
 
 // Profile kinds of the band wavefront (band.h): register bytes for up to 4 letters, else the LDS table.
 
@@ -42,17 +42,18 @@ struct TbView {
   int* error;          // set when a bounded wait gives up
 };
 
-// The columns of a tile row (rows R0 + 1 .. R0 + kTileRows) that the band of a walk at (i, j) covers, in tiles lo .. hi:
+// The columns of a tile row (rows R0 + 1 .. R0 + kTileRows) that a phase's band of a walk at (i, j) covers, in tiles lo .. hi:
 // the diagonal through (i, j) crosses the rows above it, up to row i, in columns j - (i - R0 - 1) .. j.
-__device__ __forceinline__ void tb_band(int i, int j, int R0, int* lo, int* hi) {
-  const int c_lo = j - (i - R0 - 1) - kTbBandMargin, c_hi = j - max(i - R0 - kTileRows, 0) + kTbBandMargin;
+__device__ __forceinline__ void tb_band(int i, int j, int R0, int phase, int* lo, int* hi) {
+  const int margin = kTbBandMargin << (2 * phase);
+  const int c_lo = j - (i - R0 - 1) - margin, c_hi = j - max(i - R0 - kTileRows, 0) + margin;
   *lo = c_lo > 1 ? (c_lo - 1) / kTileCols : 0;
   *hi = c_hi > 1 ? (min(c_hi, j) - 1) / kTileCols : -1;
 }
 
 // One tile of the segment `seg`, relaxed again with the codes stored.  Values are lane values of band.h, as in
 // the forward pass, so they are its own integers.
-// Phases 0 and 1 relax the tiles of the walk's band, the last phase every tile above and left of the walk.
+// The phases but the last relax the tiles of the walk's band, the last one every tile above and left of the walk.
 template <int MODE, bool AFFINE, int PROF, bool FA>
 __global__ __launch_bounds__(64 * kTWaves) void tb_tile_kernel(const KParams P, const uint8_t* __restrict__ Q,
                                                               const uint8_t* __restrict__ S, TbView V, int seg,
@@ -67,7 +68,7 @@ __global__ __launch_bounds__(64 * kTWaves) void tb_tile_kernel(const KParams P, 
   if (w_done || i_w <= seg_r0 || R0 >= i_w || C0 >= j_w) return;
   if (phase < kTbPhases - 1) {
     int lo, hi;
-    tb_band(i_w, j_w, R0, &lo, &hi);
+    tb_band(i_w, j_w, R0, phase, &lo, &hi);
     if (sc < lo || sc > hi) return;
   }
   __shared__ int32_t tab[PROF == kProfTable ? kTab * kTab : 1];
@@ -249,7 +250,7 @@ __global__ __launch_bounds__(64) void tb_walk_kernel(TbView V, int seg, int phas
     const int ia = S.i, ja = S.j;
     for (int R0 = seg_r0 + (ia - seg_r0 - 1) / kTileRows * kTileRows; R0 >= seg_r0 && !S.done && S.i > R0; R0 -= kTileRows) {
       int lo, hi;
-      tb_band(ia, ja, R0, &lo, &hi);
+      tb_band(ia, ja, R0, phase, &lo, &hi);
       if (S.j > 0 && (S.j <= lo * kTileCols || S.j > (hi + 1) * kTileCols)) break;  // the walk has left the band
       walk_core<MODE>(V.codes, V.m, seg_r0, R0, lo * kTileCols, S, win, lane, cig, cap);
       if (S.i > R0) break;  // done, or at the band's left edge

@@ -7,7 +7,8 @@
 // The walk of walk.h (the canonical rule: diagonal, then E, then F in the no-gap state; inside a gap
 // the gap-open predecessor wins ties; local walks stop at a cell whose H is 0, semi-global ones on
 // row 0 or column 0, global ones finish along row 0 or column 0), taken by one wave: the codes are
-// read from an LDS window of kWalkGroups row groups x kWalkCols columns ending at the current cell,
+// read from an LDS window along the diagonal up from the current cell (kWalkGroups row groups x kWalkCols columns each; a
+// window of 128 x 128 cells took 64 loads a lane and bound the walks of long pairs),
 // diagonal runs are taken up to 64 cells at a time (lane t looks at cell (i - t, j - t), and the first
 // lane whose cell is not a diagonal move, or lies outside the window or the codes, ends the run), and
 // gap runs are taken the same way along their column or row.  Every lane runs the same walk and
@@ -25,7 +26,11 @@
 namespace mialign {
 
 constexpr int kWalkGroups = 32;  // row groups (of kWfR rows) in a traceback window
-constexpr int kWalkCols = 128;   // columns in a traceback window
+constexpr int kWalkCols = 32;    // columns of each of them
+constexpr int kWalkLeft = 17;    // of these, left of the diagonal through the cell the window was loaded at
+// A cell is in the window while its diagonal lies this far left or right of that cell's (the columns of a row group are placed
+// for the group, so up to 3 columns are lost to either side).
+constexpr int kWalkDiagLo = -(kWalkLeft - 3), kWalkDiagHi = kWalkCols - 1 - kWalkLeft - 3;
 
 // A walk in progress.  Runs are stored last to first while walking; walk_finish reverses them.
 struct WalkState {
@@ -67,27 +72,27 @@ __device__ void walk_core(const uint16_t* __restrict__ codes, int64_t ld, int r0
   uint32_t cur_len = (uint32_t)__builtin_amdgcn_readfirstlane((int)S.cur_len);
   int64_t runs = S.runs;
   bool done = false;
-  // The window holds row groups g0-kWalkGroups+1..g0 of the segment and columns c0-kWalkCols+1..c0; it is
-  // loaded at the walk's cell, in row group g0 and column c0.  The walk only moves up and left, so every
-  // later cell is inside it as long as it lies at or below row ilo and at or right of column jlo (the
-  // window's first row and column inside the segment).  Before the first load nothing is inside.
-  int g0 = 0, c0 = 0, ilo = 0x7fffffff, jlo = 0x7fffffff;
+  // The window is loaded at the walk's cell (i0, c0), in row group g0: row group g0 - k, columns c0 - 4 k - kWalkLeft ...
+  // The walk only moves up and left, so a later cell is inside it while it lies at or below row ilo (the window's first row that
+  // the walk may take) and on a diagonal within kWalkDiagLo .. kWalkDiagHi of the window's.  Before the first load nothing is.
+  int g0 = 0, c0 = 0, i0 = 0, ilo = 0x7fffffff;
+  const int jlo = cb + 1;
   auto load = [&](int ii, int jj) {
     g0 = (ii - r0 - 1) / kWfR;
     c0 = jj;
+    i0 = ii;
     ilo = max(rs + 1, r0 + (g0 - kWalkGroups + 1) * kWfR + 1);
-    jlo = max(cb + 1, c0 - kWalkCols + 1);
     // Every load of the window is issued before the first LDS write, so the reload costs one memory
-    // latency rather than one per code.  A window cell outside the segment (row group < 0 or column
-    // < 1) loads the in-bounds cell (g0, c0) instead; it lies before row ilo or column jlo, so code()
-    // never reads it.  The loads carry no branches, so all of them stay in flight together.
+    // latency rather than one per code.  A window cell outside the segment (row group < 0) or the columns
+    // loads the in-bounds cell (g0, c0) instead; the walk never reads it.  The loads carry no branches, so all
+    // of them stay in flight together.
     constexpr int kPer = kWalkGroups * kWalkCols / 64;
     uint32_t v[kPer];
 #pragma unroll
     for (int u = 0; u < kPer; ++u) {
-      const int k = lane + 64 * u;
-      const int gg = g0 - k / kWalkCols, cc = c0 - k % kWalkCols;
-      const bool ok = gg >= 0 && cc >= 1;
+      const int w = lane + 64 * u;
+      const int k = w / kWalkCols, gg = g0 - k, cc = c0 - kWfR * k - kWalkLeft + w % kWalkCols;
+      const bool ok = gg >= 0 && cc >= 1 && cc <= ld;
       v[u] = codes[(size_t)(ok ? gg : g0) * (size_t)ld + (size_t)((ok ? cc : c0) - 1)];
     }
 #pragma unroll
@@ -97,7 +102,8 @@ __device__ void walk_core(const uint16_t* __restrict__ codes, int64_t ld, int r0
   // the code of a cell inside the window
   auto code = [&](int ii, int jj) -> uint32_t {
     const unsigned r = (unsigned)(ii - r0 - 1);
-    const uint32_t w = win[(g0 - (int)(r / kWfR)) * kWalkCols + (c0 - jj)];
+    const int k = g0 - (int)(r / kWfR);
+    const uint32_t w = win[k * kWalkCols + (jj - c0 + kWfR * k + kWalkLeft)];
     return (w >> (4 * (kWfR - 1 - r % kWfR))) & 15u;
   };
   // H came from the diagonal: bits 1..0 clear, or, without local zeros, bit 0
@@ -129,7 +135,8 @@ __device__ void walk_core(const uint16_t* __restrict__ codes, int64_t ld, int r0
       }
       if (i == rs) break;  // the rows above hold this cell
       if (cb > 0 && j == cb) break;  // the columns left of cb hold it
-      if (i < ilo || j < jlo) load(i, j);
+      const int off = (j - c0) - (i - i0);
+      if (i < ilo || off < kWalkDiagLo || off > kWalkDiagHi) load(i, j);
       // lanes t <= lim look at cells inside the window; the others read (i, j) and count as a
       // non-diagonal code, which ends the run
       const int lim = min(i - ilo, j - jlo);
@@ -143,11 +150,11 @@ __device__ void walk_core(const uint16_t* __restrict__ codes, int64_t ld, int r0
         push(ALN_CIGAR_M, (uint32_t)k);
         i -= k;
         j -= k;
-        continue;
       }
-      // lane 0 looked at (i, j) itself, which the window holds; its code also gives the first gap
+      if (k == 64 || k > lim) continue;
+      // lane k looked at the cell that ends the run, which the window holds; its code also gives the first gap
       // step, taken below without reading the cell again
-      const uint32_t c = (uint32_t)__builtin_amdgcn_readfirstlane((int)pc);
+      const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)pc, k);
       if (MODE == ALN_LOCAL && (c & 3u) == 2u) {
         done = true;  // H = 0
         break;
@@ -169,9 +176,14 @@ __device__ void walk_core(const uint16_t* __restrict__ codes, int64_t ld, int r0
       // on through a cell whose extension bit is set and which is not in row (column) 1; the first
       // cell that ends it is stepped through and returns the walk to H, unless it lies outside the
       // window, where the walk stops short of it and reloads.
-      if (i < ilo || j < jlo) load(i, j);
+      int off = (j - c0) - (i - i0);
+      if (i < ilo || off < kWalkDiagLo || off > kWalkDiagHi) {
+        load(i, j);
+        off = 0;
+      }
       const bool vert = state == 1;
-      const int lim = vert ? i - ilo : j - jlo;  // lanes t <= lim look at cells inside the window
+      // lanes t <= lim look at cells inside the window
+      const int lim = vert ? min(i - ilo, kWalkDiagHi - off) : min(j - jlo, off - kWalkDiagLo);
       const bool in = lane <= lim;
       const int t = in ? lane : 0;
       const int ii = vert ? i - t : i, jj = vert ? j : j - t;
