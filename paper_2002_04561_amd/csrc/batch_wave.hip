@@ -27,7 +27,7 @@ constexpr int kPStageBytes = 2 * 64 * 4;
 constexpr int kPLettersBytes = (int)((sizeof(LetterWindow<64>) + 15) / 16 * 16);
 __host__ __device__ constexpr int pair_lds_bytes(int alphabet, bool lane_profile) {
   const int relax = kPStageBytes + kPLettersBytes + (lane_profile ? (alphabet + 1) * 256 : 0);
-  const int walk = kWalkGroups * kWalkCols * 2;
+  const int walk = kWalkCodes * 2;
   return relax > walk ? relax : walk;
 }
 

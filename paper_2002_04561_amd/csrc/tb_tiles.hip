@@ -241,7 +241,7 @@ __global__ __launch_bounds__(64 * kTWaves) void tb_tile_kernel(const KParams P, 
 template <int MODE>
 __global__ __launch_bounds__(64) void tb_walk_kernel(TbView V, int seg, int phase, uint32_t* __restrict__ cig,
                                                      int64_t cap) {
-  __shared__ uint16_t win[kWalkGroups * kWalkCols];
+  __shared__ uint16_t win[kWalkCodes];
   const int lane = threadIdx.x;
   WalkState S = *V.walk;
   const int seg_r0 = seg * V.seg_rows;

@@ -7,8 +7,9 @@
 // The walk of walk.h (the canonical rule: diagonal, then E, then F in the no-gap state; inside a gap
 // the gap-open predecessor wins ties; local walks stop at a cell whose H is 0, semi-global ones on
 // row 0 or column 0, global ones finish along row 0 or column 0), taken by one wave: the codes are
-// read from an LDS window along the diagonal up from the current cell (kWalkGroups row groups x kWalkCols columns each; a
-// window of 128 x 128 cells took 64 loads a lane and bound the walks of long pairs),
+// read from an LDS window of kWalkCodes words loaded at the current cell (a window of 128 x 128 cells took 64 loads a lane and
+// bound the walks of long pairs): along the diagonal, or, where the walk mostly goes up or left, a rectangle of many rows or of
+// many columns (a 3500 x 300 global pair took 0.45 ms with the square one, 0.63 ms with diagonal ones alone, 0.34 ms so);
 // diagonal runs are taken up to 64 cells at a time (lane t looks at cell (i - t, j - t), and the first
 // lane whose cell is not a diagonal move, or lies outside the window or the codes, ends the run), and
 // gap runs are taken the same way along their column or row.  Every lane runs the same walk and
@@ -25,12 +26,19 @@
 
 namespace mialign {
 
-constexpr int kWalkGroups = 32;  // row groups (of kWfR rows) in a traceback window
-constexpr int kWalkCols = 32;    // columns of each of them
-constexpr int kWalkLeft = 17;    // of these, left of the diagonal through the cell the window was loaded at
-// A cell is in the window while its diagonal lies this far left or right of that cell's (the columns of a row group are placed
-// for the group, so up to 3 columns are lost to either side).
-constexpr int kWalkDiagLo = -(kWalkLeft - 3), kWalkDiagHi = kWalkCols - 1 - kWalkLeft - 3;
+constexpr int kWalkCodes = 1024;  // row group words (of kWfR rows) in a traceback window
+// Shapes: 32 row groups of 32 columns along the diagonal, the same as a rectangle, and 8 row groups of 128 columns.  The
+// rectangles end at the cell that they were loaded at.
+constexpr int kWalkLeft = 17;  // diagonal: columns left of the diagonal through the cell the window was loaded at
+// A cell is in a diagonal window while its diagonal lies this far left or right of that cell's (the columns of a row group are
+// placed for the group, so up to 3 columns are lost to either side).
+constexpr int kWalkDiagLo = -(kWalkLeft - 3), kWalkDiagHi = 32 - 1 - kWalkLeft - 3;
+
+template <int LOG_COLS, bool DIAG>
+struct WalkShape {
+  static constexpr int kLogCols = LOG_COLS;
+  static constexpr bool kDiag = DIAG;
+};
 
 // A walk in progress.  Runs are stored last to first while walking; walk_finish reverses them.
 struct WalkState {
@@ -72,43 +80,9 @@ __device__ void walk_core(const uint16_t* __restrict__ codes, int64_t ld, int r0
   uint32_t cur_len = (uint32_t)__builtin_amdgcn_readfirstlane((int)S.cur_len);
   int64_t runs = S.runs;
   bool done = false;
-  // The window is loaded at the walk's cell (i0, c0), in row group g0: row group g0 - k, columns c0 - 4 k - kWalkLeft ...
-  // The walk only moves up and left, so a later cell is inside it while it lies at or below row ilo (the window's first row that
-  // the walk may take) and on a diagonal within kWalkDiagLo .. kWalkDiagHi of the window's.  Before the first load nothing is.
-  int g0 = 0, c0 = 0, i0 = 0, ilo = 0x7fffffff;
-  const int jlo = cb + 1;
-  auto load = [&](int ii, int jj) {
-    g0 = (ii - r0 - 1) / kWfR;
-    c0 = jj;
-    i0 = ii;
-    ilo = max(rs + 1, r0 + (g0 - kWalkGroups + 1) * kWfR + 1);
-    // Every load of the window is issued before the first LDS write, so the reload costs one memory
-    // latency rather than one per code.  A window cell outside the segment (row group < 0) or the columns
-    // loads the in-bounds cell (g0, c0) instead; the walk never reads it.  The loads carry no branches, so all
-    // of them stay in flight together.
-    constexpr int kPer = kWalkGroups * kWalkCols / 64;
-    uint32_t v[kPer];
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      const int w = lane + 64 * u;
-      const int k = w / kWalkCols, gg = g0 - k, cc = c0 - kWfR * k - kWalkLeft + w % kWalkCols;
-      const bool ok = gg >= 0 && cc >= 1 && cc <= ld;
-      v[u] = codes[(size_t)(ok ? gg : g0) * (size_t)ld + (size_t)((ok ? cc : c0) - 1)];
-    }
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) win[lane + 64 * u] = (uint16_t)v[u];
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // the window is in LDS before it is read
-  };
-  // the code of a cell inside the window
-  auto code = [&](int ii, int jj) -> uint32_t {
-    const unsigned r = (unsigned)(ii - r0 - 1);
-    const int k = g0 - (int)(r / kWfR);
-    const uint32_t w = win[k * kWalkCols + (jj - c0 + kWfR * k + kWalkLeft)];
-    return (w >> (4 * (kWfR - 1 - r % kWfR))) & 15u;
-  };
   // H came from the diagonal: bits 1..0 clear, or, without local zeros, bit 0
   constexpr uint32_t kSrc = MODE == ALN_LOCAL ? 3u : 1u;
-  auto push = [&](uint32_t op, uint32_t len) {
+  auto push = [&](uint32_t op, uint32_t len) __attribute__((always_inline)) {
     if (op == cur_op) {
       cur_len += len;
       return;
@@ -121,85 +95,126 @@ __device__ void walk_core(const uint16_t* __restrict__ codes, int64_t ld, int r0
     cur_len = len;
   };
   int64_t turns = 2 * ((int64_t)i + j) + 64;
-  for (; turns > 0; --turns) {
-    if (state == 0) {
-      if (i == 0 || j == 0) {
-        if (MODE == ALN_GLOBAL) {
-          if (j > 0) push(ALN_CIGAR_D, (uint32_t)j);
-          if (i > 0) push(ALN_CIGAR_I, (uint32_t)i);
-          i = 0;
-          j = 0;
-        }
-        done = true;
-        break;
+
+  // Loads a window at the walk's cell and walks until it leaves it.
+  auto walk_window = [&](auto shape) __attribute__((always_inline)) {
+    constexpr int LC = decltype(shape)::kLogCols, kCols = 1 << LC, kGroups = kWalkCodes >> LC;
+    constexpr bool kDiag = decltype(shape)::kDiag;
+    constexpr int kSlope = kDiag ? kWfR : 0, kLeft = kDiag ? kWalkLeft : kCols - 1;
+    // Row group g0 - k's columns are c0 - kSlope k - kLeft ...  The walk only moves up and left, so a later cell is inside the
+    // window while it lies at or below row ilo and at or right of column jlo (the first that the walk may take) and, in a
+    // diagonal window, on a diagonal within kWalkDiagLo .. kWalkDiagHi of the first cell's.
+    const int g0 = (i - r0 - 1) / kWfR, c0 = j, i0 = i;
+    const int ilo = max(rs + 1, r0 + (g0 - kGroups + 1) * kWfR + 1);
+    const int jlo = kDiag ? cb + 1 : max(cb + 1, c0 - kLeft);
+    {
+      // Every load of the window is issued before the first LDS write, so the reload costs one memory
+      // latency rather than one per code.  A window cell outside the segment (row group < 0) or the columns
+      // loads the in-bounds cell (g0, c0) instead; the walk never reads it.  The loads carry no branches, so all
+      // of them stay in flight together.
+      constexpr int kPer = kWalkCodes / 64;
+      uint32_t v[kPer];
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) {
+        const int w = lane + 64 * u;
+        const int k = w >> LC, gg = g0 - k, cc = c0 - kSlope * k - kLeft + (w & (kCols - 1));
+        const bool ok = gg >= 0 && cc >= 1 && cc <= ld;
+        v[u] = codes[(size_t)(ok ? gg : g0) * (size_t)ld + (size_t)((ok ? cc : c0) - 1)];
       }
-      if (i == rs) break;  // the rows above hold this cell
-      if (cb > 0 && j == cb) break;  // the columns left of cb hold it
-      const int off = (j - c0) - (i - i0);
-      if (i < ilo || off < kWalkDiagLo || off > kWalkDiagHi) load(i, j);
-      // lanes t <= lim look at cells inside the window; the others read (i, j) and count as a
-      // non-diagonal code, which ends the run
-      const int lim = min(i - ilo, j - jlo);
-      const bool in = lane <= lim;
-      const int t = in ? lane : 0;
-      const uint32_t ct = code(i - t, j - t);
-      const uint32_t pc = in ? ct : 3u;
-      const unsigned long long stop = __builtin_amdgcn_ballot_w64((pc & kSrc) != 0u);
-      const int k = stop ? __builtin_ctzll(stop) : 64;
-      if (k > 0) {
-        push(ALN_CIGAR_M, (uint32_t)k);
-        i -= k;
-        j -= k;
-      }
-      if (k == 64 || k > lim) continue;
-      // lane k looked at the cell that ends the run, which the window holds; its code also gives the first gap
-      // step, taken below without reading the cell again
-      const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)pc, k);
-      if (MODE == ALN_LOCAL && (c & 3u) == 2u) {
-        done = true;  // H = 0
-        break;
-      }
-      state = (c & 2u) ? 2 : 1;
-      if (state == 1) {
-        push(ALN_CIGAR_I, 1);
-        if (!(c & 4u) || i == 1) state = 0;
-        --i;
-      } else {
-        push(ALN_CIGAR_D, 1);
-        if (!(c & 8u) || j == 1) state = 0;
-        --j;
-      }
-    } else {
-      if (state == 1 && i == rs) break;  // the vertical gap goes on in the rows above
-      if (cb > 0 && j == cb) break;       // the gap goes on in (or ends at) a column left of cb
-      // A gap run, up to 64 steps at a time: lane t looks at the t-th cell of the run.  The run goes
-      // on through a cell whose extension bit is set and which is not in row (column) 1; the first
-      // cell that ends it is stepped through and returns the walk to H, unless it lies outside the
-      // window, where the walk stops short of it and reloads.
-      int off = (j - c0) - (i - i0);
-      if (i < ilo || off < kWalkDiagLo || off > kWalkDiagHi) {
-        load(i, j);
-        off = 0;
-      }
-      const bool vert = state == 1;
-      // lanes t <= lim look at cells inside the window
-      const int lim = vert ? min(i - ilo, kWalkDiagHi - off) : min(j - jlo, off - kWalkDiagLo);
-      const bool in = lane <= lim;
-      const int t = in ? lane : 0;
-      const int ii = vert ? i - t : i, jj = vert ? j : j - t;
-      const uint32_t pc = code(ii, jj);
-      const bool more = in && (pc & (vert ? 4u : 8u)) != 0u && (vert ? ii : jj) > 1;
-      const unsigned long long stop = __builtin_amdgcn_ballot_w64(!more);
-      const int k = stop ? __builtin_ctzll(stop) : 64;
-      const bool ends = k < 64 && k <= lim;
-      const int steps = k + (ends ? 1 : 0);
-      push(vert ? ALN_CIGAR_I : ALN_CIGAR_D, (uint32_t)steps);
-      if (vert)
-        i -= steps;
-      else
-        j -= steps;
-      if (ends) state = 0;
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) win[lane + 64 * u] = (uint16_t)v[u];
+      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // the window is in LDS before it is read
     }
+    // the code of a cell inside the window
+    auto code = [&](int ii, int jj) __attribute__((always_inline)) -> uint32_t {
+      const unsigned r = (unsigned)(ii - r0 - 1);
+      const int k = g0 - (int)(r / kWfR);
+      const uint32_t w = win[k * kCols + (jj - c0 + kSlope * k + kLeft)];
+      return (w >> (4 * (kWfR - 1 - r % kWfR))) & 15u;
+    };
+    for (; turns > 0; --turns) {
+      if (state == 0) {
+        const int off = (j - c0) - (i - i0);
+        // (rows up to rs and columns up to cb are outside the window)
+        if (i < ilo || j < jlo || (kDiag && (off < kWalkDiagLo || off > kWalkDiagHi))) return;
+        // lanes t <= lim look at cells inside the window; the others read (i, j) and count as a
+        // non-diagonal code, which ends the run
+        const int lim = min(i - ilo, j - jlo);
+        const bool in = lane <= lim;
+        const int t = in ? lane : 0;
+        const uint32_t ct = code(i - t, j - t);
+        const uint32_t pc = in ? ct : 3u;
+        const unsigned long long ends = __builtin_amdgcn_ballot_w64((pc & kSrc) != 0u);
+        const int k = ends ? __builtin_ctzll(ends) : 64;
+        if (k > 0) {
+          push(ALN_CIGAR_M, (uint32_t)k);
+          i -= k;
+          j -= k;
+        }
+        if (k == 64 || k > lim) continue;
+        // lane k looked at the cell that ends the run, which the window holds; its code also gives the first gap
+        // step, taken below without reading the cell again
+        const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)pc, k);
+        if (MODE == ALN_LOCAL && (c & 3u) == 2u) {
+          done = true;  // H = 0
+          return;
+        }
+        const bool up = !(c & 2u);
+        push(up ? ALN_CIGAR_I : ALN_CIGAR_D, 1);
+        state = up ? ((c & 4u) && i > 1 ? 1 : 0) : ((c & 8u) && j > 1 ? 2 : 0);
+        i -= up ? 1 : 0;
+        j -= up ? 0 : 1;
+      } else {
+        // A gap run, up to 64 steps at a time: lane t looks at the t-th cell of the run.  The run goes
+        // on through a cell whose extension bit is set and which is not in row (column) 1; the first
+        // cell that ends it is stepped through and returns the walk to H, unless it lies outside the
+        // window, where the walk stops short of it and reloads.
+        const int off = (j - c0) - (i - i0);
+        if (i < ilo || j < jlo || (kDiag && (off < kWalkDiagLo || off > kWalkDiagHi))) return;
+        const bool vert = state == 1;
+        // lanes t <= lim look at cells inside the window
+        const int lim = vert ? (kDiag ? min(i - ilo, kWalkDiagHi - off) : i - ilo)
+                             : (kDiag ? min(j - jlo, off - kWalkDiagLo) : j - jlo);
+        const bool in = lane <= lim;
+        const int t = in ? lane : 0;
+        const int ii = vert ? i - t : i, jj = vert ? j : j - t;
+        const uint32_t pc = code(ii, jj);
+        const bool more = in && (pc & (vert ? 4u : 8u)) != 0u && (vert ? ii : jj) > 1;
+        const unsigned long long last = __builtin_amdgcn_ballot_w64(!more);
+        const int k = last ? __builtin_ctzll(last) : 64;
+        const bool ends = k < 64 && k <= lim;
+        const int steps = k + (ends ? 1 : 0);
+        push(vert ? ALN_CIGAR_I : ALN_CIGAR_D, (uint32_t)steps);
+        i -= vert ? steps : 0;
+        j -= vert ? 0 : steps;
+        if (ends) state = 0;
+      }
+    }
+  };
+  int pi = i, pj = j;  // the cell the last window was loaded at
+  while (turns > 0 && !done) {
+    if (state == 0 && (i == 0 || j == 0)) {
+      if (MODE == ALN_GLOBAL) {
+        if (j > 0) push(ALN_CIGAR_D, (uint32_t)j);
+        if (i > 0) push(ALN_CIGAR_I, (uint32_t)i);
+        i = 0;
+        j = 0;
+      }
+      done = true;
+      break;
+    }
+    if (state != 2 && i == rs) break;  // the rows above hold this cell, or the vertical gap goes on there
+    if (cb > 0 && j == cb) break;      // the columns left of cb hold it, or the gap goes on in (or ends at) them
+    // a gap that has left its window, or a walk that went twice as far up as left (or left as up) through the last
+    const int di = pi - i, dj = pj - j;
+    pi = i;
+    pj = j;
+    if (state ? state == 1 : di > 2 * dj)
+      walk_window(WalkShape<5, false>{});
+    else if (state ? state == 2 : dj > 2 * di)
+      walk_window(WalkShape<7, false>{});
+    else
+      walk_window(WalkShape<5, true>{});
   }
   if (turns <= 0) {
     S.stuck = 1;

@@ -942,7 +942,7 @@ __global__ __launch_bounds__(256) void wf_finish_kernel(const KParams P, WfWs W,
                                                         aln_result_t* __restrict__ out,
                                                         uint32_t* __restrict__ cigar, int64_t cigar_cap,
                                                         const int64_t* __restrict__ cigar_off) {
-  __shared__ uint16_t walk_win[TB ? 4 : 1][TB ? kWalkGroups * kWalkCols : 1];
+  __shared__ uint16_t walk_win[TB ? 4 : 1][TB ? kWalkCodes : 1];
   const int lane = threadIdx.x & 63;
   const int np = *W.n_pairs;
   const int waves = (int)gridDim.x * 4;
