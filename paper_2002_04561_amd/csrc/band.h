@@ -85,11 +85,19 @@ __device__ __forceinline__ uint32_t push_flag(uint32_t acc, uint32_t sign) {
   return __builtin_amdgcn_alignbit(acc, sign, 31);
 }
 
+// How a group of steps treats columns outside 1..m.  Local cells there need nothing: left of the matrix they hold the floor,
+// H = 0, which is column 0's value, and right of it they are below real cells.  In the other modes cells right of the matrix are
+// never used (column m is kept as it passes), and left of it they are kept at the border value by a floor of their own in the
+// first groups (kGroupStart).  Masking the updates instead took a branch a step, which kept the steps from overlapping, in the
+// 33 edge groups of a band (100003 reads of 100..250, scores: 2.26 ms, 2.14 so).
+// kGroupChecked masks them: the traceback's tiles start from any column.
+enum { kGroupInside = 0, kGroupStart = 1, kGroupChecked = 2 };
+
 // One column of a lane's rows.  in_h, in_e: H~ and E~ of the row above; in_c: the column letter (as the
-// profile kind wants it); pw: kProfLane, its words; fl[r]: the floor of row r.  With TB the column's R nibbles
+// profile kind wants it); pw: kProfLane, its words; fl[r]: the floor of row r (with FLOOR).  With TB the column's R nibbles
 // are shifted into acc; otherwise a local affine cell folds its floor into E, which leaves H as it is: the floor
 // is one of H's terms anyway, and an E raised to row i's floor stays below the floor of every row beneath it.
-template <int MODE, bool AFFINE, int PROF, bool TB, bool FA, int R>
+template <int MODE, bool AFFINE, int PROF, bool TB, bool FA, int R, bool FLOOR>
 __device__ __forceinline__ void band_column(const KParams& P, const int32_t* tab, const int (&prof)[R],
                                             const int (&pw)[(R + 3) / 4], int in_c, int in_h, int in_e,
                                             const int* fl, BandLane<R>& L, uint32_t& acc) {
@@ -106,13 +114,13 @@ __device__ __forceinline__ void band_column(const KParams& P, const int32_t* tab
     else
       d = hd + tab[prof[r] + in_c];
     const int gl = AFFINE ? L.g[r] : L.h[r];
-    constexpr bool kFold = MODE == ALN_LOCAL && AFFINE && !TB;
+    constexpr bool kFold = FLOOR && AFFINE && !TB;
     if (AFFINE)
       e = kFold ? max3i(e, gup, fl[r]) : max(e, gup);
     else
       e = gup;
     const int f = AFFINE ? max(L.f[r], gl) : gl;
-    const int dm = MODE == ALN_LOCAL && !kFold ? max(d, fl[r]) : d;
+    const int dm = FLOOR && !kFold ? max(d, fl[r]) : d;
     const int h = max3i(dm, e, f);
     if (TB) {
       if (AFFINE) {
@@ -165,23 +173,38 @@ __device__ __forceinline__ void load_words(const uint32_t* lp, BandIn<R>& I) {
   }
 }
 
-// Four steps.  Lane l of the wave is at columns j0 .. j0 + 3.  CHECKED: a lane outside columns 1..m keeps its state.
-// after(u) runs after step u.
-template <int MODE, bool AFFINE, int PROF, bool TB, bool FA, int R, bool CHECKED, typename After>
+// Four steps.  Lane l of the wave is at columns j0 .. j0 + 3.  after(u) runs after step u.
+template <int MODE, bool AFFINE, int PROF, bool TB, bool FA, int R, int EDGE, typename After>
 __device__ __forceinline__ void band_group(const KParams& P, const int32_t* tab, const int (&prof)[R],
                                            const BandIn<R>& I, int j0, int m, BandLane<R>& L, BandGroup<R>& G,
                                            After after) {
+  constexpr bool kStart = EDGE == kGroupStart && MODE != ALN_LOCAL;
+  constexpr bool kFloor = MODE == ALN_LOCAL || kStart;
   int fl[R + 3];
 #pragma unroll
-  for (int k = 0; k < R + 3; ++k)
-    fl[k] = MODE == ALN_LOCAL ? (k ? lane_add<FA>(L.floor0, -k * P.ge, P.fc[k]) : L.floor0) : 0;
+  for (int k = 0; k < R + 3; ++k) {
+    fl[k] = 0;
+    if (MODE == ALN_LOCAL) fl[k] = k ? lane_add<FA>(L.floor0, -k * P.ge, P.fc[k]) : L.floor0;
+  }
   uint32_t acc = 0;
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
     const int in_h = __builtin_amdgcn_update_dpp(I.vh[u], L.bot_h, 0x138, 0xf, 0xf, false);  // wave_shr:1
     const int in_e = AFFINE ? __builtin_amdgcn_update_dpp(I.ve[u], L.bot_e, 0x138, 0xf, 0xf, false) : 0;
-    if (!CHECKED || (j0 + u >= 1 && j0 + u <= m))
-      band_column<MODE, AFFINE, PROF, TB, FA, R>(P, tab, prof, I.pw[u], I.vc[u], in_h, in_e, fl + u, L, acc);
+    if constexpr (kStart) {
+      // the border value of the lane's first row left of column 1, and no floor from there on
+      const int level = MODE == ALN_GLOBAL ? lane_zero<FA>() + P.go
+                        : u                ? lane_add<FA>(L.floor0, -u * P.ge, P.fc[u])
+                                           : L.floor0;
+      int fs[R];
+      fs[0] = j0 + u <= 0 ? level : lane_neg<FA>();
+#pragma unroll
+      for (int r = 1; r < R; ++r)
+        fs[r] = MODE == ALN_GLOBAL ? fs[0] : lane_add<FA>(fs[0], -r * P.ge, P.fc[r]);
+      band_column<MODE, AFFINE, PROF, TB, FA, R, true>(P, tab, prof, I.pw[u], I.vc[u], in_h, in_e, fs, L, acc);
+    } else if (EDGE != kGroupChecked || (j0 + u >= 1 && j0 + u <= m)) {
+      band_column<MODE, AFFINE, PROF, TB, FA, R, kFloor>(P, tab, prof, I.pw[u], I.vc[u], in_h, in_e, fl + u, L, acc);
+    }
 #pragma unroll
     for (int r = 0; r < R; ++r) G.v[u][r] = AFFINE ? L.g[r] : L.h[r];
     G.oh[u] = L.bot_h;

@@ -59,8 +59,8 @@ struct LetterWindow {
 };
 
 // What a lane keeps of its best cells.  Local: the best score, the group of 4 steps that first reached it (its first
-// column and its cells' values), and the largest score known anywhere in the band minus one.  Semi-global: the best
-// of row n.
+// column and its cells' values), and the largest score known anywhere in the band minus one.  Otherwise: the best score in
+// column m and its row (kj), and the best of row n.
 template <int R>
 struct BandBest {
   int32_t bs = kNeg32;
@@ -184,6 +184,25 @@ __device__ __forceinline__ void track_last_row(const KParams& P, const BandLane<
   }
 }
 
+// After 4 steps that hold column m for some lanes: its best cell in rows below n, or (ROW_N: the global optimum and a given
+// end) its cell in row n.
+template <bool FA, int R, bool ROW_N>
+__device__ __forceinline__ void track_last_column(const KParams& P, const BandGroup<R>& G, int j0, int n, int m, int irow0,
+                                                  BandBest<R>& B) {
+  const bool here = j0 <= m && m <= j0 + 3;
+  const unsigned long long b0 = __builtin_amdgcn_ballot_w64((m - j0) & 1), b1 = __builtin_amdgcn_ballot_w64((m - j0) & 2);
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int v = mask_select(b1, mask_select(b0, G.v[3][r], G.v[2][r]), mask_select(b0, G.v[1][r], G.v[0][r]));
+    const int i = irow0 + r + 1;
+    const int sc = v - P.go - lane_zero<FA>() + (i + m) * P.ge;
+    if (here && (ROW_N ? i == n : i < n && sc > B.bs)) {
+      B.bs = sc;
+      B.kj = i;
+    }
+  }
+}
+
 // The start of a band: a lane's row letters (kPad past the end), profile, column 0 and empty bests.
 template <int MODE, int PROF, bool FA, int R>
 __device__ __forceinline__ void band_start(const KParams& P, const uint32_t* sig2, const uint8_t* __restrict__ q, int n, bool flip, int irow0,
@@ -204,8 +223,8 @@ __device__ __forceinline__ void band_start(const KParams& P, const uint32_t* sig
     rowc[r] = c;
   }
   band_profile<PROF, R>(P, sig2, rowc, flip, prof, lp);
-  // A local lane also runs its columns before the first: they hold the floor, which is column 0's value.
-  const int jstart = MODE == ALN_LOCAL ? -lane : 0;
+  // A lane also runs its columns before the first; global ones all hold column 0's value.
+  const int jstart = MODE == ALN_GLOBAL ? 0 : -lane;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     L.h[r] = border_h<MODE, FA>(P, irow0 + r + 1, jstart);
@@ -221,7 +240,7 @@ __device__ __forceinline__ void band_start(const KParams& P, const uint32_t* sig
 
 // The band's optimum in (score, i, j) order over the lane's rows, then across the wave.
 template <int MODE, bool FA, int R>
-__device__ __forceinline__ int4 band_optimum(const KParams& P, const BandLane<R>& L, const BandBest<R>& B, int n,
+__device__ __forceinline__ int4 band_optimum(const KParams& P, const BandBest<R>& B, int n,
                                              int m, bool flip, bool last_band, int irow0, bool bad, bool failed) {
   int bs = kNeg32, bi = 0, bjj = 0;
   const int rn = n - 1 - irow0;
@@ -231,17 +250,9 @@ __device__ __forceinline__ int4 band_optimum(const KParams& P, const BandLane<R>
   for (int r = 0; r < R; ++r) {
     const int i = irow0 + r + 1;
     if (i > n) continue;
-    int sc = 0, jj = 0;
-    bool cand = false;
-    if (MODE == ALN_LOCAL) {
-      sc = B.bs;
-      jj = bj;
-      cand = sc > 0 && r == br;
-    } else {
-      sc = L.h[r] - lane_zero<FA>() + (i + m) * P.ge;  // H(i, m): last-column candidate; row n is handled below
-      jj = m;
-      cand = MODE == ALN_SEMIGLOBAL ? i < n : i == n;
-    }
+    const int sc = B.bs, jj = MODE == ALN_LOCAL ? bj : m;
+    // row n's other columns are handled below
+    const bool cand = MODE == ALN_LOCAL ? sc > 0 && r == br : i == B.kj;
     // a flipped pair's cell (i, jj) is the call's cell (jj, i)
     const int ci = flip ? jj : i, cj = flip ? i : jj;
     if (cand && better(sc, ci, cj, bs, bi, bjj)) {

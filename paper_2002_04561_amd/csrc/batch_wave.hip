@@ -18,7 +18,9 @@ namespace mialign {
 namespace {
 
 constexpr int kPWavesPerBlock = 4;
-constexpr int kPWavesPerCU = 16;
+// Three waves a SIMD (168 registers each): four, with 128, spilled 9 to 180 of them (20011 reads of 100..250 traced back from
+// their ends 732 us, 722 so; 400 such reads with CIGARs 109 us, 104 so).
+constexpr int kPWavesPerCU = 12;
 constexpr int kPBand = 64 * kWfR;
 
 // LDS of one wave: while it relaxes, the stage of top-row inputs and outputs (H~ and E~ of 64 columns), the letter window and
@@ -54,7 +56,6 @@ __device__ __forceinline__ int4 relax_pair(const KParams& P, const int32_t* tab,
     uint16_t* __restrict__ codes = codes0 + (size_t)(b * 64 + lane) * (size_t)m;
     const bool last_band = b == nb - 1;
     const int rn = n - 1 - irow0;
-    int cap[R] = {};  // FIXED, local: the lane's values of column m (the others keep their state there)
     int c_next = 1 + lane <= m ? (int)s[lane] : -1;
     int c_idx = letter_index<PROF, R>(P, -1, false, bad);
     lett.clear_tail(lane);
@@ -90,19 +91,14 @@ __device__ __forceinline__ int4 relax_pair(const KParams& P, const int32_t* tab,
         const int ph = L.bot_h, pe = L.bot_e, floor0 = L.floor0;
         BandGroup<R> G;
         const bool inside = t0 >= 63 && t0 + 3 < m;
-        if (MODE == ALN_LOCAL || inside)
-          band_group<MODE, AFFINE, PROF, true, FA, R, false>(P, tab, prof, I, j0, m, L, G, [](int) {});
+        if (MODE == ALN_LOCAL || t0 >= 63)
+          band_group<MODE, AFFINE, PROF, true, FA, R, kGroupInside>(P, tab, prof, I, j0, m, L, G, [](int) {});
         else
-          band_group<MODE, AFFINE, PROF, true, FA, R, true>(P, tab, prof, I, j0, m, L, G, [](int) {});
+          band_group<MODE, AFFINE, PROF, true, FA, R, kGroupStart>(P, tab, prof, I, j0, m, L, G, [](int) {});
+        if ((MODE != ALN_LOCAL || FIXED) && t0 + 4 >= m)
+          track_last_column<FA, R, MODE == ALN_GLOBAL || FIXED>(P, G, j0, n, m, irow0, B);
         if (irow0 < n) store_codes<R>(G, codes, j0, m, inside);  // row groups past n have no room
-        if constexpr (FIXED) {
-          if (MODE == ALN_LOCAL && last_band && t0 + 3 >= m - 1) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-              for (int r = 0; r < R; ++r) cap[r] = j0 + u == m ? G.v[u][r] - P.go : cap[r];
-          }
-        } else {
+        if constexpr (!FIXED) {
           if constexpr (MODE == ALN_LOCAL) track_local<AFFINE, R>(P, L, G, floor0, j0, false, B);
           if (MODE == ALN_SEMIGLOBAL && last_band) track_last_row<AFFINE, R>(P, L, G, floor0, m, rn, j0, B);
         }
@@ -122,14 +118,10 @@ __device__ __forceinline__ int4 relax_pair(const KParams& P, const int32_t* tab,
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     if constexpr (FIXED) {
       if (last_band) {
-        int h = 0;
-#pragma unroll
-        for (int r = 0; r < R; ++r) h = r == rn ? (MODE == ALN_LOCAL ? cap[r] : L.h[r]) : h;
-        const int hn = __builtin_amdgcn_readlane(h, (n - 1 - i0) / R);
-        best = make_int4(hn - lane_zero<FA>() + (n + m) * P.ge, n, m, 0);
+        best = make_int4(__builtin_amdgcn_readlane(B.bs, (n - 1 - i0) / R), n, m, 0);
       }
     } else {
-      const int4 o = band_optimum<MODE, FA, R>(P, L, B, n, m, false, last_band, irow0, false, false);
+      const int4 o = band_optimum<MODE, FA, R>(P, B, n, m, false, last_band, irow0, false, false);
       if (better(o.x, o.y, o.z, best.x, best.y, best.z)) best = o;
     }
   }
@@ -139,7 +131,7 @@ __device__ __forceinline__ int4 relax_pair(const KParams& P, const int32_t* tab,
 // FIXED: trace back from the end cell a forward pass found (fwd[p].q_end, fwd[p].s_end); the pair is relaxed only up to that
 // cell, whose H must equal fwd[p].score.
 template <int MODE, bool AFFINE, int PROF, bool FA, bool FIXED>
-__global__ __launch_bounds__(64 * kPWavesPerBlock, 4) void batch_wave_kernel(const KParams P, const WaveArgs A, int n_waves,
+__global__ __launch_bounds__(64 * kPWavesPerBlock, kPWavesPerCU / 4) void batch_wave_kernel(const KParams P, const WaveArgs A, int n_waves,
                                                                              size_t wave_bytes, size_t row_bytes) {
   // FIXED falls back to the 32-bit table, whose pad letter no alignment takes, where a letter is invalid: its H must be
   // the one of aln_traceback's other kernel

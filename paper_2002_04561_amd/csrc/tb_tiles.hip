@@ -215,9 +215,9 @@ __global__ __launch_bounds__(64 * kTWaves) void tb_tile_kernel(const KParams P, 
         out_e = __builtin_amdgcn_update_dpp(L.bot_e, out_e, 0x130, 0xf, 0xf, false);
       };
       if (inside)
-        band_group<MODE, AFFINE, PROF, true, FA, R, false>(P, tab, prof, I, j0, cols, L, G, collect);
+        band_group<MODE, AFFINE, PROF, true, FA, R, kGroupInside>(P, tab, prof, I, j0, cols, L, G, collect);
       else
-        band_group<MODE, AFFINE, PROF, true, FA, R, true>(P, tab, prof, I, j0, cols, L, G, collect);
+        band_group<MODE, AFFINE, PROF, true, FA, R, kGroupChecked>(P, tab, prof, I, j0, cols, L, G, collect);
       store_codes<R>(G, codes, j0, cols, inside);
     }
     // lanes 64-BLK.. hold lane 63's outputs of steps tb..tb+BLK-1, i.e. tile columns tb-62..tb+BLK-63

@@ -225,11 +225,12 @@ __global__ __launch_bounds__(kWfBlockAlone, 4) void wf_i32_kernel(const KParams 
         const int ph = L.bot_h, pe = L.bot_e, floor0 = L.floor0;
         BandGroup<R> G;
         const bool inside = t0 >= 63 && t0 + 3 < m;
-        // local cells outside the matrix are harmless (raise_local_floor); the others keep their state there
-        if (MODE == ALN_LOCAL || inside)
-          band_group<MODE, AFFINE, PROF, TB, FA, R, false>(P, tab, prof, I, j0, m, L, G, [](int) {});
+        if (MODE == ALN_LOCAL || t0 >= 63)
+          band_group<MODE, AFFINE, PROF, TB, FA, R, kGroupInside>(P, tab, prof, I, j0, m, L, G, [](int) {});
         else
-          band_group<MODE, AFFINE, PROF, TB, FA, R, true>(P, tab, prof, I, j0, m, L, G, [](int) {});
+          band_group<MODE, AFFINE, PROF, TB, FA, R, kGroupStart>(P, tab, prof, I, j0, m, L, G, [](int) {});
+        if (MODE != ALN_LOCAL && t0 + 4 >= m)
+          track_last_column<FA, R, MODE == ALN_GLOBAL>(P, G, j0, n, m, irow0, B);
         if (TB) store_codes<R>(G, codes, j0, m, inside);
         if constexpr (MODE == ALN_LOCAL) track_local<AFFINE, R>(P, L, G, floor0, j0, flip, B);
         if (MODE == ALN_SEMIGLOBAL && last_band) track_last_row<AFFINE, R>(P, L, G, floor0, m, rn, j0, B);
@@ -256,7 +257,7 @@ __global__ __launch_bounds__(kWfBlockAlone, 4) void wf_i32_kernel(const KParams 
           __hip_atomic_store(W.flags + t, published, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     }
-    const int4 opt = band_optimum<MODE, FA, R>(P, L, B, n, m, flip, last_band, irow0, bad, failed);
+    const int4 opt = band_optimum<MODE, FA, R>(P, B, n, m, flip, last_band, irow0, bad, failed);
     if (lane == 0) W.band_res[t] = opt;
   }
 }
@@ -858,16 +859,17 @@ __global__ __launch_bounds__(kWfBlock, CKPT ? 3 : 4) void wf_i32_group_kernel(co
               dst[1] = make_int4(L.h[2], L.f[2], L.h[3], L.f[3]);
             }
           };
-          if (MODE == ALN_LOCAL || inside)
-            band_group<MODE, AFFINE, PROF, TB, FA, R, false>(P, tab, prof, I, j0, m, L, G, checkpoint);
+          if (MODE == ALN_LOCAL || t0 >= 63)
+            band_group<MODE, AFFINE, PROF, TB, FA, R, kGroupInside>(P, tab, prof, I, j0, m, L, G, checkpoint);
           else
-            band_group<MODE, AFFINE, PROF, TB, FA, R, true>(P, tab, prof, I, j0, m, L, G, checkpoint);
-        } else if (MODE == ALN_LOCAL || inside) {
-          // local cells outside the matrix are harmless (raise_local_floor); the others keep their state there
-          band_group<MODE, AFFINE, PROF, TB, FA, R, false>(P, tab, prof, I, j0, m, L, G, [](int) {});
+            band_group<MODE, AFFINE, PROF, TB, FA, R, kGroupStart>(P, tab, prof, I, j0, m, L, G, checkpoint);
+        } else if (MODE == ALN_LOCAL || t0 >= 63) {
+          band_group<MODE, AFFINE, PROF, TB, FA, R, kGroupInside>(P, tab, prof, I, j0, m, L, G, [](int) {});
         } else {
-          band_group<MODE, AFFINE, PROF, TB, FA, R, true>(P, tab, prof, I, j0, m, L, G, [](int) {});
+          band_group<MODE, AFFINE, PROF, TB, FA, R, kGroupStart>(P, tab, prof, I, j0, m, L, G, [](int) {});
         }
+        if (MODE != ALN_LOCAL && t0 + 4 >= m)
+          track_last_column<FA, R, MODE == ALN_GLOBAL>(P, G, j0, n, m, irow0, B);
         if (TB) store_codes<R>(G, codes, j0, m, inside);
         if constexpr (MODE == ALN_LOCAL) track_local<AFFINE, R>(P, L, G, floor0, j0, flip, B);
         if (MODE == ALN_SEMIGLOBAL && last_band) track_last_row<AFFINE, R>(P, L, G, floor0, m, rn, j0, B);
@@ -885,7 +887,7 @@ __global__ __launch_bounds__(kWfBlock, CKPT ? 3 : 4) void wf_i32_group_kernel(co
           __hip_atomic_store(&pub[cw + 1], min(hi, m), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       }
     }
-    const int4 opt = band_optimum<MODE, FA, R>(P, L, B, n, m, flip, last_band, irow0, bad, failed);
+    const int4 opt = band_optimum<MODE, FA, R>(P, B, n, m, flip, last_band, irow0, bad, failed);
     if (lane == 0) W.band_res[t] = opt;
     }
     }
