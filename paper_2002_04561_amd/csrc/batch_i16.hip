@@ -22,6 +22,8 @@
 #include "internal.h"
 #include "walk.h"
 
+#include <algorithm>
+
 namespace mialign {
 namespace {
 
@@ -47,6 +49,16 @@ __device__ __forceinline__ s2 pk(int lo, int hi) {
 }
 __device__ __forceinline__ uint32_t bits(s2 x) { return __builtin_bit_cast(uint32_t, x); }
 __device__ __forceinline__ s2 from_bits(uint32_t x) { return __builtin_bit_cast(s2, x); }
+__device__ __forceinline__ s2 mxu(s2 a, s2 b) {
+  return __builtin_bit_cast(s2, __builtin_elementwise_max(__builtin_bit_cast(u2, a), __builtin_bit_cast(u2, b)));
+}
+// Per half, the largest of three values below 0x7c00: as half floats of these bits they order as integers, and the maximum of
+// three is one instruction there (there is none for packed integers).
+__device__ __forceinline__ s2 mx3_15(s2 a, s2 b, s2 c) {
+  uint32_t r;
+  asm("v_pk_maximum3_f16 %0, %1, %2, %3" : "=v"(r) : "v"(bits(a)), "v"(bits(b)), "v"(bits(c)));
+  return from_bits(r);
+}
 __device__ __forceinline__ int lo16(s2 x) { return (int)x.x; }
 __device__ __forceinline__ int hi16(s2 x) { return (int)x.y; }
 // a * b + c on unsigned halves (small non-negative values)
@@ -78,6 +90,18 @@ __device__ __forceinline__ uint32_t tree_pick(const uint32_t* x, const uint32_t*
   return t[0];
 }
 
+// The 15-bit cells (kWord): a global or semi-global batch over at most 4 letters whose values, with a bias of -ge for every row
+// and column and of kept zero -3 go, all lie in 0 .. kWordTop (word_cells).  Then
+//   E~(i, j) = max(E~(i-1, j), g(i-1, j)),  F~(i, j) = max(F~(i, j-1), g(i, j-1)),  g = H~ + go,
+//   H~(i, j) = max(g(i-1, j-1) + (sigma - 2 ge - go), E~, F~):
+// neither gap costs an add, the one g of a cell serves three neighbours, no half carries into the other (so both are added as
+// one 32-bit word), and the four scores of a row's letter are the bytes of one word, non-negative, so one v_perm picks both
+// pairs' scores from registers: no profile in LDS.  Cells outside a pair add 0 and reach no cell inside.
+// It is 15 instructions a row with codes, 17 and the profile's reads with the general cells, and VALU issue bounds both (1048576
+// reads of 100..250 with CIGARs: 18.3 ms with the general cells, 17.9 with these, 16.6 with the loop's branches gone as well,
+// where issue takes 84% of the time; codes and rows between strips are 54 GB of memory traffic, 3.2 TB/s).
+constexpr int kWordTop = 0x7bff;
+
 // LDS query profile of one wave, in 32-bit words.  For letter c, the R scores of a pair slot are
 // W = R/2 words, cut into chunks of CW words (one ds_read_b128, or b64 when R = 4); chunk k of every
 // slot of a letter lies in one block, [letter][chunk][slot][CW words].  Each letter block spans a
@@ -100,8 +124,8 @@ __device__ __forceinline__ int64_t next_group(int* ticket, int lane) {
   return (int64_t)__shfl(g, 0, 64);
 }
 
-template <int MODE, bool AFFINE, bool TB, int R>
-__global__ __launch_bounds__(kI16Block) void batch_i16_kernel(
+template <int MODE, bool AFFINE, bool TB, int R, bool WORD>
+__global__ __launch_bounds__(kI16Block, 2) void batch_i16_kernel(
     const KParams P, const uint8_t* __restrict__ q, const int64_t* __restrict__ q_off, const uint8_t* __restrict__ s,
     const int64_t* __restrict__ s_off, int64_t n_pairs, int64_t max_n, int64_t max_m, aln_result_t* __restrict__ out,
     uint32_t* __restrict__ cigar, const int64_t* __restrict__ cigar_off, char* __restrict__ ws, size_t slab_bytes,
@@ -114,8 +138,24 @@ __global__ __launch_bounds__(kI16Block) void batch_i16_kernel(
   // every term of row i shifted by the same constant.  Local pairs, whose floor H = 0 would become a
   // per-row constant, keep plain values.
   constexpr bool kBias = MODE != ALN_LOCAL;
+  static_assert(!WORD || (MODE != ALN_LOCAL && R == 16), "15-bit cells");
   extern __shared__ char smem[];
   int32_t* tab = reinterpret_cast<int32_t*>(smem);
+  // WORD: the byte scores of each query letter (4: none, all 0), one word each
+  uint32_t* rowsig = reinterpret_cast<uint32_t*>(smem);
+  const int kept0 = -3 * P.go;  // WORD: the kept value of 0
+  if constexpr (WORD) {
+    if (threadIdx.x < 5) {
+      uint32_t w = 0;
+      for (int b = 0; b < 4; ++b) {
+        const int a = threadIdx.x;
+        if (a >= P.alphabet || b >= P.alphabet) continue;
+        const int v = (P.use_table ? (int)P.sig[a * kMaxAlphabet + b] : (a == b ? P.match : P.mismatch)) - 2 * P.ge - P.go;
+        w |= (uint32_t)(v & 0xff) << (8 * b);
+      }
+      rowsig[threadIdx.x] = w;
+    }
+  } else
   for (int k = threadIdx.x; k < kTab * kTab; k += blockDim.x) {
     const int a = k / kTab, b = k % kTab;
     int32_t v;
@@ -135,7 +175,7 @@ __global__ __launch_bounds__(kI16Block) void batch_i16_kernel(
   uint32_t* __restrict__ profw =
       reinterpret_cast<uint32_t*>(smem + kI16ProfBase) + (size_t)wib * i16_wave_prof_words(AP, R);
   uint32_t* __restrict__ padw = profw + (size_t)AP * SC;
-  if (lane < W) padw[lane] = (0xffffu & (uint32_t)kPadSigma16) | ((uint32_t)kPadSigma16 << 16);  // read by this wave only
+  if (!WORD && lane < W) padw[lane] = (0xffffu & (uint32_t)kPadSigma16) | ((uint32_t)kPadSigma16 << 16);  // read by this wave only
 
   const int64_t wave = (int64_t)blockIdx.x * kI16WavesPerBlock + wib;
   char* slab = ws + wave * slab_bytes;
@@ -215,6 +255,11 @@ __global__ __launch_bounds__(kI16Block) void batch_i16_kernel(
           else
             bad[1] = true;
         }
+        // WORD: selector bytes of v_perm (0x0c selects zero)
+        if (WORD) {
+          ca = ca < P.alphabet ? ca : 0x0c;
+          cb = cb < P.alphabet ? 4 + cb : 0x0c;
+        }
         if (j0 + u <= mmax) letters[(size_t)(j0 + u - 1) * 64 + lane] = (uint16_t)(ca | (cb << 8));
       }
     }
@@ -229,36 +274,53 @@ __global__ __launch_bounds__(kI16Block) void batch_i16_kernel(
 
     for (int k = 0; k < strips; ++k) {
       const int i0 = k * R;
-      // query profile of this strip for both pairs: row r of letter c is sigma(q_{i0+r+1}, c)
-      for (int h = 0; h < 2; ++h) {
-        uint32_t* pr = profw + (size_t)(h * 64 + lane) * CW;
-        int qc[R];
+      uint32_t sig[2][R];  // WORD
+      if constexpr (WORD) {
+        for (int h = 0; h < 2; ++h) {
+          int qc[R];
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const int i = i0 + 1 + r;
-          int c = kPad;
-          if (i <= nn[h]) {
-            c = q[qb[h] + i - 1];
-            if (c >= P.alphabet) {
+          for (int r = 0; r < R; ++r) qc[r] = i0 + 1 + r <= nn[h] ? (int)q[qb[h] + i0 + r] : 4;
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            if (i0 + 1 + r <= nn[h] && qc[r] >= P.alphabet) {
               bad[h] = true;
-              c = kPad;
+              qc[r] = 4;
             }
+            sig[h][r] = rowsig[qc[r]];
           }
-          qc[r] = c * kTab;
         }
-        for (int c = 0; c < AP; ++c) {
-          const int cc = c < P.alphabet ? c : kPad;
-          uint32_t w[W];
+      } else {
+        // query profile of this strip for both pairs: row r of letter c is sigma(q_{i0+r+1}, c)
+        for (int h = 0; h < 2; ++h) {
+          uint32_t* pr = profw + (size_t)(h * 64 + lane) * CW;
+          int qc[R];
 #pragma unroll
-          for (int r = 0; r < R; r += 2)
-            w[r / 2] = (uint32_t)(tab[qc[r] + cc] & 0xffff) | ((uint32_t)tab[qc[r + 1] + cc] << 16);
-          uint32_t* dst = pr + (size_t)c * SC;
+          for (int r = 0; r < R; ++r) {
+            const int i = i0 + 1 + r;
+            int c = kPad;
+            if (i <= nn[h]) {
+              c = q[qb[h] + i - 1];
+              if (c >= P.alphabet) {
+                bad[h] = true;
+                c = kPad;
+              }
+            }
+            qc[r] = c * kTab;
+          }
+          for (int c = 0; c < AP; ++c) {
+            const int cc = c < P.alphabet ? c : kPad;
+            uint32_t w[W];
 #pragma unroll
-          for (int k = 0; k < NCH; ++k) {
-            if constexpr (CW == 4)
-              *reinterpret_cast<uint4*>(dst + k * SCH) = make_uint4(w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3]);
-            else
-              *reinterpret_cast<uint2*>(dst + k * SCH) = make_uint2(w[2 * k], w[2 * k + 1]);
+            for (int r = 0; r < R; r += 2)
+              w[r / 2] = (uint32_t)(tab[qc[r] + cc] & 0xffff) | ((uint32_t)tab[qc[r + 1] + cc] << 16);
+            uint32_t* dst = pr + (size_t)c * SC;
+#pragma unroll
+            for (int k = 0; k < NCH; ++k) {
+              if constexpr (CW == 4)
+                *reinterpret_cast<uint4*>(dst + k * SCH) = make_uint4(w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3]);
+              else
+                *reinterpret_cast<uint2*>(dst + k * SCH) = make_uint2(w[2 * k], w[2 * k + 1]);
+            }
           }
         }
       }
@@ -267,13 +329,16 @@ __global__ __launch_bounds__(kI16Block) void batch_i16_kernel(
       for (int r = 0; r < R; ++r) {
         const int i = i0 + 1 + r;
         hl[r] = sp((MODE == ALN_GLOBAL) ? P.go + (kBias ? 0 : i * P.ge) : (kBias ? -i * P.ge : 0));
-        f[r] = neg2;
+        // WORD: hl holds g, H~ + go; no gap reaches column 0's right, as 0 is below every kept value
+        if (WORD) hl[r] = sp(kept0 + P.go + (MODE == ALN_GLOBAL ? P.go : -i * P.ge));
+        f[r] = WORD ? zero : neg2;
         bv[r] = sp(-32768);
         bjr[r] = zero;
         cap[r] = zero;
       }
       // H(i0, 0), with the row bias where it applies
       s2 hdiag = sp((MODE == ALN_GLOBAL && i0 > 0) ? P.go + (kBias ? 0 : i0 * P.ge) : (kBias ? -i0 * P.ge : 0));
+      if (WORD) hdiag = sp(kept0 + P.go + (MODE == ALN_GLOBAL ? (i0 > 0 ? P.go : 0) : -i0 * P.ge));  // g(i0, 0)
       const int rnA = nn[0] - 1 - i0, rnB = nn[1] - 1 - i0;
       const bool lastA = rnA >= 0 && rnA < R, lastB = rnB >= 0 && rnB < R;
       const bool track_last = (MODE == ALN_SEMIGLOBAL) && __any(lastA || lastB);
@@ -283,86 +348,129 @@ __global__ __launch_bounds__(kI16Block) void batch_i16_kernel(
 #pragma unroll
       for (int b = 0; b < kRB; ++b)
         rnb[b] = (((rnA >> b) & 1) ? 0x0000ffffu : 0u) | (((rnB >> b) & 1) ? 0xffff0000u : 0u);
-      // Letters and top-row inputs of column j (the pad letter of the profile past a subject's end).
+      // Letters and top-row inputs of column j.  With codes to store, nothing here or in a column branches around a load or a
+      // store: both share one counter of outstanding accesses, and after a branch that may have stored, the wait for a load is
+      // one for every store as well, a memory write's latency every 4 columns (1048576 reads of 100..250 with CIGARs 17.9 ms,
+      // 16.5 so).  Without codes the accesses saved are worth more (200003 peptides: 1.32 ms so, 1.22 with the branches).
       auto fetch = [&](int j, int& ca, int& cb, uint2& top) {
-        const uint32_t l2 = j <= mmax ? (uint32_t)letters[(size_t)(j - 1) * 64 + lane] : 0u;
-        ca = j <= mmax ? (int)(l2 & 0xffu) : P.alphabet;
-        cb = j <= mmax ? (int)(l2 >> 8) : P.alphabet;
-        if (k == 0)
-          top = make_uint2(bits(sp((MODE == ALN_GLOBAL) ? P.go + j * P.ge : 0)), bits(neg2));
-        else
-          top = (j <= mmax) ? rowbuf[(size_t)j * 64 + lane] : make_uint2(0u, 0u);
+        const uint2 border =
+            WORD ? make_uint2(bits(sp(kept0 + P.go + (MODE == ALN_GLOBAL ? P.go : -j * P.ge))), 0u)
+                 : make_uint2(bits(sp((MODE == ALN_GLOBAL) ? P.go + j * P.ge : 0)), bits(neg2));
+        uint32_t l2 = 0u;
+        uint2 above = make_uint2(0u, 0u);
+        if constexpr (TB) {
+          const int jc = min(j, mmax);  // (columns past mmax are not relaxed)
+          l2 = letters[(size_t)max(jc - 1, 0) * 64 + lane];
+          above = rowbuf[(size_t)jc * 64 + lane];
+        } else if (j <= mmax) {
+          l2 = letters[(size_t)(j - 1) * 64 + lane];
+          if (k > 0) above = rowbuf[(size_t)j * 64 + lane];
+        }
+        ca = WORD ? (int)l2 : (int)(l2 & 0xffu);
+        cb = WORD ? 0 : (int)(l2 >> 8);
+        top.x = k == 0 ? border.x : above.x;
+        top.y = k == 0 ? border.y : above.y;
       };
       // One column of the strip for both pairs.
       auto column = [&](int j, int ca, int cb, uint2 top) {
         s2 hup = from_bits(top.x), eup = from_bits(top.y);
         s2 hd = hdiag;
         hdiag = hup;
-        // chunk k of a slot's letter is SCH words after chunk k-1; the pad row's chunks are adjacent
-        const uint32_t* pa = ca < AP ? profw + (size_t)ca * SC + (size_t)lane * CW : padw;
-        const uint32_t* pb = cb < AP ? profw + (size_t)cb * SC + (size_t)(64 + lane) * CW : padw;
-        const int sa = ca < AP ? SCH : CW, sb2 = cb < AP ? SCH : CW;
         uint32_t wa[W], wb[W];
+        if constexpr (!WORD) {
+          // chunk k of a slot's letter is SCH words after chunk k-1; the pad row's chunks are adjacent
+          const uint32_t* pa = ca < AP ? profw + (size_t)ca * SC + (size_t)lane * CW : padw;
+          const uint32_t* pb = cb < AP ? profw + (size_t)cb * SC + (size_t)(64 + lane) * CW : padw;
+          const int sa = ca < AP ? SCH : CW, sb2 = cb < AP ? SCH : CW;
 #pragma unroll
-        for (int k = 0; k < NCH; ++k) {
-          if constexpr (CW == 4) {
-            const uint4 va = *reinterpret_cast<const uint4*>(pa + k * sa);
-            const uint4 vb = *reinterpret_cast<const uint4*>(pb + k * sb2);
-            wa[4 * k] = va.x, wa[4 * k + 1] = va.y, wa[4 * k + 2] = va.z, wa[4 * k + 3] = va.w;
-            wb[4 * k] = vb.x, wb[4 * k + 1] = vb.y, wb[4 * k + 2] = vb.z, wb[4 * k + 3] = vb.w;
-          } else {
-            const uint2 va = *reinterpret_cast<const uint2*>(pa + k * sa);
-            const uint2 vb = *reinterpret_cast<const uint2*>(pb + k * sb2);
-            wa[2 * k] = va.x, wa[2 * k + 1] = va.y;
-            wb[2 * k] = vb.x, wb[2 * k + 1] = vb.y;
+          for (int k = 0; k < NCH; ++k) {
+            if constexpr (CW == 4) {
+              const uint4 va = *reinterpret_cast<const uint4*>(pa + k * sa);
+              const uint4 vb = *reinterpret_cast<const uint4*>(pb + k * sb2);
+              wa[4 * k] = va.x, wa[4 * k + 1] = va.y, wa[4 * k + 2] = va.z, wa[4 * k + 3] = va.w;
+              wb[4 * k] = vb.x, wb[4 * k + 1] = vb.y, wb[4 * k + 2] = vb.z, wb[4 * k + 3] = vb.w;
+            } else {
+              const uint2 va = *reinterpret_cast<const uint2*>(pa + k * sa);
+              const uint2 vb = *reinterpret_cast<const uint2*>(pb + k * sb2);
+              wa[2 * k] = va.x, wa[2 * k + 1] = va.y;
+              wb[2 * k] = vb.x, wb[2 * k + 1] = vb.y;
+            }
           }
         }
+        // bytes (letter of A, 0x0c, letter of B, 0x0c)
+        const uint32_t sel = WORD ? __builtin_amdgcn_perm((uint32_t)ca, 0x0c0c0c0cu, 0x00050004u) : 0u;
         uint32_t acc[RW];
 #pragma unroll
         for (int w = 0; w < RW; ++w) acc[w] = 0;
         const s2 jj = sp(j);
+        if constexpr (WORD) {
+          const uint32_t k7 = 0x7fff7fffu, gow = 0x00010001u * (uint32_t)(-P.go);
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const s2 sg = from_bits(__builtin_amdgcn_perm(wb[r / 2], wa[r / 2], (r & 1) ? 0x07060302u : 0x05040100u));
-          const s2 hlo = hl[r];
-          const s2 d = adds(hd, sg);
-          const s2 tup = adds(hup, kBias ? go2 : goe2);
-          const s2 e = AFFINE ? mx(kBias ? eup : adds(eup, ge2), tup) : (kBias ? hup : adds(hup, ge2));
-          const s2 tle = adds(hlo, goe2);
-          const s2 ff = AFFINE ? mx(adds(f[r], ge2), tle) : adds(hlo, ge2);
-          s2 hv = mx(mx(d, e), ff);
-          if (MODE == ALN_LOCAL) hv = mx(hv, zero);
-          if (kFlagCodes) {
-            // words 2g and 2g + 1 of the column hold row group g; byte order (pair A, pair B) per flag
-            const uint32_t bit = 0x01010101u << (r & 7);
-            const uint32_t nd_ne = __builtin_amdgcn_perm(bits(subs(e, hv)), bits(subs(d, hv)), 0x0b0a0908u);
-            acc[2 * (r >> 3)] = (nd_ne & bit) | acc[2 * (r >> 3)];
-            if (AFFINE) {
-              const uint32_t xe_xf = __builtin_amdgcn_perm(bits(subs(tle, ff)), bits(subs(tup, e)), 0x0b0a0908u);
-              acc[2 * (r >> 3) + 1] = (xe_xf & bit) | acc[2 * (r >> 3) + 1];
+          for (int r = 0; r < R; ++r) {
+            const uint32_t gl = bits(hl[r]), gup = bits(hup);
+            const uint32_t d = bits(hd) + __builtin_amdgcn_perm(sig[1][r], sig[0][r], sel);
+            const uint32_t e = AFFINE ? bits(mxu(eup, hup)) : gup;
+            const uint32_t ff = AFFINE ? bits(mxu(f[r], hl[r])) : gl;
+            const uint32_t hv = bits(mx3_15(from_bits(d), from_bits(e), from_bits(ff)));
+            if (TB) {
+              // bit 15 of a half of (x + 0x7fff) - y says x > y
+              const uint32_t bit = 0x01010101u << (r & 7), w = hv + k7;
+              acc[2 * (r >> 3)] |= __builtin_amdgcn_perm(w - e, w - d, 0x0b0a0908u) & bit;
+              if (AFFINE) {
+                const uint32_t xe = (gup ^ k7) + e, xf = (gl ^ k7) + ff;
+                acc[2 * (r >> 3) + 1] |= __builtin_amdgcn_perm(xf, xe, 0x0b0a0908u) & bit;
+              }
             }
-          } else if (TB) {
-            const s2 bd = mn(subs(hv, d), one);
-            const s2 be = mn(subs(hv, e), one);
-            s2 hs = mad_u(bd, be, bd);
-            if (MODE == ALN_LOCAL) hs = mx(hs, mad_u(subs(one, mn(hv, one)), sp(3), zero));
-            s2 nib = hs;
-            if (AFFINE) {
-              nib = mad_u1(mn(subs(e, tup), one), sp(4), nib);
-              nib = mad_u1(mn(subs(ff, tle), one), sp(8), nib);
+            hd = hl[r];
+            hl[r] = from_bits(AFFINE ? hv - gow : hv);
+            if (AFFINE) f[r] = from_bits(ff);
+            hup = hl[r];
+            eup = from_bits(e);
+          }
+        } else {
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            const s2 sg = from_bits(__builtin_amdgcn_perm(wb[r / 2], wa[r / 2], (r & 1) ? 0x07060302u : 0x05040100u));
+            const s2 hlo = hl[r];
+            const s2 d = adds(hd, sg);
+            const s2 tup = adds(hup, kBias ? go2 : goe2);
+            const s2 e = AFFINE ? mx(kBias ? eup : adds(eup, ge2), tup) : (kBias ? hup : adds(hup, ge2));
+            const s2 tle = adds(hlo, goe2);
+            const s2 ff = AFFINE ? mx(adds(f[r], ge2), tle) : adds(hlo, ge2);
+            s2 hv = mx(mx(d, e), ff);
+            if (MODE == ALN_LOCAL) hv = mx(hv, zero);
+            if (kFlagCodes) {
+              // words 2g and 2g + 1 of the column hold row group g; byte order (pair A, pair B) per flag
+              const uint32_t bit = 0x01010101u << (r & 7);
+              const uint32_t nd_ne = __builtin_amdgcn_perm(bits(subs(e, hv)), bits(subs(d, hv)), 0x0b0a0908u);
+              acc[2 * (r >> 3)] = (nd_ne & bit) | acc[2 * (r >> 3)];
+              if (AFFINE) {
+                const uint32_t xe_xf = __builtin_amdgcn_perm(bits(subs(tle, ff)), bits(subs(tup, e)), 0x0b0a0908u);
+                acc[2 * (r >> 3) + 1] = (xe_xf & bit) | acc[2 * (r >> 3) + 1];
+              }
+            } else if (TB) {
+              const s2 bd = mn(subs(hv, d), one);
+              const s2 be = mn(subs(hv, e), one);
+              s2 hs = mad_u(bd, be, bd);
+              if (MODE == ALN_LOCAL) hs = mx(hs, mad_u(subs(one, mn(hv, one)), sp(3), zero));
+              s2 nib = hs;
+              if (AFFINE) {
+                nib = mad_u1(mn(subs(e, tup), one), sp(4), nib);
+                nib = mad_u1(mn(subs(ff, tle), one), sp(8), nib);
+              }
+              acc[r / 4] |= bits(nib) << (4 * (r & 3));
             }
-            acc[r / 4] |= bits(nib) << (4 * (r & 3));
+            if (MODE == ALN_LOCAL) {
+              const s2 gt = mn(mx(subs(hv, bv[r]), zero), one);
+              bjr[r] = mad_u(gt, subs(jj, bjr[r]), bjr[r]);
+              bv[r] = mx(bv[r], hv);
+            }
+            f[r] = ff;
+            hl[r] = hv;
+            hd = hlo;
+            hup = hv;
+            eup = e;
           }
-          if (MODE == ALN_LOCAL) {
-            const s2 gt = mn(mx(subs(hv, bv[r]), zero), one);
-            bjr[r] = mad_u(gt, subs(jj, bjr[r]), bjr[r]);
-            bv[r] = mx(bv[r], hv);
-          }
-          f[r] = ff;
-          hl[r] = hv;
-          hd = hlo;
-          hup = hv;
-          eup = e;
         }
         if (MODE != ALN_LOCAL && (j == mm[0] || j == mm[1])) {
           const uint32_t msk = (j == mm[0] ? 0x0000ffffu : 0u) | (j == mm[1] ? 0xffff0000u : 0u);
@@ -375,7 +483,8 @@ __global__ __launch_bounds__(kI16Block) void batch_i16_kernel(
 #pragma unroll
           for (int r = 0; r < R; ++r) hw[r] = bits(hl[r]);
           const s2 hn = from_bits(tree_pick<R>(hw, rnb));
-          const int va = lo16(hn) + (kBias ? nn[0] * P.ge : 0), vb = hi16(hn) + (kBias ? nn[1] * P.ge : 0);
+          const int off = WORD ? j * P.ge - kept0 - P.go : 0;
+          const int va = lo16(hn) + off + (kBias ? nn[0] * P.ge : 0), vb = hi16(hn) + off + (kBias ? nn[1] * P.ge : 0);
           if (lastA && j <= mm[0] && va > brow[0]) {
             brow[0] = va;
             browj[0] = j;
@@ -385,7 +494,7 @@ __global__ __launch_bounds__(kI16Block) void batch_i16_kernel(
             browj[1] = j;
           }
         }
-        if (k + 1 < strips) rowbuf[(size_t)j * 64 + lane] = make_uint2(bits(hup), bits(eup));
+        if (TB || k + 1 < strips) rowbuf[(size_t)j * 64 + lane] = make_uint2(bits(hup), bits(eup));
         if (kFlagCodes) {
           uint2* __restrict__ d2 = reinterpret_cast<uint2*>(dirs);
 #pragma unroll
@@ -404,14 +513,14 @@ __global__ __launch_bounds__(kI16Block) void batch_i16_kernel(
       uint2 top[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) fetch(1 + u, ca[u], cb[u], top[u]);
-      for (int j0 = 1; j0 <= mmax; j0 += 4) {
+      int j0 = 1;
+      for (; j0 + 3 <= mmax; j0 += 4) {
         int nca[4], ncb[4];
         uint2 ntop[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) fetch(j0 + 4 + u, nca[u], ncb[u], ntop[u]);
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-          if (j0 + u <= mmax) column(j0 + u, ca[u], cb[u], top[u]);
+        for (int u = 0; u < 4; ++u) column(j0 + u, ca[u], cb[u], top[u]);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           ca[u] = nca[u];
@@ -419,6 +528,10 @@ __global__ __launch_bounds__(kI16Block) void batch_i16_kernel(
           top[u] = ntop[u];
         }
       }
+      for (int u = 0; j0 <= mmax; ++j0, ++u)
+        column(j0, u == 0 ? ca[0] : u == 1 ? ca[1] : ca[2], u == 0 ? cb[0] : u == 1 ? cb[1] : cb[2],
+               make_uint2(u == 0 ? top[0].x : u == 1 ? top[1].x : top[2].x,
+                          u == 0 ? top[0].y : u == 1 ? top[1].y : top[2].y));
       // merge this strip's rows in row order
 #pragma unroll
       for (int r = 0; r < R; ++r) {
@@ -432,7 +545,8 @@ __global__ __launch_bounds__(kI16Block) void batch_i16_kernel(
               bj[h] = h ? hi16(bjr[r]) : lo16(bjr[r]);
             }
           } else {
-            const int v = (h ? hi16(cap[r]) : lo16(cap[r])) + (kBias ? i * P.ge : 0);
+            const int v = (h ? hi16(cap[r]) : lo16(cap[r])) + (kBias ? i * P.ge : 0) +
+                          (WORD ? mm[h] * P.ge - kept0 - P.go : 0);
             if (MODE == ALN_SEMIGLOBAL && i < nn[h] && v > best[h]) {
               best[h] = v;
               bi[h] = i;
@@ -515,26 +629,45 @@ __global__ __launch_bounds__(kI16Block) void batch_i16_kernel(
   }
 }
 
-template <int MODE, bool AFFINE, bool TB, int R>
+template <int MODE, bool AFFINE, bool TB, int R, bool WORD>
 void launch_i16_t(const KParams& kp, const BatchPlan16& pl, const I16Args& a, hipStream_t stream) {
   const int blocks = (pl.n_waves + kI16WavesPerBlock - 1) / kI16WavesPerBlock;
-  const size_t lds = (size_t)kI16ProfBase + (size_t)kI16WavesPerBlock * i16_wave_prof_words(kp.alphabet, R) * 4;
+  const size_t lds =
+      WORD ? 32 : (size_t)kI16ProfBase + (size_t)kI16WavesPerBlock * i16_wave_prof_words(kp.alphabet, R) * 4;
   ProfScope prof(TB ? "batch_i16_traceback" : "batch_i16_score", stream);
-  hipLaunchKernelGGL((batch_i16_kernel<MODE, AFFINE, TB, R>), dim3(blocks), dim3(kI16Block), lds, stream, kp, a.q,
+  hipLaunchKernelGGL((batch_i16_kernel<MODE, AFFINE, TB, R, WORD>), dim3(blocks), dim3(kI16Block), lds, stream, kp, a.q,
                      a.q_off, a.s, a.s_off, pl.n_pairs, pl.max_n, pl.max_m, a.out, a.cigar, a.cigar_off,
                      static_cast<char*>(a.ws), pl.slab_bytes, pl.rowbuf_bytes, pl.rowbuf_bytes + pl.letters_bytes,
                      a.idx, a.idx_count, a.redo_idx,
                      a.redo_cnt, a.ticket);
 }
 
+// Whether every pair of the batch can run in 15-bit cells: its letters' scores are bytes, and no value leaves
+// 0 .. kWordTop.  The kept values lie above 0 (from 0 of the matrix's corner at -3 go, every cell is within two gap opens of a border, and its g one
+// below) and rise by at most max(sigma) - 2 ge a diagonal step and -ge a border cell, in whole strips.
+bool word_cells(const KParams& kp, const BatchPlan16& pl) {
+  if (kp.mode == ALN_LOCAL || kp.alphabet > 4 || pl.R != 16) return false;
+  if (kp.sigma_min - 2ll * kp.ge - kp.go < 0 || kp.sigma_max - 2ll * kp.ge - kp.go > 255) return false;
+  const int64_t n = (pl.max_n + 15) / 16 * 16, m = pl.max_m;
+  if (n > kWordTop || m > kWordTop) return false;  // (before the products below)
+  const int64_t step = std::max<int64_t>(kp.sigma_max - 2ll * kp.ge, 0);
+  return -4ll * kp.go - (n + m) * kp.ge + std::min(n, m) * step <= kWordTop;
+}
+
 template <int MODE, bool AFFINE, bool TB>
 void launch_i16_r(const KParams& kp, const BatchPlan16& pl, const I16Args& a, hipStream_t st) {
+  if constexpr (MODE != ALN_LOCAL) {
+    if (word_cells(kp, pl)) {
+      launch_i16_t<MODE, AFFINE, TB, 16, true>(kp, pl, a, st);
+      return;
+    }
+  }
   if (pl.R == 16)
-    launch_i16_t<MODE, AFFINE, TB, 16>(kp, pl, a, st);
+    launch_i16_t<MODE, AFFINE, TB, 16, false>(kp, pl, a, st);
   else if (pl.R == 8)
-    launch_i16_t<MODE, AFFINE, TB, 8>(kp, pl, a, st);
+    launch_i16_t<MODE, AFFINE, TB, 8, false>(kp, pl, a, st);
   else
-    launch_i16_t<MODE, AFFINE, TB, 4>(kp, pl, a, st);
+    launch_i16_t<MODE, AFFINE, TB, 4, false>(kp, pl, a, st);
 }
 
 template <int MODE>
