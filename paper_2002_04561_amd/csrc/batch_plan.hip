@@ -196,7 +196,9 @@ __global__ __launch_bounds__(kPlanThreads) void sort_scatter_kernel(int64_t n_pa
 
 // Exclusive prefix sums of the bands (item0) and row slots (row_off) of the big pairs, over kScanBlocks blocks that
 // each own one contiguous chunk: the first kernel sums each chunk (into V.hist, which the scatter has done with), the
-// second starts each chunk at the sum of those before it.  One block over all pairs took 331 us for 100,003 pairs.
+// second starts each chunk at the sum of those before it.  One block over all pairs took 331 us for 100,003 pairs.  Up to
+// kScanBlocks pairs are one block's, whose threads take a pair each as their chunk: no first kernel (a batch of 150 reads 76 us,
+// 73 so).
 // Should the totals exceed what the workspace was sized for (the caller understated total_q or
 // total_s), the wavefront pairs are dropped and their results flagged instead.
 constexpr int kScanBlocks = 256;
@@ -212,7 +214,7 @@ __device__ __forceinline__ BandSums pair_sums(const WfPair& p) {
   return s;
 }
 __device__ __forceinline__ void chunk_of_scan(int np, int* k0, int* k1) {
-  const int per = (np + kScanBlocks - 1) / kScanBlocks;
+  const int per = (np + (int)gridDim.x - 1) / (int)gridDim.x;
   *k0 = min((int)blockIdx.x * per, np);
   *k1 = min(*k0 + per, np);
 }
@@ -259,7 +261,11 @@ __global__ __launch_bounds__(256) void split_scan_kernel(SplitView V, WfWs W, in
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   static_assert(kScanBlocks == 256, "one chunk sum per thread");
   {
-    const BandSums a = reinterpret_cast<const BandSums*>(V.hist)[threadIdx.x];
+    BandSums a = {0, 0};
+    if (gridDim.x == kScanBlocks)
+      a = reinterpret_cast<const BandSums*>(V.hist)[threadIdx.x];
+    else if ((int)threadIdx.x < np)
+      a = pair_sums(W.pairs[threadIdx.x]);
     const int64_t it = wave_scan(a.items, lane), rw = wave_scan(a.rows, lane);
     if (lane == 63) part[wave] = {it, rw};
     __syncthreads();
@@ -459,8 +465,9 @@ void launch_split(const SplitPlan& sp, int64_t n_pairs, const int64_t* q_off, co
   hipLaunchKernelGGL(sort_scan_kernel, dim3(1), dim3(kScanThreads), 0, stream, V);
   hipLaunchKernelGGL(sort_scatter_kernel, dim3((unsigned)blocks), dim3(kPlanThreads), 0, stream, n_pairs, q_off,
                      s_off, sp.orient, sp.code_cap, V, W);
-  hipLaunchKernelGGL(split_sum_kernel, dim3(kScanBlocks), dim3(256), 0, stream, V, W);
-  hipLaunchKernelGGL(split_scan_kernel, dim3(kScanBlocks), dim3(256), 0, stream, V, W, sp.item_cap, sp.row_cap, out);
+  const bool one_block = n_pairs <= kScanBlocks;
+  if (!one_block) hipLaunchKernelGGL(split_sum_kernel, dim3(kScanBlocks), dim3(256), 0, stream, V, W);
+  hipLaunchKernelGGL(split_scan_kernel, dim3(one_block ? 1 : kScanBlocks), dim3(256), 0, stream, V, W, sp.item_cap, sp.row_cap, out);
 }
 
 }  // namespace mialign
