@@ -132,7 +132,7 @@ struct BatchLayout {
   BatchPlan16 bp16;
   SplitPlan sp;
   bool use16;
-  bool lanes_bounded;      // every pair left to the small-pair kernels is within lane_n x lane_m
+  bool lanes_bounded;      // every pair left to the small-pair kernels is within lane_n x lane_m, where the totals are true
   int64_t lane_n, lane_m;  // largest sides they are sized for
   size_t off_redo, off_redo_cnt, off_split, total;
 };
@@ -262,10 +262,8 @@ aln_status_t aln_align_batch_ex(const aln_scoring_t* scoring, int64_t n_pairs, c
     a.s = s;
     a.s_off = s_off;
     a.n_pairs = n_pairs;
-    a.max_n = max_n;
-    a.max_m = max_m;
-    a.lane_n = L.lane_n;
-    a.lane_m = L.lane_m;
+    a.max_n = L.lane_n;
+    a.max_m = L.lane_m;
     a.idx = list;
     a.idx_count = list_cnt;
     a.use16 = L.use16;
@@ -395,8 +393,8 @@ aln_status_t aln_traceback(const aln_scoring_t* scoring, int64_t n_pairs, const 
     a.s = s;
     a.s_off = s_off;
     a.n_pairs = n_pairs;
-    a.max_n = a.lane_n = max_n;
-    a.max_m = a.lane_m = max_m;
+    a.max_n = max_n;
+    a.max_m = max_m;
     a.fwd = fwd;
     a.out = out;
     a.cigar = cigar;

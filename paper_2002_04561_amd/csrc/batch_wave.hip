@@ -158,6 +158,7 @@ __global__ __launch_bounds__(64 * kPWavesPerBlock, kPWavesPerCU / 4) void batch_
     int n = 0, m = 0;
     uint32_t flags = 0;
     aln_result_t fw{};
+    // (the list may hold a longer pair than the slabs: one that found no room in an arena sized from understated totals)
     if (nn > A.max_n || mm > A.max_m || nn < 0 || mm < 0) {
       flags |= ALN_RES_TOO_LONG;
     } else {
@@ -243,7 +244,7 @@ template <int MODE, bool AFFINE, int PROF, bool FA>
 void launch_f(const KParams& kp, const WaveArgs& a, int waves, hipStream_t stream) {
   const int blocks = (waves + kPWavesPerBlock - 1) / kPWavesPerBlock;
   const size_t lds = (size_t)kPWavesPerBlock * pair_lds_bytes(kp.alphabet, PROF == kProfLane);
-  const size_t rb = row_bytes(a.lane_m), wb = rb + code_bytes(a.lane_n, a.lane_m);
+  const size_t rb = row_bytes(a.max_m), wb = rb + code_bytes(a.max_n, a.max_m);
   if (a.fwd)
     hipLaunchKernelGGL((batch_wave_kernel<MODE, AFFINE, PROF, FA, true>), dim3(blocks), dim3(64 * kPWavesPerBlock), lds,
                        stream, kp, a, waves, wb, rb);
@@ -255,7 +256,7 @@ void launch_f(const KParams& kp, const WaveArgs& a, int waves, hipStream_t strea
 template <int MODE>
 void launch_m(const KParams& kp, const WaveArgs& a, int waves, hipStream_t stream) {
   const bool bytes = kp.sigma_max - 2 * kp.ge <= 127 && kp.sigma_min - 2 * kp.ge >= -127;
-  const bool fa = band_fits_fa(kp, a.lane_n, a.lane_m);
+  const bool fa = band_fits_fa(kp, a.max_n, a.max_m);
   auto go = [&](auto affine, auto lanes) {
     constexpr bool kAffine = decltype(affine)::value, kFa = decltype(lanes)::value;
     if (kAffine && !kFa)

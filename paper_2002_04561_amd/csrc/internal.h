@@ -184,8 +184,8 @@ struct WaveArgs {
   const int64_t* q_off;
   const uint8_t* s;
   const int64_t* s_off;
-  int64_t n_pairs, max_n, max_m;  // pairs beyond the bounds are flagged
-  int64_t lane_n, lane_m;         // the largest sides a listed pair may have
+  int64_t n_pairs;
+  int64_t max_n, max_m;           // the largest sides that a wave's slab holds: longer pairs are flagged, never relaxed
   const int* idx;                 // the pairs (null: all n_pairs in order), their number at *idx_count
   const int* idx_count;
   bool use16;                     // flag the pairs that the 16-bit kernel would leave to a 32-bit pass
