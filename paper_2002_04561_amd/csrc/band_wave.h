@@ -25,11 +25,11 @@ __device__ __forceinline__ int raise_local_floor(int32_t& bs, int32_t top_h) {
   return fl;
 }
 
-// Per lane, a where the lane's bit of mask is set, else b: one v_cndmask, never a branch.
+// Per lane, a where the lane's bit of mask is set, else b: one v_cndmask.  The select is the compiler's own, which keeps the wait
+// states that an SGPR written by a VALU instruction (a comparison, v_readlane) needs before a VALU instruction reads it;
+// inline asm does not get them.  The mask stays a mask: the compiler cannot tell which comparison it came from and branch on it.
 __device__ __forceinline__ int mask_select(unsigned long long mask, int a, int b) {
-  int r;
-  asm("v_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(r) : "v"(b), "v"(a), "s"(mask));
-  return r;
+  return __builtin_amdgcn_inverse_ballot_w64(mask) ? a : b;
 }
 
 // (score, i, j) order of optima: larger score, then smaller i, then smaller j.

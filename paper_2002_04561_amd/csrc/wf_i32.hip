@@ -49,15 +49,6 @@ __device__ __forceinline__ int dpp_shl1(int old, int src) {
   return __builtin_amdgcn_update_dpp(old, src, 0x130, 0xf, 0xf, false);  // wave_shl:1, lane 63 keeps old
 }
 
-// c ? a : b as one v_cndmask on the lane mask of c, so the compiler cannot turn the choice into a
-// branch around the computation of a
-__device__ __forceinline__ int lane_select(bool c, int a, int b) {
-  const unsigned long long mask = __builtin_amdgcn_ballot_w64(c);
-  int r;
-  asm("v_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(r) : "v"(b), "v"(a), "s"(mask));
-  return r;
-}
-
 // Packed 16-bit bands (local alignment, score only; register profiles for up to 4 letters, per-lane LDS
 // profiles of two 16-bit rows per half for up to 32).  A 32-bit lane
 // register holds two 16-bit cells: rows of the band's upper half (HB = 128 rows) in its low half and
@@ -673,7 +664,7 @@ __global__ __launch_bounds__(kWfBlock, CKPT ? 3 : 4) void wf_i32_group_kernel(co
                 k = half(hk[1][r]) == mv ? 1 : k;
                 k = half(hk[0][r]) == mv ? 0 : k;
                 const bool up = mv > half(bvr[r]);
-                bjA[h][r] = lane_select(up, t0 - lane + 1 - (h ? D : 0) + k, bjA[h][r]);
+                bjA[h][r] = mask_select(__builtin_amdgcn_ballot_w64(up), t0 - lane + 1 - (h ? D : 0) + k, bjA[h][r]);
                 bvA[h][r] = max(bvA[h][r], mv + (h ? B1 : B0));
               }
               bvr[r] = pmax(bvr[r], mk[r]);
