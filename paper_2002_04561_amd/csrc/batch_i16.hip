@@ -138,6 +138,12 @@ __global__ __launch_bounds__(kI16Block, 2) void batch_i16_kernel(
   // every term of row i shifted by the same constant.  Local pairs, whose floor H = 0 would become a
   // per-row constant, keep plain values.
   constexpr bool kBias = MODE != ALN_LOCAL;
+  // Four columns in a row, no access and no column behind a branch (see fetch).  Local pairs with codes keep their branches:
+  // with 4-bit codes and a best cell kept for every row, four columns that the scheduler may interleave need more registers than a
+  // wave's share (16 rows: 10 spilled) and wait longer on memory.  300,000 pairs of 260..300 letters with CIGARs, without
+  // branches and with them: 4 letters 21.1 and 20.5 ms, linear gaps 17.2 and 15.8; 5 letters 25.6 and 21.8, linear 22.7 and
+  // 17.3; 20 letters with linear gaps 36.3 and 19.9, but with affine ones 23.1 and 24.9.
+  constexpr bool kStraight = MODE != ALN_LOCAL || !TB || (AFFINE && R == 4);
   static_assert(!WORD || (MODE != ALN_LOCAL && R == 16), "15-bit cells");
   extern __shared__ char smem[];
   int32_t* tab = reinterpret_cast<int32_t*>(smem);
@@ -358,7 +364,7 @@ __global__ __launch_bounds__(kI16Block, 2) void batch_i16_kernel(
                  : make_uint2(bits(sp((MODE == ALN_GLOBAL) ? P.go + j * P.ge : 0)), bits(neg2));
         uint32_t l2 = 0u;
         uint2 above = make_uint2(0u, 0u);
-        if constexpr (TB) {
+        if constexpr (TB && kStraight) {
           const int jc = min(j, mmax);  // (columns past mmax are not relaxed)
           l2 = letters[(size_t)max(jc - 1, 0) * 64 + lane];
           above = rowbuf[(size_t)jc * 64 + lane];
@@ -494,7 +500,7 @@ __global__ __launch_bounds__(kI16Block, 2) void batch_i16_kernel(
             browj[1] = j;
           }
         }
-        if (TB || k + 1 < strips) rowbuf[(size_t)j * 64 + lane] = make_uint2(bits(hup), bits(eup));
+        if ((TB && kStraight) || k + 1 < strips) rowbuf[(size_t)j * 64 + lane] = make_uint2(bits(hup), bits(eup));
         if (kFlagCodes) {
           uint2* __restrict__ d2 = reinterpret_cast<uint2*>(dirs);
 #pragma unroll
@@ -514,13 +520,14 @@ __global__ __launch_bounds__(kI16Block, 2) void batch_i16_kernel(
 #pragma unroll
       for (int u = 0; u < 4; ++u) fetch(1 + u, ca[u], cb[u], top[u]);
       int j0 = 1;
-      for (; j0 + 3 <= mmax; j0 += 4) {
+      for (; kStraight ? j0 + 3 <= mmax : j0 <= mmax; j0 += 4) {
         int nca[4], ncb[4];
         uint2 ntop[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) fetch(j0 + 4 + u, nca[u], ncb[u], ntop[u]);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) column(j0 + u, ca[u], cb[u], top[u]);
+        for (int u = 0; u < 4; ++u)
+          if (kStraight || j0 + u <= mmax) column(j0 + u, ca[u], cb[u], top[u]);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           ca[u] = nca[u];
