@@ -126,8 +126,8 @@ aln_status_t aln_batch_workspace_size(const aln_scoring_t* scoring, int64_t n_pa
  * In traceback calls the rule is fixed: pairs with n*m >= 2^18, or longer than 1024 on either side,
  * run on the band wavefront and store their 4-bit predecessor codes in an arena of the workspace (about
  * n*m/2 bytes each); the one-pair-per-lane kernels then hold code slabs for pairs up to 1024 x 1024
- * only.  Where the batch is too short to fill those kernels (a rule on its pair count and largest
- * sides), the pairs they would take run one per wave, in 32-bit lanes.  The arena is sized by a bound
+ * only.  Where the batch is too short to fill those kernels (a rule on its pair count and
+ * lengths), the pairs they would take run one per wave, in 32-bit lanes.  The arena is sized by a bound
  * from max_n, max_m, total_q and total_s; where that bound exceeds the arena budget
  * (aln_set_batch_code_arena, 16 GiB by default) the arena is the budget, pairs take room in the order
  * they reach it, those that find none run one pair per lane, and the lanes' slabs are sized for

@@ -241,10 +241,12 @@ aln_status_t aln_align_batch_ex(const aln_scoring_t* scoring, int64_t n_pairs, c
   int* redo_idx = reinterpret_cast<int*>(base + L.off_redo);
   int* redo_cnt = reinterpret_cast<int*>(base + L.off_redo_cnt);
 
+  // A traceback batch too short to fill the one-pair-per-lane kernels runs one pair per wave (lengths permitting, see wave_pair_route).
+  const PairRoute route = tb && L.lanes_bounded ? wave_pair_route(n_pairs, L.lane_n, L.lane_m, L.off_redo, L.use16) : PairRoute{};
   // The inter-sequence kernels see a shape-sorted list of the small pairs; the large ones go to the
   // wavefront engine (in a traceback call, those whose codes found room in its arena).
   char* split_ws = base + L.off_split;
-  launch_split(L.sp, n_pairs, q_off, s_off, max_n, max_m, out, split_ws, stream);
+  launch_split(L.sp, n_pairs, q_off, s_off, max_n, max_m, route, out, split_ws, stream);
   if (!tb || L.sp.code_cap > 0) {
     WfWs W = wf_view(split_ws + L.sp.wf_base, L.sp.wf);
     st = launch_wf_i32(kp, W, q, s, out, L.sp.wf_waves, L.sp.grouped, tb, !tb && L.sp.wf_p16,
@@ -253,9 +255,11 @@ aln_status_t aln_align_batch_ex(const aln_scoring_t* scoring, int64_t n_pairs, c
   }
   const int* list = reinterpret_cast<const int*>(split_ws + L.sp.off_small_idx);
   const int* list_cnt = reinterpret_cast<const int*>(split_ws + L.sp.off_small_cnt);
-  // a traceback batch too short to fill the one-pair-per-lane kernels runs one pair per wave
-  const int waves = tb && L.lanes_bounded ? wave_pair_waves(n_pairs, L.lane_n, L.lane_m, L.off_redo, L.use16) : 0;
-  if (waves > 0) {
+  // the redo counter and the group tickets of the 16- and 32-bit launches start at zero
+  int* ticket16 = redo_cnt + 16;
+  int* ticket32 = redo_cnt + 32;
+  constexpr int kCounters = 48;
+  if (route.waves > 0) {
     WaveArgs a{};
     a.q = q;
     a.q_off = q_off;
@@ -265,18 +269,20 @@ aln_status_t aln_align_batch_ex(const aln_scoring_t* scoring, int64_t n_pairs, c
     a.max_n = L.lane_n;
     a.max_m = L.lane_m;
     a.idx = list;
-    a.idx_count = list_cnt;
+    a.idx_count = list_cnt + 2;
     a.use16 = L.use16;
     a.out = out;
     a.cigar = cigar;
     a.cigar_off = cigar_off;
     a.ws = workspace;
-    return launch_batch_wave(kp, a, waves, stream);
+    if (!route.measure) return launch_batch_wave(kp, a, route.waves, stream);
+    a.zero = redo_cnt;
+    a.n_zero = kCounters;
+    st = launch_batch_wave(kp, a, route.waves, stream);
+    if (st != ALN_OK) return st;
+  } else {
+    hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(64), 0, stream, redo_cnt, kCounters, 0);
   }
-  // the redo counter and the group tickets of the 16- and 32-bit launches start at zero
-  int* ticket16 = redo_cnt + 16;
-  int* ticket32 = redo_cnt + 32;
-  hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(64), 0, stream, redo_cnt, 48, 0);
   if (!L.use16)
     return launch_batch_i32(kp, L.bp, q, q_off, s, s_off, tb, out, cigar, cigar_off, workspace, list, list_cnt, 0u,
                             ticket32, stream);
@@ -385,8 +391,12 @@ aln_status_t aln_traceback(const aln_scoring_t* scoring, int64_t n_pairs, const 
   st = tb_layout(kp, n_pairs, max_n, max_m, &bp, &off_ticket, &total);
   if (st != ALN_OK) return st;
   if (!workspace || workspace_bytes < total) return ALN_E_WORKSPACE;
-  const int waves = wave_pair_waves(n_pairs, max_n, max_m, off_ticket, false);
-  if (waves > 0) {
+  // the measures of calls that take them lie at the end of the slabs, which the kernel of one wave per pair then leaves free
+  const size_t work_bytes = kWorkSlots * sizeof(PairWork);
+  const PairRoute route = wave_pair_route(n_pairs, max_n, max_m, off_ticket - std::min(off_ticket, work_bytes), false);
+  int* ticket = reinterpret_cast<int*>(static_cast<char*>(workspace) + off_ticket);
+  int* lane_count = nullptr;
+  if (route.waves > 0) {
     WaveArgs a{};
     a.q = q;
     a.q_off = q_off;
@@ -400,11 +410,22 @@ aln_status_t aln_traceback(const aln_scoring_t* scoring, int64_t n_pairs, const 
     a.cigar = cigar;
     a.cigar_off = cigar_off;
     a.ws = workspace;
-    return launch_batch_wave(kp, a, waves, stream);
+    if (!route.measure) return launch_batch_wave(kp, a, route.waves, stream);
+    PairWork* work = reinterpret_cast<PairWork*>(static_cast<char*>(workspace) + off_ticket - work_bytes);
+    launch_pair_work(a, work, stream);
+    lane_count = ticket + 1;
+    a.work = work;
+    a.step_ns = route.step_ns;
+    a.cell_ns = route.cell_ns;
+    a.lane_count = lane_count;
+    a.zero = ticket;
+    a.n_zero = 1;
+    st = launch_batch_wave(kp, a, route.waves, stream);
+    if (st != ALN_OK) return st;
+  } else {
+    hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(64), 0, stream, ticket, 1, 0);
   }
-  int* ticket = reinterpret_cast<int*>(static_cast<char*>(workspace) + off_ticket);
-  hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(64), 0, stream, ticket, 1, 0);
-  return launch_batch_i32(kp, bp, q, q_off, s, s_off, true, out, cigar, cigar_off, workspace, nullptr, nullptr, 0u,
+  return launch_batch_i32(kp, bp, q, q_off, s, s_off, true, out, cigar, cigar_off, workspace, nullptr, lane_count, 0u,
                           ticket, stream, fwd);
 }
 

@@ -145,6 +145,7 @@ __global__ __launch_bounds__(kI16Block, 2) void batch_i16_kernel(
   // 17.3; 20 letters with linear gaps 36.3 and 19.9, but with affine ones 23.1 and 24.9.
   constexpr bool kStraight = MODE != ALN_LOCAL || !TB || (AFFINE && R == 4);
   static_assert(!WORD || (MODE != ALN_LOCAL && R == 16), "15-bit cells");
+  if (idx_count && *idx_count == 0) return;  // (before the table is filled and the ticket taken)
   extern __shared__ char smem[];
   int32_t* tab = reinterpret_cast<int32_t*>(smem);
   // WORD: the byte scores of each query letter (4: none, all 0), one word each

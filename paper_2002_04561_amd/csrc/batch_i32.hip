@@ -45,6 +45,8 @@ __global__ __launch_bounds__(kBlock) void batch_i32_kernel(
     int* __restrict__ ticket, const aln_result_t* __restrict__ fwd) {
   constexpr bool TB = TBK != 0;
   constexpr bool FIXED = TBK == 2;
+  // (before the table is filled and the ticket taken: a list is often empty, and one counter serves an atomic every 38 ns)
+  if (idx_count && *idx_count == 0) return;
   __shared__ int32_t tab[kTab * kTab];
   for (int k = threadIdx.x; k < kTab * kTab; k += blockDim.x) {
     const int a = k / kTab, b = k % kTab;
@@ -65,8 +67,8 @@ __global__ __launch_bounds__(kBlock) void batch_i32_kernel(
   // that every strip reads one coalesced row per column instead of a byte of 64 different subjects
   uint8_t* __restrict__ letters = reinterpret_cast<uint8_t*>(slab + letters_off);
   uint32_t* __restrict__ dirs = reinterpret_cast<uint32_t*>(slab + dirs_off);
-  // pairs come in input order, or from an index list whose length is a device value
-  const int64_t count = idx ? (int64_t)*idx_count : n_pairs;
+  // pairs come in input order, or from an index list; their number may be a device value
+  const int64_t count = idx_count ? (int64_t)*idx_count : n_pairs;
   const int64_t groups = (count + 63) / 64;
   const int32_t go = P.go, ge = P.ge, goe = P.goe;
 

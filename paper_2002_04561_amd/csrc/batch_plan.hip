@@ -22,7 +22,8 @@ static_assert(kKeys % kScanThreads == 0, "keys per scan thread");
 
 struct SplitView {
   int* small_idx;  // sorted inter-sequence list
-  int* counters;   // [0] small pairs, [1] big pairs
+  int* counters;   // small pairs: [0] those for the one-pair-per-lane kernels, [2] for the one-wave-per-pair one; [1] big pairs
+  PairWork* work;  // a call that measures them: the small pairs' work
   int* keys;       // per pair: sort key
   int* hist;       // [kKeys] counts, then cursors
   int64_t* code_off;                 // traceback calls: per pair, offset of its codes in the code arena
@@ -59,7 +60,8 @@ __device__ __forceinline__ bool orient_flip(int64_t n, int64_t m, int orient) {
 
 __global__ void split_reset_kernel(SplitView V) {
   for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < kKeys; k += gridDim.x * blockDim.x) V.hist[k] = 0;
-  if (blockIdx.x == 0 && threadIdx.x < 2) V.counters[threadIdx.x] = 0;
+  if (blockIdx.x == 0 && threadIdx.x < 3) V.counters[threadIdx.x] = 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) V.work->steps = V.work->cells = 0;
   if (blockIdx.x == 0 && threadIdx.x == 0) *V.code_used = 0;
 }
 
@@ -79,11 +81,16 @@ __global__ __launch_bounds__(kPlanThreads) void split_classify_kernel(int64_t n_
                                                                       const int64_t* __restrict__ s_off,
                                                                       int64_t max_n, int64_t max_m,
                                                                       int64_t big_cells, int64_t lane_dim, int orient,
-                                                                      bool tb, int64_t code_cap, SplitView V) {
+                                                                      bool tb, int64_t code_cap, bool measure, SplitView V) {
   __shared__ int h[kKeys];
   __shared__ int n_big;
+  __shared__ PairWork s_work;
+  unsigned long long steps = 0, cells = 0;
   for (int k = threadIdx.x; k < kKeys; k += blockDim.x) h[k] = 0;
-  if (threadIdx.x == 0) n_big = 0;
+  if (threadIdx.x == 0) {
+    n_big = 0;
+    s_work.steps = s_work.cells = 0;
+  }
   __syncthreads();
   int64_t p0, p1;
   chunk_of_block(n_pairs, &p0, &p1);
@@ -114,18 +121,33 @@ __global__ __launch_bounds__(kPlanThreads) void split_classify_kernel(int64_t n_
       atomicAdd(&n_big, 1);
     } else {
       key = log_bin(n) * kShapeBins + log_bin(m);
+      if (measure && fits) {
+        steps += (unsigned long long)wave_pair_steps(n, m);
+        cells = max(cells, (unsigned long long)lane_pair_cells(n, m));
+      }
     }
     V.keys[p] = key;
     atomicAdd(&h[key], 1);
+  }
+  if (measure) {
+    const PairWork w = wave_work({steps, cells});
+    if ((threadIdx.x & 63) == 0) {
+      atomicAdd(&s_work.steps, w.steps);
+      atomicMax(&s_work.cells, w.cells);
+    }
   }
   __syncthreads();
   for (int k = threadIdx.x; k < kKeys; k += blockDim.x)
     if (h[k]) atomicAdd(&V.hist[k], h[k]);
   if (threadIdx.x == 0 && n_big) atomicAdd(&V.counters[1], n_big);
+  if (threadIdx.x == 0 && measure) {
+    atomicAdd(&V.work->steps, s_work.steps);
+    atomicMax(&V.work->cells, s_work.cells);
+  }
 }
 
-// One block: turns the key histogram into cursors, largest keys first, and counts the small list.
-__global__ __launch_bounds__(kScanThreads) void sort_scan_kernel(SplitView V) {
+// One block: turns the key histogram into cursors, largest keys first, counts the small list and says which kernel takes it.
+__global__ __launch_bounds__(kScanThreads) void sort_scan_kernel(SplitView V, PairRoute route) {
   __shared__ int part[kScanThreads];
   constexpr int per = kKeys / kScanThreads;
   int local[per];
@@ -148,7 +170,12 @@ __global__ __launch_bounds__(kScanThreads) void sort_scan_kernel(SplitView V) {
     V.hist[kKeys - 1 - (threadIdx.x * per + k)] = run;
     run += local[k];
   }
-  if (threadIdx.x == kScanThreads - 1) V.counters[0] = part[kScanThreads - 1] - V.counters[1];
+  if (threadIdx.x == kScanThreads - 1) {
+    const int small = part[kScanThreads - 1] - V.counters[1];
+    const bool waves = route.waves > 0 && (!route.measure || (double)V.work->steps * route.step_ns <= (double)V.work->cells * route.cell_ns);
+    V.counters[0] = waves ? 0 : small;
+    V.counters[2] = waves ? small : 0;
+  }
 }
 
 // Places every pair at its sorted position: big pairs (positions 0 .. n_big-1) become entries of
@@ -445,11 +472,12 @@ aln_status_t plan_split(int64_t n_pairs, int64_t total_q, int64_t total_s, bool 
 }
 
 void launch_split(const SplitPlan& sp, int64_t n_pairs, const int64_t* q_off, const int64_t* s_off, int64_t max_n,
-                  int64_t max_m, aln_result_t* out, void* ws, hipStream_t stream) {
+                  int64_t max_m, const PairRoute& route, aln_result_t* out, void* ws, hipStream_t stream) {
   char* base = static_cast<char*>(ws);
   SplitView V;
   V.small_idx = reinterpret_cast<int*>(base + sp.off_small_idx);
   V.counters = reinterpret_cast<int*>(base + sp.off_small_cnt);
+  V.work = reinterpret_cast<PairWork*>(V.counters + 4);
   V.keys = reinterpret_cast<int*>(base + sp.off_keys);
   V.hist = reinterpret_cast<int*>(base + sp.off_hist);
   V.code_off = reinterpret_cast<int64_t*>(base + sp.off_code_off);
@@ -461,8 +489,8 @@ void launch_split(const SplitPlan& sp, int64_t n_pairs, const int64_t* q_off, co
   int64_t blocks = (n_pairs + 4095) / 4096;
   blocks = blocks < 1 ? 1 : (blocks > 512 ? 512 : blocks);
   hipLaunchKernelGGL(split_classify_kernel, dim3((unsigned)blocks), dim3(kPlanThreads), 0, stream, n_pairs, q_off,
-                     s_off, max_n, max_m, sp.big_cells, sp.lane_dim, sp.orient, sp.tb, sp.code_cap, V);
-  hipLaunchKernelGGL(sort_scan_kernel, dim3(1), dim3(kScanThreads), 0, stream, V);
+                     s_off, max_n, max_m, sp.big_cells, sp.lane_dim, sp.orient, sp.tb, sp.code_cap, route.measure, V);
+  hipLaunchKernelGGL(sort_scan_kernel, dim3(1), dim3(kScanThreads), 0, stream, V, route);
   hipLaunchKernelGGL(sort_scatter_kernel, dim3((unsigned)blocks), dim3(kPlanThreads), 0, stream, n_pairs, q_off,
                      s_off, sp.orient, sp.code_cap, V, W);
   const bool one_block = n_pairs <= kScanBlocks;

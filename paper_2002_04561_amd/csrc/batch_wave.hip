@@ -150,7 +150,15 @@ __global__ __launch_bounds__(64 * kPWavesPerBlock, kPWavesPerCU / 4) void batch_
   char* slab = static_cast<char*>(A.ws) + wave * wave_bytes;
   int2* row = reinterpret_cast<int2*>(slab);
   uint16_t* codes = reinterpret_cast<uint16_t*>(slab + row_bytes);
-  const int64_t count = A.idx ? (int64_t)*A.idx_count : A.n_pairs;
+  int64_t count = A.idx ? (int64_t)*A.idx_count : A.n_pairs;
+  if (FIXED && A.work) {
+    static_assert(kWorkSlots == 64, "a slot per lane");
+    const PairWork w = wave_work(A.work[lane]);
+    const bool waves = (double)w.steps * A.step_ns <= (double)w.cells * A.cell_ns;
+    if (wave == 0 && lane == 0) *A.lane_count = waves ? 0 : (int)A.n_pairs;
+    if (!waves) count = 0;
+  }
+  if (A.zero && wave == 0 && lane < A.n_zero) A.zero[lane] = 0;
   for (int64_t slot = wave; slot < count; slot += n_waves) {
     const int64_t p = A.idx ? (int64_t)A.idx[slot] : slot;
     const int64_t qb = A.q_off[p], sb = A.s_off[p];
@@ -278,24 +286,62 @@ void launch_m(const KParams& kp, const WaveArgs& a, int waves, hipStream_t strea
 
 }  // namespace
 
-// The rule compares both kernels' times, from what they measured (picoseconds, 256 compute units).  One pair per wave:
-// 128 ps for every step of every band and pair, 105 steps a band beyond its columns (65,536 reads of 100..250 letters
-// 2.9 ms, of 20..30 letters 1.6 ms).  One pair per lane: a wave's largest pair alone, 56 ns a cell of it in 16 bits and 87 ns
-// in 32, 1.65 times that once two waves share a SIMD (reads of 100..250 letters 4.5 and 7.0 ms for up to 65,536 pairs,
-// 8.1 ms for 262,144 in 16 bits); a batch that more than fills those waves stays with them.  So reads of 100..250
-// letters go one per wave up to about 80,000 pairs (2.9 against 4.7 ms at 65,536), of 20..30 up to 5,000.
-int wave_pair_waves(int64_t n_pairs, int64_t lane_n, int64_t lane_m, size_t ws_bytes, bool use16) {
+// The rule compares both kernels' times, from what they measured (256 compute units).  One pair per wave: 0.128 ns for
+// every step of every band and pair, 105 steps a band beyond its columns (65,536 reads of 100..250 letters 2.9 ms, of
+// 20..30 letters 1.6 ms).  One pair per lane: a wave's largest pair alone, 56 ns a cell of it in 16 bits and 87 ns in 32, 1.65
+// times that once two waves share a SIMD (reads of 100..250 letters 4.5 and 7.0 ms for up to 65,536 pairs, 8.1 ms for
+// 262,144 in 16 bits); a batch that more than fills those waves stays with them.  Taken by the call's bounds, reads of
+// 100..250 letters go one per wave up to 83,933 pairs (there 3.7 ms against 5.0 one per lane), of 8..30 up to 3111 (0.10 and 0.13).
+// Local pairs, 20 letters and linear gaps gain more there (1.2 to 2.9 times), so the line could lie higher for them.
+//
+// The bounds may be far above the pairs' lengths, and then one wave per pair loses by as much as the lanes' largest pair is
+// smaller than the bound (100,000 pairs of 8..30 letters under a bound of 1024: 1.47 ms one per wave, 0.20 per lane).  So above the
+// number of pairs where every wave has one to itself, where it costs at most what the lanes do whatever the lengths
+// (5000 pairs of 8..30 letters: 0.13 ms and 0.14), the pairs' own steps and largest cells are summed on the device and have to
+// agree.  Both kernels are then launched, and the one that is not taken finds no pairs (20,011 reads of 100..250 letters traced back
+// from their ends 720 us, 728 so; 60,000 with CIGARs 3.5 ms either way).
+PairRoute wave_pair_route(int64_t n_pairs, int64_t lane_n, int64_t lane_m, size_t ws_bytes, bool use16) {
+  PairRoute r{};
   const int cus = device_cu_count();
-  if (cus <= 0 || n_pairs < 1 || lane_n < 1 || lane_m < 1) return 0;
+  if (cus <= 0 || n_pairs < 1 || lane_n < 1 || lane_m < 1) return r;
   const int64_t lane_waves = (n_pairs + (use16 ? 127 : 63)) / (use16 ? 128 : 64);
-  if (use16 && lane_waves > (int64_t)8 * cus) return 0;
-  const double t_wave = (double)n_pairs * (double)((lane_n + kPBand - 1) / kPBand) * (double)(lane_m + 105) * 0.128 * 256 / cus;
-  const double t_lane = (double)((lane_n + 15) / 16 * 16) * (double)lane_m * (use16 ? 56.0 : 87.0) *
-                        (lane_waves > (int64_t)4 * cus ? 1.65 * std::max(1.0, (double)lane_waves / (8 * cus)) : 1.0);
-  if (t_wave > t_lane) return 0;
-  const int64_t want = std::min<int64_t>(n_pairs, (int64_t)cus * kPWavesPerCU);
+  if (use16 && lane_waves > (int64_t)8 * cus) return r;
+  r.step_ns = 0.128 * 256 / cus;
+  r.cell_ns = (use16 ? 56.0 : 87.0) *
+              (lane_waves > (int64_t)4 * cus ? 1.65 * std::max(1.0, (double)lane_waves / (8 * cus)) : 1.0);
+  if ((double)n_pairs * (double)wave_pair_steps(lane_n, lane_m) * r.step_ns > (double)lane_pair_cells(lane_n, lane_m) * r.cell_ns)
+    return r;
+  const int64_t all = (int64_t)cus * kPWavesPerCU;
+  r.measure = n_pairs > all;
   const int64_t fit = (int64_t)(ws_bytes / (row_bytes(lane_m) + code_bytes(lane_n, lane_m)));
-  return (int)std::min(want, fit);
+  r.waves = (int)std::min(std::min(n_pairs, all), fit);
+  return r;
+}
+
+// The work of one part of aln_traceback's pairs: the rectangles up to their end cells.
+__global__ __launch_bounds__(256) void pair_work_kernel(const WaveArgs A, PairWork* __restrict__ work) {
+  __shared__ PairWork s_work;
+  if (threadIdx.x == 0) s_work.steps = s_work.cells = 0;
+  __syncthreads();
+  unsigned long long steps = 0, cells = 0;
+  for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < A.n_pairs; p += (int64_t)gridDim.x * blockDim.x) {
+    // (an end cell outside the pair is flagged by the kernels, and within the bounds it does no harm here)
+    const int n = A.fwd[p].q_end, m = A.fwd[p].s_end;
+    if (n < 0 || m < 0 || n > A.max_n || m > A.max_m) continue;
+    steps += (unsigned long long)wave_pair_steps(n, m);
+    cells = max(cells, (unsigned long long)lane_pair_cells(n, m));
+  }
+  const PairWork w = wave_work({steps, cells});
+  if ((threadIdx.x & 63) == 0) {
+    atomicAdd(&s_work.steps, w.steps);
+    atomicMax(&s_work.cells, w.cells);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) work[blockIdx.x] = s_work;
+}
+
+void launch_pair_work(const WaveArgs& a, PairWork* work, hipStream_t stream) {
+  hipLaunchKernelGGL(pair_work_kernel, dim3(kWorkSlots), dim3(256), 0, stream, a, work);
 }
 
 aln_status_t launch_batch_wave(const KParams& kp, const WaveArgs& a, int waves, hipStream_t stream) {

@@ -179,6 +179,31 @@ __host__ __device__ __forceinline__ bool fits16(const KParams& P, int n, int m, 
 }
 
 // batch_wave.hip: one wave per pair
+// What a pair costs one wave, in steps (an empty pair still takes a wave's start and end), and one lane, in cells.
+__host__ __device__ __forceinline__ int64_t wave_pair_steps(int64_t n, int64_t m) {
+  return (n > kWfBand ? (n + kWfBand - 1) / kWfBand : 1) * (m + 105);
+}
+__host__ __device__ __forceinline__ int64_t lane_pair_cells(int64_t n, int64_t m) { return (n + 15) / 16 * 16 * m; }
+struct PairWork {
+  unsigned long long steps;  // of all pairs
+  unsigned long long cells;  // of the largest
+};
+// over the wave
+__device__ __forceinline__ PairWork wave_work(PairWork w) {
+  for (int o = 32; o >= 1; o >>= 1) {
+    w.steps += __shfl_xor(w.steps, o, 64);
+    const unsigned long long c = __shfl_xor(w.cells, o, 64);
+    w.cells = c > w.cells ? c : w.cells;
+  }
+  return w;
+}
+// How the small pairs of a traceback call run (see wave_pair_route).
+struct PairRoute {
+  int waves;       // waves of the one-wave-per-pair launch; 0: one pair per lane
+  bool measure;    // the pairs' own lengths decide on the device: both kernels are launched, and one finds no pairs
+  double step_ns;  // one wave per pair where steps * step_ns <= cells * cell_ns
+  double cell_ns;
+};
 struct WaveArgs {
   const uint8_t* q;
   const int64_t* q_off;
@@ -188,6 +213,14 @@ struct WaveArgs {
   int64_t max_n, max_m;           // the largest sides that a wave's slab holds: longer pairs are flagged, never relaxed
   const int* idx;                 // the pairs (null: all n_pairs in order), their number at *idx_count
   const int* idx_count;
+  // Calls that measure their pairs (PairRoute): aln_traceback's partial measures, by which the kernel runs all pairs or none and
+  // leaves the others' number at *lane_count (null: the planner has decided); and the counters of the kernels of one pair
+  // per lane that follow, which start at zero.
+  const PairWork* work;
+  double step_ns, cell_ns;
+  int* lane_count;
+  int* zero;
+  int n_zero;
   bool use16;                     // flag the pairs that the 16-bit kernel would leave to a 32-bit pass
   const aln_result_t* fwd;        // aln_traceback: forward results, traced back from their end cells
   aln_result_t* out;
@@ -195,9 +228,12 @@ struct WaveArgs {
   const int64_t* cigar_off;
   void* ws;
 };
-// Waves of a one-wave-per-pair launch over at most n_pairs pairs of at most lane_n x lane_m, within ws_bytes of
-// workspace; 0 where the one-pair-per-lane kernels (16- or 32-bit) are the better choice.
-int wave_pair_waves(int64_t n_pairs, int64_t lane_n, int64_t lane_m, size_t ws_bytes, bool use16);
+// The route of n_pairs pairs of at most lane_n x lane_m within ws_bytes of workspace; use16: the one-pair-per-lane kernel would be the
+// 16-bit one.
+PairRoute wave_pair_route(int64_t n_pairs, int64_t lane_n, int64_t lane_m, size_t ws_bytes, bool use16);
+// aln_traceback: the measures of kWorkSlots parts of the pairs.
+constexpr int kWorkSlots = 64;
+void launch_pair_work(const WaveArgs& a, PairWork* work, hipStream_t stream);
 aln_status_t launch_batch_wave(const KParams& kp, const WaveArgs& a, int waves, hipStream_t stream);
 
 // wf_i32.hip
@@ -277,7 +313,9 @@ BatchCfg resolve_cfg(const aln_batch_config_t* c);
 void route_rule(int64_t n_pairs, bool tb, const BatchCfg& cfg, int cus, int64_t* min_cells, int64_t* lane_dim);
 aln_status_t plan_split(int64_t n_pairs, int64_t total_q, int64_t total_s, bool tb, int64_t max_n, int64_t max_m,
                         const BatchCfg& cfg, SplitPlan* sp);
+// route: a traceback call's; the small pairs' number is left at off_small_cnt, [0] for the one-pair-per-lane kernels and [2] for the
+// one-wave-per-pair one.
 void launch_split(const SplitPlan& sp, int64_t n_pairs, const int64_t* q_off, const int64_t* s_off, int64_t max_n,
-                  int64_t max_m, aln_result_t* out, void* ws, hipStream_t stream);
+                  int64_t max_m, const PairRoute& route, aln_result_t* out, void* ws, hipStream_t stream);
 
 }  // namespace mialign
