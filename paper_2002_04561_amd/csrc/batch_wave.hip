@@ -55,7 +55,7 @@ __device__ __forceinline__ int4 relax_pair(const KParams& P, const int32_t* tab,
     band_start<MODE, PROF, FA, R>(P, sig2, q, n, false, irow0, lane, lp, prof, L, B, bad);
     uint16_t* __restrict__ codes = codes0 + (size_t)(b * 64 + lane) * (size_t)m;
     const bool last_band = b == nb - 1;
-    const int rn = n - 1 - irow0;
+    if (MODE == ALN_SEMIGLOBAL && last_band) last_row_start<R>(P, n - 1 - irow0, B);
     int c_next = 1 + lane <= m ? (int)s[lane] : -1;
     int c_idx = letter_index<PROF, R>(P, -1, false, bad);
     lett.clear_tail(lane);
@@ -100,7 +100,7 @@ __device__ __forceinline__ int4 relax_pair(const KParams& P, const int32_t* tab,
         if (irow0 < n) store_codes<R>(G, codes, j0, m, inside);  // row groups past n have no room
         if constexpr (!FIXED) {
           if constexpr (MODE == ALN_LOCAL) track_local<AFFINE, R>(P, L, G, floor0, j0, false, B);
-          if (MODE == ALN_SEMIGLOBAL && last_band) track_last_row<AFFINE, R>(P, L, G, floor0, m, rn, j0, B);
+          if (MODE == ALN_SEMIGLOBAL && last_band) track_last_row<AFFINE, R>(P, L, G, floor0, m, n - 1 - i0, j0, B);
         }
         if (lane == 63) {
           reinterpret_cast<int4*>(st_h)[g4] = make_int4(ph, G.oh[0], G.oh[1], G.oh[2]);

@@ -143,7 +143,7 @@ __global__ __launch_bounds__(kWfBlockAlone, 4) void wf_i32_kernel(const KParams 
     band_start<MODE, PROF, FA, R>(P, sig2, q, n, flip, irow0, lane, lp, prof, L, B, bad);
     uint16_t* __restrict__ codes = TB ? W.codes + pr.code_off + (size_t)(b * 64 + lane) * (size_t)m : nullptr;
     const bool last_band = (b == nb - 1);
-    const int rn = n - 1 - irow0;  // index of row n among this lane's rows
+    if (MODE == ALN_SEMIGLOBAL && last_band) last_row_start<R>(P, n - 1 - irow0, B);
     int2* __restrict__ prev = W.rows + pr.row_off + (int64_t)((b + 1) & 1) * ld;
     int2* __restrict__ cur = W.rows + pr.row_off + (int64_t)(b & 1) * ld;
     bool failed = false;
@@ -224,7 +224,7 @@ __global__ __launch_bounds__(kWfBlockAlone, 4) void wf_i32_kernel(const KParams 
           track_last_column<FA, R, MODE == ALN_GLOBAL>(P, G, j0, n, m, irow0, B);
         if (TB) store_codes<R>(G, codes, j0, m, inside);
         if constexpr (MODE == ALN_LOCAL) track_local<AFFINE, R>(P, L, G, floor0, j0, flip, B);
-        if (MODE == ALN_SEMIGLOBAL && last_band) track_last_row<AFFINE, R>(P, L, G, floor0, m, rn, j0, B);
+        if (MODE == ALN_SEMIGLOBAL && last_band) track_last_row<AFFINE, R>(P, L, G, floor0, m, n - 1 - i0, j0, B);
         if (lane == 63) {
           reinterpret_cast<int4*>(st_h)[g4] = make_int4(ph, G.oh[0], G.oh[1], G.oh[2]);
           reinterpret_cast<int4*>(st_e)[g4] = make_int4(pe, G.oe[0], G.oe[1], G.oe[2]);
@@ -768,7 +768,7 @@ __global__ __launch_bounds__(kWfBlock, CKPT ? 3 : 4) void wf_i32_group_kernel(co
     band_start<MODE, PROF, FA, R>(P, sig2, q, n, flip, irow0, lane, lp, prof, L, B, bad);
     uint16_t* __restrict__ codes = TB ? W.codes + pr.code_off + (size_t)(b * 64 + lane) * (size_t)m : nullptr;
     const bool last_band = (b == nb - 1);
-    const int rn = n - 1 - irow0;  // index of row n among this lane's rows
+    if (MODE == ALN_SEMIGLOBAL && last_band) last_row_start<R>(P, n - 1 - irow0, B);
     bool failed = false;
     int *rin_h = ring_h(cw), *rin_e = ring_e(cw);           // row of the band above (b > 0)
     int *rout_h = ring_h(cw + 1), *rout_e = ring_e(cw + 1);  // this band's bottom row, for the band below
@@ -863,7 +863,7 @@ __global__ __launch_bounds__(kWfBlock, CKPT ? 3 : 4) void wf_i32_group_kernel(co
           track_last_column<FA, R, MODE == ALN_GLOBAL>(P, G, j0, n, m, irow0, B);
         if (TB) store_codes<R>(G, codes, j0, m, inside);
         if constexpr (MODE == ALN_LOCAL) track_local<AFFINE, R>(P, L, G, floor0, j0, flip, B);
-        if (MODE == ALN_SEMIGLOBAL && last_band) track_last_row<AFFINE, R>(P, L, G, floor0, m, rn, j0, B);
+        if (MODE == ALN_SEMIGLOBAL && last_band) track_last_row<AFFINE, R>(P, L, G, floor0, m, n - 1 - i0, j0, B);
         if (has_out && lane == 63) {
           reinterpret_cast<int4*>(rout_h)[((t0 - 64) & (kRing - 1)) / 4] = make_int4(ph, G.oh[0], G.oh[1], G.oh[2]);
           reinterpret_cast<int4*>(rout_e)[((t0 - 64) & (kRing - 1)) / 4] = make_int4(pe, G.oe[0], G.oe[1], G.oe[2]);
