@@ -249,7 +249,7 @@ aln_status_t aln_align_batch_ex(const aln_scoring_t* scoring, int64_t n_pairs, c
   launch_split(L.sp, n_pairs, q_off, s_off, max_n, max_m, route, out, split_ws, stream);
   if (!tb || L.sp.code_cap > 0) {
     WfWs W = wf_view(split_ws + L.sp.wf_base, L.sp.wf);
-    st = launch_wf_i32(kp, W, q, s, out, L.sp.wf_waves, L.sp.grouped, tb, !tb && L.sp.wf_p16,
+    st = launch_wf_i32(kp, W, q, s, out, L.sp.wf_waves, L.sp.grouped, L.sp.crowded, tb, !tb && L.sp.wf_p16,
                        band_fits_fa(kp, max_n, max_m), cigar, 0, stream, tb ? cigar_off : nullptr);
     if (st != ALN_OK) return st;
   }

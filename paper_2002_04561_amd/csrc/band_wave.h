@@ -316,9 +316,20 @@ __device__ __forceinline__ void fill_table(const KParams& P, int32_t* tab, uint3
 
 // The first ng of a block's groups of 4 steps.  A group's inputs are read from LDS while the group before runs (its
 // letters one group earlier still where they lead to profile words), so that no group waits for LDS.
-template <int PROF, int R, int NG, typename Window, typename Rows, typename Run>
+// AHEAD false: when the group starts, which leaves the waiting to the other waves of the SIMD and takes fewer registers.
+template <int PROF, int R, int NG, bool AHEAD = true, typename Window, typename Rows, typename Run>
 __device__ __forceinline__ void run_block(const Window& lett, const uint32_t* lp, int lane, int ng, Rows load_rows,
                                           Run run) {
+  if constexpr (!AHEAD) {
+    for (int g4 = 0; g4 < ng; ++g4) {
+      BandIn<R> I;
+      lett.get(lane, g4, I.vc);
+      load_rows(g4, I);
+      load_words<PROF, R>(lp, I);
+      run(g4, I);
+    }
+    return;
+  }
   BandIn<R> A, C;
   lett.get(lane, 0, A.vc);
   load_rows(0, A);

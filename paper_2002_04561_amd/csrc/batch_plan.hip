@@ -458,6 +458,10 @@ aln_status_t plan_split(int64_t n_pairs, int64_t total_q, int64_t total_s, bool 
   // (bands handed out level by level) overtakes between 46 and 70 estimated bands per compute unit.
   const int64_t est_bands = (total_q + total_s) / (2 * kWfBand);
   sp->grouped = cfg.wf_group == 4 || (cfg.wf_group == 0 && est_bands < (int64_t)56 * (cus > 0 ? cus : 1));
+  // A batch of many short chains of bands spends its time waiting along them, so its workgroups should all be resident.
+  // Bands are estimated from the rows: the queries, or either side where pairs may be transposed.
+  const int64_t est_rows = (sp->orient ? std::max(total_q, total_s) : total_q) / kWfBand + n_pairs / 2;
+  sp->crowded = sp->grouped && cus > 0 && est_rows / kWfGroupBands > (int64_t)kWfResident * cus;
   if (sp->grouped && !cfg.waves_given && cus > 0) {
     // Workgroups take their groups in the order they start, wherever they sit, so a grid with more
     // workgroups than groups can stack several working ones on a compute unit while others idle.

@@ -239,6 +239,8 @@ aln_status_t launch_batch_wave(const KParams& kp, const WaveArgs& a, int waves, 
 // wf_i32.hip
 constexpr int kWfWavesPerCUDefault = 16;
 constexpr int kWfGroupBands = 4;  // bands (compute waves) of a workgroup of the grouped wavefront engine
+// Workgroups (4 bands and a courier) that a compute unit holds at 4 waves a SIMD.
+constexpr int kWfResident = 4 * 4 / (kWfGroupBands + 1);
 constexpr int kWfWavesPerCUMax = 32;
 int wf_waves(int per_cu);
 size_t wf_layout(int64_t max_pairs, int64_t max_items, int64_t row_words, int64_t code_words, WfOffsets* o);
@@ -249,8 +251,9 @@ WfWs wf_view(void* base, const WfOffsets& o);
 // cigar_off: batches, each pair's CIGAR room (cigar[cigar_off[k] .. cigar_off[k + 1]]); else one pair with
 // cigar_cap words at cigar
 // fa: band_fits_fa of the largest pair
+// crowded: SplitPlan::crowded
 aln_status_t launch_wf_i32(const KParams& kp, const WfWs& W, const uint8_t* q, const uint8_t* s, aln_result_t* out,
-                           int max_waves, bool grouped, bool tb, bool p16, bool fa, uint32_t* cigar,
+                           int max_waves, bool grouped, bool crowded, bool tb, bool p16, bool fa, uint32_t* cigar,
                            int64_t cigar_cap, hipStream_t stream, const int64_t* cigar_off = nullptr);
 // Whether every lane value of pairs up to n x m stays in the 2^23 consecutive integers that lanes held as floats
 // cover (band.h): values are at least 2 go - 127 and at most min(n, m) max(sigma, 0) + (n + m) |ge|, taken here over
@@ -285,6 +288,7 @@ struct SplitPlan {
   int orient;         // wavefront pair orientation: 1 longer sequence along the rows, 0 as given, 2 cheaper
   int64_t item_cap, row_cap;  // bands and row-slot entries the workspace holds
   bool grouped;               // the wavefront engine runs workgroups of 4 consecutive bands
+  bool crowded;               // ... and more of them than a compute unit holds at 4 waves a SIMD (kWfResident)
   bool wf_p16;                // grouped score-only local bands may use packed 16-bit cells
   bool tb;                    // a traceback call
   int64_t lane_dim;           // traceback calls: pairs longer than this on a side go to the wavefront

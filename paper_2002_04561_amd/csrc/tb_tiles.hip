@@ -392,7 +392,7 @@ aln_status_t launch_long_ls(const KParams& kp, const LongLsPlan& pl, const uint8
   launch_single_pair(W, (int)n, (int)m, stream);
   // the forward pass: score, end cell and the checkpoints (grouped bands)
   const bool fa = band_fits_fa(kp, n, m);
-  aln_status_t st = launch_wf_i32(kp, W, q, s, out, pl.n_waves, true, false, false, fa, nullptr, 0, stream);
+  aln_status_t st = launch_wf_i32(kp, W, q, s, out, pl.n_waves, true, false, false, false, fa, nullptr, 0, stream);
   if (st != ALN_OK) return st;
   TbView V;
   V.n = (int)n;

@@ -259,8 +259,13 @@ __global__ __launch_bounds__(kWfBlockAlone, 4) void wf_i32_kernel(const KParams 
 // CKPT: also store checkpoints for a linear-space traceback (one pair, groups aligned with its bands):
 // every group's bottom row stays in its own row slot instead of two rotating ones, and every
 // kTileCols-th column's H~ and F~ of all rows go to W.ckcols.
-template <int MODE, bool AFFINE, int PROF, bool TB, bool FA, int R, bool P16, bool CKPT>
-__global__ __launch_bounds__(kWfBlock, CKPT ? 3 : 4) void wf_i32_group_kernel(const KParams P, const uint8_t* __restrict__ Q,
+// WAVES: the waves a SIMD it is built for.  5 leave 96 registers, so a group's inputs are read when it starts and not a group
+// ahead: for launches of more workgroups than are resident at 4 (SplitPlan::crowded).  Short chains of bands wait
+// along the chain for most of their time, and then the number of chains in flight is what counts: 4096 pairs of 1024 x 64 letters,
+// global affine 0.50 and 0.43 ms, semi-global linear 0.55 and 0.44, 4096 of 512 x 1600 (local) 0.98 and 0.87.  With a workgroup or
+// two a compute unit 4 is better: 1024 pairs of 512 x 1600 0.32 and 0.40.
+template <int MODE, bool AFFINE, int PROF, bool TB, bool FA, int R, bool P16, bool CKPT, int WAVES>
+__global__ __launch_bounds__(kWfBlock, WAVES) void wf_i32_group_kernel(const KParams P, const uint8_t* __restrict__ Q,
                                                           const uint8_t* __restrict__ S, WfWs W) {
   static_assert(PROF != kProfLane || R == 4, "a lane profile word holds 4 rows");
   constexpr int BLK = kBlkGrouped;
@@ -869,7 +874,7 @@ __global__ __launch_bounds__(kWfBlock, CKPT ? 3 : 4) void wf_i32_group_kernel(co
           reinterpret_cast<int4*>(rout_e)[((t0 - 64) & (kRing - 1)) / 4] = make_int4(pe, G.oe[0], G.oe[1], G.oe[2]);
         }
       };
-      run_block<PROF, R, BLK / 4>(lett, lp, lane, min(BLK / 4, (steps - tb + 3) / 4), load_rows, run);
+      run_block<PROF, R, BLK / 4, WAVES < 5>(lett, lp, lane, min(BLK / 4, (steps - tb + 3) / 4), load_rows, run);
       // the block's ring reads are complete and its outputs written before either is announced
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       if (lane == 0) {
@@ -1197,66 +1202,73 @@ bool p16_exact(const KParams& kp) {
 
 template <int MODE, bool AFFINE, int PROF, bool TB, bool FA>
 void launch_wf_t(const KParams& kp, const uint8_t* q, const uint8_t* s, const WfWs& W, int n_waves, bool grouped,
-                 bool p16, hipStream_t stream) {
+                 bool crowded, bool p16, hipStream_t stream) {
   const int blocks = (n_waves + kWfWavesPerBlock - 1) / kWfWavesPerBlock;
   const size_t lds = PROF == kProfLane ? (size_t)kWfWavesPerBlock * (kp.alphabet + 1) * 64 * sizeof(uint32_t) : 0;
   constexpr bool kCanPack = MODE == ALN_LOCAL && (PROF == kProfReg || PROF == kProfLane) && !TB;
   if (kCanPack && grouped && p16 && p16_exact(kp)) {
     // packed bands keep two 16-bit rows of each half per letter and lane: twice the words
     ProfScope prof("wavefront_p16", stream);
-    hipLaunchKernelGGL((wf_i32_group_kernel<MODE, AFFINE, PROF, TB, false, kWfR, kCanPack, false>), dim3(blocks),
+    hipLaunchKernelGGL((wf_i32_group_kernel<MODE, AFFINE, PROF, TB, false, kWfR, kCanPack, false, 4>), dim3(blocks),
                        dim3(kWfBlock), 2 * lds, stream, kp, q, s, W);
     return;
   }
   if (!TB && W.ckcols) {
     ProfScope prof("wavefront_i32_checkpoints", stream);
-    hipLaunchKernelGGL((wf_i32_group_kernel<MODE, AFFINE, PROF, false, FA, kWfR, false, !TB>), dim3(blocks),
+    hipLaunchKernelGGL((wf_i32_group_kernel<MODE, AFFINE, PROF, false, FA, kWfR, false, !TB, TB ? 4 : 3>), dim3(blocks),
                        dim3(kWfBlock), lds, stream, kp, q, s, W);
     return;
   }
   ProfScope prof(TB ? "wavefront_i32_traceback" : "wavefront_i32", stream);
-  if (grouped)
-    hipLaunchKernelGGL((wf_i32_group_kernel<MODE, AFFINE, PROF, TB, FA, kWfR, false, false>), dim3(blocks),
+  if (grouped) {
+    if constexpr (!TB) {
+      if (crowded) {
+        hipLaunchKernelGGL((wf_i32_group_kernel<MODE, AFFINE, PROF, TB, FA, kWfR, false, false, 5>), dim3(blocks),
+                           dim3(kWfBlock), lds, stream, kp, q, s, W);
+        return;
+      }
+    }
+    hipLaunchKernelGGL((wf_i32_group_kernel<MODE, AFFINE, PROF, TB, FA, kWfR, false, false, 4>), dim3(blocks),
                        dim3(kWfBlock), lds, stream, kp, q, s, W);
-  else
+  } else
     hipLaunchKernelGGL((wf_i32_kernel<MODE, AFFINE, PROF, TB, FA, kWfR>), dim3(blocks), dim3(kWfBlockAlone), lds,
                        stream, kp, q, s, W);
 }
 
 template <int MODE, bool AFFINE, bool TB, bool FA>
-void launch_wf_p(const KParams& kp, const uint8_t* q, const uint8_t* s, const WfWs& W, int nw, bool grouped, bool p16,
+void launch_wf_p(const KParams& kp, const uint8_t* q, const uint8_t* s, const WfWs& W, int nw, bool grouped, bool crowded, bool p16,
                  hipStream_t st) {
   const bool bytes = kp.sigma_max - 2 * kp.ge <= 127 && kp.sigma_min - 2 * kp.ge >= -127;
   if (bytes && kp.alphabet <= 4)
-    launch_wf_t<MODE, AFFINE, kProfReg, TB, FA>(kp, q, s, W, nw, grouped, p16, st);
+    launch_wf_t<MODE, AFFINE, kProfReg, TB, FA>(kp, q, s, W, nw, grouped, crowded, p16, st);
   else if (bytes)
-    launch_wf_t<MODE, AFFINE, kProfLane, TB, FA>(kp, q, s, W, nw, grouped, p16, st);
+    launch_wf_t<MODE, AFFINE, kProfLane, TB, FA>(kp, q, s, W, nw, grouped, crowded, p16, st);
   else
-    launch_wf_t<MODE, AFFINE, kProfTable, TB, FA>(kp, q, s, W, nw, grouped, false, st);
+    launch_wf_t<MODE, AFFINE, kProfTable, TB, FA>(kp, q, s, W, nw, grouped, crowded, false, st);
 }
 
 // fa: float lanes (band.h).  Only affine gaps add a constant per cell; linear ones always use integer lanes.
 template <int MODE, bool TB>
-void launch_wf_m(const KParams& kp, const uint8_t* q, const uint8_t* s, const WfWs& W, int nw, bool grouped, bool p16,
+void launch_wf_m(const KParams& kp, const uint8_t* q, const uint8_t* s, const WfWs& W, int nw, bool grouped, bool crowded, bool p16,
                  bool fa, hipStream_t st) {
   if (kp.go == 0)
-    launch_wf_p<MODE, false, TB, false>(kp, q, s, W, nw, grouped, p16, st);
+    launch_wf_p<MODE, false, TB, false>(kp, q, s, W, nw, grouped, crowded, p16, st);
   else if (fa)
-    launch_wf_p<MODE, true, TB, true>(kp, q, s, W, nw, grouped, p16, st);
+    launch_wf_p<MODE, true, TB, true>(kp, q, s, W, nw, grouped, crowded, p16, st);
   else
-    launch_wf_p<MODE, true, TB, false>(kp, q, s, W, nw, grouped, p16, st);
+    launch_wf_p<MODE, true, TB, false>(kp, q, s, W, nw, grouped, crowded, p16, st);
 }
 
 template <int MODE>
-void launch_wf_mode(const KParams& kp, const uint8_t* q, const uint8_t* s, const WfWs& W, int nw, bool grouped, bool tb,
-                    bool p16, bool fa, aln_result_t* out, uint32_t* cigar, int64_t cap, const int64_t* cigar_off,
+void launch_wf_mode(const KParams& kp, const uint8_t* q, const uint8_t* s, const WfWs& W, int nw, bool grouped, bool crowded,
+                    bool tb, bool p16, bool fa, aln_result_t* out, uint32_t* cigar, int64_t cap, const int64_t* cigar_off,
                     hipStream_t st) {
   if (tb) {
-    launch_wf_m<MODE, true>(kp, q, s, W, nw, grouped, false, fa, st);
+    launch_wf_m<MODE, true>(kp, q, s, W, nw, grouped, false, false, fa, st);
     hipLaunchKernelGGL((wf_finish_kernel<MODE, true>), dim3(256), dim3(256), 0, st, kp, W, q, s, out, cigar, cap,
                        cigar_off);
   } else {
-    launch_wf_m<MODE, false>(kp, q, s, W, nw, grouped, p16, fa, st);
+    launch_wf_m<MODE, false>(kp, q, s, W, nw, grouped, crowded, p16, fa, st);
     hipLaunchKernelGGL((wf_finish_kernel<MODE, false>), dim3(256), dim3(256), 0, st, kp, W, q, s, out, cigar, cap,
                        cigar_off);
   }
@@ -1326,7 +1338,7 @@ WfWs wf_view(void* base_, const WfOffsets& o) {
 }
 
 aln_status_t launch_wf_i32(const KParams& kp, const WfWs& W, const uint8_t* q, const uint8_t* s,
-                           aln_result_t* out, int max_waves, bool grouped, bool tb, bool p16, bool fa, uint32_t* cigar,
+                           aln_result_t* out, int max_waves, bool grouped, bool crowded, bool tb, bool p16, bool fa, uint32_t* cigar,
                            int64_t cigar_cap, hipStream_t stream, const int64_t* cigar_off) {
   hipLaunchKernelGGL(wf_reset_kernel, dim3(256), dim3(256), 0, stream, W);
   if (!grouped) {
@@ -1336,13 +1348,13 @@ aln_status_t launch_wf_i32(const KParams& kp, const WfWs& W, const uint8_t* q, c
   }
   switch (kp.mode) {
     case ALN_GLOBAL:
-      launch_wf_mode<ALN_GLOBAL>(kp, q, s, W, max_waves, grouped, tb, p16, fa, out, cigar, cigar_cap, cigar_off, stream);
+      launch_wf_mode<ALN_GLOBAL>(kp, q, s, W, max_waves, grouped, crowded, tb, p16, fa, out, cigar, cigar_cap, cigar_off, stream);
       break;
     case ALN_LOCAL:
-      launch_wf_mode<ALN_LOCAL>(kp, q, s, W, max_waves, grouped, tb, p16, fa, out, cigar, cigar_cap, cigar_off, stream);
+      launch_wf_mode<ALN_LOCAL>(kp, q, s, W, max_waves, grouped, crowded, tb, p16, fa, out, cigar, cigar_cap, cigar_off, stream);
       break;
     default:
-      launch_wf_mode<ALN_SEMIGLOBAL>(kp, q, s, W, max_waves, grouped, tb, p16, fa, out, cigar, cigar_cap, cigar_off,
+      launch_wf_mode<ALN_SEMIGLOBAL>(kp, q, s, W, max_waves, grouped, crowded, tb, p16, fa, out, cigar, cigar_cap, cigar_off,
                                      stream);
       break;
   }
@@ -1378,7 +1390,7 @@ aln_status_t launch_long(const KParams& kp, const LongPlan& pl, const uint8_t* q
   hipLaunchKernelGGL(wf_single_pair_kernel, dim3(1), dim3(64), 0, stream, W, (int)n, (int)m, kWfBand);
   // one pair: its bands are few per SIMD, so the grouped engine (no device-memory stalls in the
   // compute waves) is the faster one
-  return launch_wf_i32(kp, W, q, s, out, pl.n_waves, true, pl.tb, false, band_fits_fa(kp, n, m), cigar,
+  return launch_wf_i32(kp, W, q, s, out, pl.n_waves, true, false, pl.tb, false, band_fits_fa(kp, n, m), cigar,
                        cigar_cap, stream);
 }
 

@@ -44,3 +44,12 @@ def test_local_lanes_with_codes_do_not_spill(kernels):
     """One pair per lane in 16 bits, local, with codes (mode 1, any gaps, traceback)."""
     for name, k in _named(kernels, r"batch_i16_kernelILi1ELb[01]ELb1E").items():
         assert int(k["vgpr_spill_count"]) == 0, (name, k["vgpr_count"], k["vgpr_spill_count"])
+
+
+def test_grouped_scores_leave_room_for_five_waves(kernels):
+    """The score-only bands in groups that are built for 5 waves a SIMD (last template argument) keep to a fifth of its 512
+    registers: else their workgroups are not all resident, whatever the launch holds."""
+    got = _named(kernels, r"wf_i32_group_kernelILi\d.*Li4ELb0ELb0ELi5E")
+    assert len(got) == 27, sorted(got)  # 3 modes, linear and affine gaps (float and integer lanes), 3 profiles
+    for name, k in got.items():
+        assert int(k["vgpr_count"]) <= 96, (name, k["vgpr_count"])
