@@ -29,10 +29,11 @@ namespace mialign {
 //   kProfTable  a 32-bit LDS table indexed by both letters (any score range);
 //   kProfReg    alphabets of up to 4 letters: one register per row holds the scores of the row's
 //               letter against the 4 letters as signed bytes; a column letter is the one-hot byte 1 << 8c;
+//   kProfRegBits the same registers, a column letter as the bit offset 8c, for an extract and an add;
 //   kProfLane   alphabets of up to 32 letters: per letter, every lane keeps the scores of 4 rows as 4
 //               signed bytes in one LDS word, so a step reads one word per 4 rows.
 // The byte forms need every sigma - 2 ge in -127..127 (-128 marks rows past the end).
-constexpr int kProfTable = 0, kProfReg = 1, kProfLane = 2;
+constexpr int kProfTable = 0, kProfReg = 1, kProfLane = 2, kProfRegBits = 3;
 constexpr uint32_t kPadWord = 0x80808080u;  // four rows past the end, or the letter past a subject's end
 
 constexpr int kFaBits = 0x4B000000;  // the float 2^23
@@ -109,7 +110,9 @@ __device__ __forceinline__ void band_column(const KParams& P, const int32_t* tab
     int d;
     // Linear gaps add nothing else to a cell: a step waits for its chain of maxima, and the extract and add that the chain does not wait
     // for beat the dot product's latency (30000 x 30000 proteins 5.17 and 4.64 ms, 3000 of 64..2000 semi-global 1.38 and 1.01).
-    if constexpr (PROF == kProfLane && !AFFINE)
+    if constexpr (PROF == kProfRegBits)
+      d = hd + __builtin_amdgcn_sbfe(prof[r], in_c, 8);
+    else if constexpr (PROF == kProfLane && !AFFINE)
       d = hd + __builtin_amdgcn_sbfe(pw[r / 4], 8 * (r & 3), 8);
     else if constexpr (PROF == kProfReg)
       d = __builtin_amdgcn_sdot4(prof[r], in_c, hd, false);
@@ -260,7 +263,7 @@ __device__ __forceinline__ void band_profile(const KParams& P, const uint32_t* s
   const uint32_t* rows = sig2 + (flip ? kMaxAlphabet * 8 : 0);
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    if (PROF == kProfReg)
+    if (PROF == kProfReg || PROF == kProfRegBits)
       prof[r] = (int)(rowc[r] < kMaxAlphabet ? rows[rowc[r] * 8] : kPadWord);
     else if (PROF == kProfTable)
       prof[r] = flip ? rowc[r] : rowc[r] * kTab;  // the table is indexed [query letter][subject letter]
@@ -303,6 +306,7 @@ __device__ __forceinline__ int letter_index(const KParams& P, int c, bool flip, 
     c = -1;
   }
   if (PROF == kProfReg) return c < 0 ? 0 : 1 << (8 * c);
+  if (PROF == kProfRegBits) return c < 0 ? 31 : 8 * c;  // (the extract at bit 31 gives 0 or -1)
   if (PROF == kProfLane) return (c < 0 ? P.alphabet : c) * 256 * (R / 4);  // bytes
   return (c < 0 ? kPad : c) * (flip ? kTab : 1);
 }

@@ -1213,22 +1213,27 @@ void launch_wf_t(const KParams& kp, const uint8_t* q, const uint8_t* s, const Wf
                        dim3(kWfBlock), 2 * lds, stream, kp, q, s, W);
     return;
   }
-  if (!TB && W.ckcols) {
-    ProfScope prof("wavefront_i32_checkpoints", stream);
-    hipLaunchKernelGGL((wf_i32_group_kernel<MODE, AFFINE, PROF, false, FA, kWfR, false, !TB, TB ? 4 : 3>), dim3(blocks),
-                       dim3(kWfBlock), lds, stream, kp, q, s, W);
-    return;
+  // Local linear score-only bands in groups: their steps wait for latency (30000 x 30000 5.03 and 4.68 ms), where bands on their own
+  // fill the SIMD and the dot product's fewer issue slots are worth more (1500 pairs of 2000..6000 4.48 and 4.86).
+  constexpr int kGroupProf = PROF == kProfReg && MODE == ALN_LOCAL && !AFFINE && !TB ? kProfRegBits : PROF;
+  if constexpr (!TB) {
+    if (W.ckcols) {
+      ProfScope prof("wavefront_i32_checkpoints", stream);
+      hipLaunchKernelGGL((wf_i32_group_kernel<MODE, AFFINE, kGroupProf, TB, FA, kWfR, false, true, 3>), dim3(blocks),
+                         dim3(kWfBlock), lds, stream, kp, q, s, W);
+      return;
+    }
   }
   ProfScope prof(TB ? "wavefront_i32_traceback" : "wavefront_i32", stream);
   if (grouped) {
     if constexpr (!TB) {
       if (crowded) {
-        hipLaunchKernelGGL((wf_i32_group_kernel<MODE, AFFINE, PROF, TB, FA, kWfR, false, false, 5>), dim3(blocks),
+        hipLaunchKernelGGL((wf_i32_group_kernel<MODE, AFFINE, kGroupProf, TB, FA, kWfR, false, false, 5>), dim3(blocks),
                            dim3(kWfBlock), lds, stream, kp, q, s, W);
         return;
       }
     }
-    hipLaunchKernelGGL((wf_i32_group_kernel<MODE, AFFINE, PROF, TB, FA, kWfR, false, false, 4>), dim3(blocks),
+    hipLaunchKernelGGL((wf_i32_group_kernel<MODE, AFFINE, kGroupProf, TB, FA, kWfR, false, false, 4>), dim3(blocks),
                        dim3(kWfBlock), lds, stream, kp, q, s, W);
   } else
     hipLaunchKernelGGL((wf_i32_kernel<MODE, AFFINE, PROF, TB, FA, kWfR>), dim3(blocks), dim3(kWfBlockAlone), lds,
