@@ -60,9 +60,10 @@ aln_status_t make_params(const aln_scoring_t* sc, KParams* kp) {
   kp->sigma_min = smin;
   kp->fgo = (float)kp->go;
   for (int k = 0; k < 20; ++k) kp->fc[k] = (float)(-k * kp->ge);
+  kp->sig_off = std::max(0, smax - 2 * kp->ge - 127);
   for (int a = 0; a < A; ++a)
     for (int b = 0; b < A; ++b) {
-      const int8_t v = (int8_t)(kp->sig[a * kMaxAlphabet + b] - 2 * kp->ge);
+      const int8_t v = (int8_t)(kp->sig[a * kMaxAlphabet + b] - 2 * kp->ge - kp->sig_off);
       kp->sig2[a * kMaxAlphabet + b] = v;
       kp->sig2[kMaxAlphabet * kMaxAlphabet + b * kMaxAlphabet + a] = v;
     }

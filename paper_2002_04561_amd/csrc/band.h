@@ -31,9 +31,15 @@ namespace mialign {
 //               letter against the 4 letters as signed bytes; a column letter is the one-hot byte 1 << 8c;
 //   kProfRegBits the same registers, a column letter as the bit offset 8c, for an extract and an add;
 //   kProfLane   alphabets of up to 32 letters: per letter, every lane keeps the scores of 4 rows as 4
-//               signed bytes in one LDS word, so a step reads one word per 4 rows.
-// The byte forms need every sigma - 2 ge in -127..127 (-128 marks rows past the end).
-constexpr int kProfTable = 0, kProfReg = 1, kProfLane = 2, kProfRegBits = 3;
+//               signed bytes in one LDS word, so a step reads one word per 4 rows;
+//   kProfRegLow, kProfLaneLow  the two for scores past a byte: the bytes hold sigma - 2 ge - sig_off, and a cell adds
+//               sig_off back.  The one addition more is dear where cells fill the SIMD (1500 linear-gap protein pairs of
+//               2000..6000 3.28 ms without and 3.71 with), and the table dearer yet: extend -70, 4 letters, local,
+//               30000 x 30000 8.25 ms from the table and 5.34 so, 3000 of 64..2000 2.56 and 1.64.
+// The byte forms need every one of their bytes in -127..127 (-128 marks rows past the end).
+constexpr int kProfTable = 0, kProfReg = 1, kProfLane = 2, kProfRegBits = 3, kProfRegLow = 4, kProfLaneLow = 5;
+constexpr bool reg_bits(int prof) { return prof == kProfRegBits || prof == kProfRegLow; }  // column letters as bit offsets
+constexpr bool lane_words(int prof) { return prof == kProfLane || prof == kProfLaneLow; }
 constexpr uint32_t kPadWord = 0x80808080u;  // four rows past the end, or the letter past a subject's end
 
 constexpr int kFaBits = 0x4B000000;  // the float 2^23
@@ -112,6 +118,10 @@ __device__ __forceinline__ void band_column(const KParams& P, const int32_t* tab
     // for beat the dot product's latency (30000 x 30000 proteins 5.17 and 4.64 ms, 3000 of 64..2000 semi-global 1.38 and 1.01).
     if constexpr (PROF == kProfRegBits)
       d = hd + __builtin_amdgcn_sbfe(prof[r], in_c, 8);
+    else if constexpr (PROF == kProfRegLow)
+      d = hd + P.sig_off + __builtin_amdgcn_sbfe(prof[r], in_c, 8);
+    else if constexpr (PROF == kProfLaneLow)
+      d = hd + P.sig_off + __builtin_amdgcn_sbfe(pw[r / 4], 8 * (r & 3), 8);
     else if constexpr (PROF == kProfLane && !AFFINE)
       d = hd + __builtin_amdgcn_sbfe(pw[r / 4], 8 * (r & 3), 8);
     else if constexpr (PROF == kProfReg)
@@ -120,6 +130,8 @@ __device__ __forceinline__ void band_column(const KParams& P, const int32_t* tab
       d = __builtin_amdgcn_sdot4(pw[r / 4], 1 << (8 * (r & 3)), hd, false);
     else
       d = hd + tab[prof[r] + in_c];
+    // (a pad column left of the matrix must not rise above the border value by the lowered bytes' offset)
+    if (PROF == kProfRegLow && MODE == ALN_GLOBAL && FLOOR) d = in_c == 31 ? hd : d;
     const int gl = AFFINE ? L.g[r] : L.h[r];
     constexpr bool kFold = FLOOR && AFFINE && !TB;
     if (AFFINE)
@@ -171,7 +183,7 @@ struct BandIn {
 };
 template <int PROF, int R>
 __device__ __forceinline__ void load_words(const uint32_t* lp, BandIn<R>& I) {
-  if constexpr (PROF == kProfLane) {
+  if constexpr (lane_words(PROF)) {
 #pragma unroll
     for (int u = 0; u < 4; ++u)
 #pragma unroll
@@ -263,14 +275,14 @@ __device__ __forceinline__ void band_profile(const KParams& P, const uint32_t* s
   const uint32_t* rows = sig2 + (flip ? kMaxAlphabet * 8 : 0);
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    if (PROF == kProfReg || PROF == kProfRegBits)
+    if (PROF == kProfReg || reg_bits(PROF))
       prof[r] = (int)(rowc[r] < kMaxAlphabet ? rows[rowc[r] * 8] : kPadWord);
     else if (PROF == kProfTable)
       prof[r] = flip ? rowc[r] : rowc[r] * kTab;  // the table is indexed [query letter][subject letter]
     else
       prof[r] = 0;
   }
-  if constexpr (PROF == kProfLane) {
+  if constexpr (lane_words(PROF)) {
     constexpr int NW = R / 4;
     for (int a = 0; a < P.alphabet; a += 4) {
 #pragma unroll
@@ -298,7 +310,7 @@ __device__ __forceinline__ void band_profile(const KParams& P, const uint32_t* s
 }
 
 // A subject letter as the profile kind wants it; col < 1 or past the end (c < 0) gives the pad letter, whose
-// score is at most 2 ge: a cell of a pad column is below a real cell.
+// score is at most 2 ge, or at most -1 of the lowered bytes: a cell of a pad column is below a real cell.
 template <int PROF, int R>
 __device__ __forceinline__ int letter_index(const KParams& P, int c, bool flip, bool& bad) {
   if (c >= P.alphabet) {
@@ -306,8 +318,8 @@ __device__ __forceinline__ int letter_index(const KParams& P, int c, bool flip, 
     c = -1;
   }
   if (PROF == kProfReg) return c < 0 ? 0 : 1 << (8 * c);
-  if (PROF == kProfRegBits) return c < 0 ? 31 : 8 * c;  // (the extract at bit 31 gives 0 or -1)
-  if (PROF == kProfLane) return (c < 0 ? P.alphabet : c) * 256 * (R / 4);  // bytes
+  if (reg_bits(PROF)) return c < 0 ? 31 : 8 * c;  // (the extract at bit 31 gives 0 or -1)
+  if (lane_words(PROF)) return (c < 0 ? P.alphabet : c) * 256 * (R / 4);  // bytes
   return (c < 0 ? kPad : c) * (flip ? kTab : 1);
 }
 

@@ -333,11 +333,11 @@ __device__ __forceinline__ void run_block(const Window& lett, const uint32_t* lp
   BandIn<R> A, C;
   lett.get(lane, 0, A.vc);
   load_rows(0, A);
-  if (PROF == kProfLane) lett.get(lane, 1, C.vc);
+  if (lane_words(PROF)) lett.get(lane, 1, C.vc);
   load_words<PROF, R>(lp, A);
   for (int g4 = 0; g4 < ng; g4 += 2) {
     load_rows(g4 + 1, C);
-    if (PROF == kProfLane) {
+    if (lane_words(PROF)) {
       load_words<PROF, R>(lp, C);
       lett.get(lane, g4 + 2, A.vc);
     } else {
@@ -346,7 +346,7 @@ __device__ __forceinline__ void run_block(const Window& lett, const uint32_t* lp
     run(g4, A);
     if (g4 + 1 >= ng) break;
     load_rows(g4 + 2, A);
-    if (PROF == kProfLane) {
+    if (lane_words(PROF)) {
       load_words<PROF, R>(lp, A);
       lett.get(lane, g4 + 3, C.vc);
     } else {

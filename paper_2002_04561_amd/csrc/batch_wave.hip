@@ -263,7 +263,7 @@ void launch_f(const KParams& kp, const WaveArgs& a, int waves, hipStream_t strea
 
 template <int MODE>
 void launch_m(const KParams& kp, const WaveArgs& a, int waves, hipStream_t stream) {
-  const bool bytes = kp.sigma_max - 2 * kp.ge <= 127 && kp.sigma_min - 2 * kp.ge >= -127;
+  const bool bytes = score_bytes(kp);
   const bool fa = band_fits_fa(kp, a.max_n, a.max_m);
   auto go = [&](auto affine, auto lanes) {
     constexpr bool kAffine = decltype(affine)::value, kFa = decltype(lanes)::value;

@@ -31,10 +31,18 @@ struct KParams {
   int64_t spin_lds;  // polls of LDS a bounded wait makes before giving up
   float fgo;      // go
   float fc[20];   // fc[k] = -k * ge
+  int32_t sig_off;  // what sig2 is lowered by: 0 unless the largest sigma - 2 ge exceeds a signed byte
   int8_t sig[kMaxAlphabet * kMaxAlphabet];  // row-major sigma(q, s) over the real alphabet
-  // sigma - 2 ge (low bytes; exact where every one fits a byte): row-major by query letter, then by subject letter
+  // sigma - 2 ge - sig_off (low bytes; exact where every one fits a byte): row-major by query letter, then by subject letter
   alignas(4) int8_t sig2[2 * kMaxAlphabet * kMaxAlphabet];
 };
+
+// Whether sig2 is exact and lowered by nothing: the byte profiles of the bands (band.h).
+inline bool score_bytes(const KParams& P) { return P.sig_off == 0 && P.sigma_min - 2 * P.ge >= -127; }
+// Whether sig2 is exact, lowered or not, and a pad letter, which scores sigma_max - 127 at most, is a mismatch.
+inline bool lowered_score_bytes(const KParams& P) {
+  return P.sigma_max <= 126 && P.sigma_min - 2 * P.ge - P.sig_off >= -127;
+}
 
 // Traceback slabs of the one-pair-per-lane kernels hold every cell's code for the waves in flight; a batch
 // of large pairs runs fewer waves rather than asking for more than this.

@@ -28,7 +28,7 @@ constexpr int kTWaves = kTileRows / kWfBand;  // bands (waves) of a tile
 constexpr int kTbBandMargin = kTileCols / 2;   // columns of the first band to either side of the walk's diagonal
 constexpr int kTbPhases = 4;                   // three bands, each 4 times as wide as the one before, then every tile
 
-// Profile kinds of the band wavefront (band.h): register bytes for up to 4 letters, else the LDS table.
+// Profile kinds of the band wavefront (band.h): register bytes for up to 4 letters, lowered or not, else the LDS table.
 
 struct TbView {
   int n, m;            // rows (query) and columns (subject) of the pair
@@ -161,7 +161,7 @@ __global__ __launch_bounds__(64 * kTWaves) void tb_tile_kernel(const KParams P, 
     if (col > cols) return 0;
     int c = s[col - 1];
     if (c >= P.alphabet) c = PROF == kProfTable ? kPad : 0;
-    return PROF == kProfReg ? 1 << (8 * c) : c;
+    return PROF == kProfReg ? 1 << (8 * c) : reg_bits(PROF) ? 8 * c : c;
   };
 
   const int steps = cols + 63;
@@ -316,15 +316,16 @@ template <int MODE>
 void launch_rounds(const KParams& kp, const uint8_t* q, const uint8_t* s, const TbView& V, int nseg, bool fa,
                    aln_result_t* out, uint32_t* cigar, int64_t cap, hipStream_t stream) {
   hipLaunchKernelGGL((tb_init_kernel<MODE>), dim3(1), dim3(64), 0, stream, out, V, cigar, cap);
-  const bool bytes = kp.sigma_max - 2 * kp.ge <= 127 && kp.sigma_min - 2 * kp.ge >= -127;
   for (int seg = nseg - 1; seg >= 0; --seg) {
     for (int phase = 0; phase < kTbPhases; ++phase) {
       {
         ProfScope prof("traceback_tiles", stream);
         auto tiles = [&](auto affine, auto lanes) {
           constexpr bool kAffine = decltype(affine)::value, kFa = decltype(lanes)::value;
-          if (bytes && kp.alphabet <= 4)
+          if (kp.alphabet <= 4 && score_bytes(kp))
             launch_tiles<MODE, kAffine, kProfReg, kFa>(kp, q, s, V, seg, phase, stream);
+          else if (kp.alphabet <= 4 && lowered_score_bytes(kp))
+            launch_tiles<MODE, kAffine, kProfRegLow, kFa>(kp, q, s, V, seg, phase, stream);
           else
             launch_tiles<MODE, kAffine, kProfTable, kFa>(kp, q, s, V, seg, phase, stream);
         };

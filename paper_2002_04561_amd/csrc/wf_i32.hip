@@ -87,11 +87,11 @@ __device__ __forceinline__ int unrel16(int rel, int base) { return rel == kNeg16
 template <int MODE, bool AFFINE, int PROF, bool TB, bool FA, int R>
 __global__ __launch_bounds__(kWfBlockAlone, 4) void wf_i32_kernel(const KParams P, const uint8_t* __restrict__ Q,
                                                           const uint8_t* __restrict__ S, WfWs W) {
-  static_assert(PROF != kProfLane || R == 4, "a lane profile word holds 4 rows");
+  static_assert(!lane_words(PROF) || R == 4, "a lane profile word holds 4 rows");
   __shared__ int32_t tab[PROF == kProfTable ? kTab * kTab : 1];
   __shared__ int4 stage[kWfWavesPerBlock][2][16];
   __shared__ LetterWindow<64> letters[kWfWavesPerBlock];
-  extern __shared__ uint32_t lprof[];  // kProfLane: [wave][letter][lane], alphabet letters and the pad letter
+  extern __shared__ uint32_t lprof[];  // lane words: [wave][letter][lane], alphabet letters and the pad letter
   __shared__ uint32_t sig2[PROF == kProfTable ? 1 : kScoreWords];
   fill_table<PROF>(P, tab, sig2);
   __syncthreads();
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(kWfBlockAlone, 4) void wf_i32_kernel(const KParams 
   int* st_h = reinterpret_cast<int*>(&stage[wib][0][0]);
   int* st_e = reinterpret_cast<int*>(&stage[wib][1][0]);
   LetterWindow<64>& lett = letters[wib];
-  uint32_t* __restrict__ lp = lprof + (PROF == kProfLane ? wib * (P.alphabet + 1) * 64 + lane : 0);
+  uint32_t* __restrict__ lp = lprof + (lane_words(PROF) ? wib * (P.alphabet + 1) * 64 + lane : 0);
   const int np = *W.n_pairs;
   const int64_t n_items = *W.n_items;
 
@@ -267,7 +267,7 @@ __global__ __launch_bounds__(kWfBlockAlone, 4) void wf_i32_kernel(const KParams 
 template <int MODE, bool AFFINE, int PROF, bool TB, bool FA, int R, bool P16, bool CKPT, int WAVES>
 __global__ __launch_bounds__(kWfBlock, WAVES) void wf_i32_group_kernel(const KParams P, const uint8_t* __restrict__ Q,
                                                           const uint8_t* __restrict__ S, WfWs W) {
-  static_assert(PROF != kProfLane || R == 4, "a lane profile word holds 4 rows");
+  static_assert(!lane_words(PROF) || R == 4, "a lane profile word holds 4 rows");
   constexpr int BLK = kBlkGrouped;
   // packed bands: sigma - ge by (query letter, subject letter), the source of their profiles; kProfTable: sigma - 2 ge
   __shared__ int32_t tab[P16 || PROF == kProfTable ? kTab * kTab : 1];
@@ -280,7 +280,7 @@ __global__ __launch_bounds__(kWfBlock, WAVES) void wf_i32_group_kernel(const KPa
   __shared__ int con[kWfWavesPerBlock + 1];  // columns read out of each ring
   __shared__ long long s_t0;                 // first item of the group
   __shared__ int s_err;
-  extern __shared__ uint32_t lprof[];        // kProfLane: [wave][letter][lane], alphabet letters and the pad letter
+  extern __shared__ uint32_t lprof[];        // lane words: [wave][letter][lane], alphabet letters and the pad letter
   static_assert(!P16 || (MODE == ALN_LOCAL && (PROF == kProfReg || PROF == kProfLane) && !TB && R == 4),
                 "packed bands: local, score only, register or per-lane profiles");
   static_assert(!CKPT || (!TB && !P16 && R == 4), "checkpoints: 32-bit score-only bands");
@@ -764,7 +764,7 @@ __global__ __launch_bounds__(kWfBlock, WAVES) void wf_i32_group_kernel(const KPa
     const uint8_t* __restrict__ s = (flip ? Q : S) + pr.s_off;
 
     const int i0 = b * BH, irow0 = i0 + lane * R;
-    uint32_t* __restrict__ lp = lprof + (PROF == kProfLane ? cw * (P.alphabet + 1) * 64 + lane : 0);
+    uint32_t* __restrict__ lp = lprof + (lane_words(PROF) ? cw * (P.alphabet + 1) * 64 + lane : 0);
     LetterWindow<BLK>& lett = letters[cw];
     int prof[R];
     BandLane<R> L;
@@ -1204,7 +1204,7 @@ template <int MODE, bool AFFINE, int PROF, bool TB, bool FA>
 void launch_wf_t(const KParams& kp, const uint8_t* q, const uint8_t* s, const WfWs& W, int n_waves, bool grouped,
                  bool crowded, bool p16, hipStream_t stream) {
   const int blocks = (n_waves + kWfWavesPerBlock - 1) / kWfWavesPerBlock;
-  const size_t lds = PROF == kProfLane ? (size_t)kWfWavesPerBlock * (kp.alphabet + 1) * 64 * sizeof(uint32_t) : 0;
+  const size_t lds = lane_words(PROF) ? (size_t)kWfWavesPerBlock * (kp.alphabet + 1) * 64 * sizeof(uint32_t) : 0;
   constexpr bool kCanPack = MODE == ALN_LOCAL && (PROF == kProfReg || PROF == kProfLane) && !TB;
   if (kCanPack && grouped && p16 && p16_exact(kp)) {
     // packed bands keep two 16-bit rows of each half per letter and lane: twice the words
@@ -1243,11 +1243,15 @@ void launch_wf_t(const KParams& kp, const uint8_t* q, const uint8_t* s, const Wf
 template <int MODE, bool AFFINE, bool TB, bool FA>
 void launch_wf_p(const KParams& kp, const uint8_t* q, const uint8_t* s, const WfWs& W, int nw, bool grouped, bool crowded, bool p16,
                  hipStream_t st) {
-  const bool bytes = kp.sigma_max - 2 * kp.ge <= 127 && kp.sigma_min - 2 * kp.ge >= -127;
+  const bool bytes = score_bytes(kp), lowered = lowered_score_bytes(kp);
   if (bytes && kp.alphabet <= 4)
     launch_wf_t<MODE, AFFINE, kProfReg, TB, FA>(kp, q, s, W, nw, grouped, crowded, p16, st);
+  else if (lowered && kp.alphabet <= 4)
+    launch_wf_t<MODE, AFFINE, kProfRegLow, TB, FA>(kp, q, s, W, nw, grouped, crowded, false, st);
   else if (bytes)
     launch_wf_t<MODE, AFFINE, kProfLane, TB, FA>(kp, q, s, W, nw, grouped, crowded, p16, st);
+  else if (lowered && kp.sig_off <= 127)  // (128 and more would lift the pad letter's -128 above 0)
+    launch_wf_t<MODE, AFFINE, kProfLaneLow, TB, FA>(kp, q, s, W, nw, grouped, crowded, false, st);
   else
     launch_wf_t<MODE, AFFINE, kProfTable, TB, FA>(kp, q, s, W, nw, grouped, crowded, false, st);
 }
