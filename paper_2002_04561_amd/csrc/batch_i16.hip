@@ -119,6 +119,9 @@ static_assert(kI16ProfBase % 256 == 0, "profiles start on a bank sweep");
 // order (largest shapes first), so the waves drain the list evenly whatever number of them is
 // resident.
 __device__ __forceinline__ int64_t next_group(int* ticket, int lane) {
+  // Keeps the whole wave together here: without a convergent operation before it, lane 0's branch may be joined with one on
+  // lane 0 at the end of the caller's loop, which sends the other lanes to the shuffle ahead of it.
+  __builtin_amdgcn_wave_barrier();
   int g = 0;
   if (lane == 0) g = atomicAdd(ticket, 1);
   return (int64_t)__shfl(g, 0, 64);
