@@ -90,16 +90,18 @@ __device__ __forceinline__ uint32_t tree_pick(const uint32_t* x, const uint32_t*
   return t[0];
 }
 
-// The 15-bit cells (kWord): a global or semi-global batch over at most 4 letters whose values, with a bias of -ge for every row
+// The 15-bit cells (WORD): a global or semi-global batch over at most 4 letters whose values, with a bias of -ge for every row
 // and column and of kept zero -3 go, all lie in 0 .. kWordTop (word_cells).  Then
 //   E~(i, j) = max(E~(i-1, j), g(i-1, j)),  F~(i, j) = max(F~(i, j-1), g(i, j-1)),  g = H~ + go,
 //   H~(i, j) = max(g(i-1, j-1) + (sigma - 2 ge - go), E~, F~):
 // neither gap costs an add, the one g of a cell serves three neighbours, no half carries into the other (so both are added as
 // one 32-bit word), and the four scores of a row's letter are the bytes of one word, non-negative, so one v_perm picks both
 // pairs' scores from registers: no profile in LDS.  Cells outside a pair add 0 and reach no cell inside.
-// It is 15 instructions a row with codes, 17 and the profile's reads with the general cells, and VALU issue bounds both (1048576
-// reads of 100..250 with CIGARs: 18.3 ms with the general cells, 17.9 with these, 16.6 with the loop's branches gone as well,
-// where issue takes 84% of the time; codes and rows between strips are 54 GB of memory traffic, 3.2 TB/s).
+// It is 15 instructions a row with codes, 17 and the profile's reads with the general cells (1048576 reads of 100..250 with
+// CIGARs: 18.3 ms with the general cells, 17.9 with these, 16.6 with the loop's branches gone as well).  Memory binds it now as
+// much as VALU issue does: a launch reads 36 GB (rows between strips, the walks' codes) and writes 37 (codes, rows), 4.5 TB/s where
+// a large copy reaches 4.9, and issues VALU instructions in 79 % of its cycles (counted at 4 cycles each).  With codes the kernel
+// takes all 256 registers and spills 15; a smaller strip doubles the rows between strips.
 constexpr int kWordTop = 0x7bff;
 
 // LDS query profile of one wave, in 32-bit words.  For letter c, the R scores of a pair slot are
@@ -165,16 +167,17 @@ __global__ __launch_bounds__(kI16Block, 2) void batch_i16_kernel(
       }
       rowsig[threadIdx.x] = w;
     }
-  } else
-  for (int k = threadIdx.x; k < kTab * kTab; k += blockDim.x) {
-    const int a = k / kTab, b = k % kTab;
-    int32_t v;
-    if (a >= P.alphabet || b >= P.alphabet)
-      v = kPadSigma16;
-    else
-      v = (P.use_table ? (int32_t)P.sig[a * kMaxAlphabet + b] : (a == b ? P.match : P.mismatch)) -
-          (kBias ? P.ge : 0);
-    tab[k] = v;
+  } else {
+    for (int k = threadIdx.x; k < kTab * kTab; k += blockDim.x) {
+      const int a = k / kTab, b = k % kTab;
+      int32_t v;
+      if (a >= P.alphabet || b >= P.alphabet)
+        v = kPadSigma16;
+      else
+        v = (P.use_table ? (int32_t)P.sig[a * kMaxAlphabet + b] : (a == b ? P.match : P.mismatch)) -
+            (kBias ? P.ge : 0);
+      tab[k] = v;
+    }
   }
   __syncthreads();
   const int AP = P.alphabet;  // profile letters per pair; past a subject's end, the shared pad row

@@ -1,10 +1,10 @@
 // One wave per pair: traceback batches too short to fill the one-pair-per-lane kernels, and aln_traceback.
 //
-// A lane of batch_i16.hip takes a whole pair, so a wave's time is that of its largest pair whatever the batch holds: 4.5 ms
-// for reads of 100..250 letters against windows 64 longer, be it 400 pairs or 262,144.  Here a wave relaxes its pair
+// A lane of batch_i16.hip takes a whole pair, so a batch takes at least as long as its largest pair on one lane: 4.5 ms
+// for 400 reads of 100..250 letters against windows 64 longer, and 8.1 for 262,144 of them.  Here a wave relaxes its pair
 // band by band (256 rows: 64 lanes x 4) with the recurrence of band.h, in 32-bit lanes, keeps the bottom row of a band in a
 // row buffer of its own for the next, and walks the codes back with the whole wave (walk_wave.h).  Bound by VALU issue:
-// a read's band takes (m + 64) steps of about 55 instructions, 70 % of its rows and columns padding.
+// a read's band takes (m + 64) steps of about 55 instructions, about 46 % of its lane-steps padding (256 rows for 175, m + 64 steps for m).
 // Pairs come in the planner's order, largest first, and the waves take them in turn.
 #include "band.h"
 #include "band_wave.h"
@@ -19,7 +19,8 @@ namespace {
 
 constexpr int kPWavesPerBlock = 4;
 // Three waves a SIMD (168 registers each): four, with 128, spilled 9 to 180 of them (20011 reads of 100..250 traced back from
-// their ends 732 us, 722 so; 400 such reads with CIGARs 109 us, 104 so).
+// their ends 732 us, 722 so; 400 such reads with CIGARs 109 us, 104 so).  At three the semi-global reads and all linear gaps fit;
+// the local affine kernels still spill 19 to 37, and two semi-global ones with the table 13 and 15.
 constexpr int kPWavesPerCU = 12;
 constexpr int kPBand = 64 * kWfR;
 

@@ -238,9 +238,9 @@ __device__ void walk_core(const uint16_t* __restrict__ codes, int64_t ld, int r0
 }
 
 // Ends a walk: stores the last run and reverses the runs (last to first while walking) with the whole
-// wave.  Lane l swaps the pairs (a, runs-1-a) with a = l, l+64, ...: no two lanes touch the same run,
-// and each lane's loads are its own earlier stores' addresses only through the walk, which has
-// completed.  Returns the number of runs.
+// wave.  Lane l swaps the pairs (a, runs-1-a) with a = l, l+64, ...: no two lanes touch the same run.  Run r
+// was stored by lane r % 64, so a lane loads other lanes' stores: the wait before the swap completes them.
+// Returns the number of runs.
 __device__ inline int64_t walk_finish(WalkState& S, int lane, uint32_t* __restrict__ cig, int64_t cap) {
   int64_t runs = S.runs;
   if (S.cur_len) {
