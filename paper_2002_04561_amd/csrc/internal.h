@@ -31,10 +31,12 @@ struct KParams {
   int64_t spin_lds;  // polls of LDS a bounded wait makes before giving up
   float fgo;      // go
   float fc[20];   // fc[k] = -k * ge
-  int32_t sig_off;  // what sig2 is lowered by: 0 unless the largest sigma - 2 ge exceeds a signed byte
   int8_t sig[kMaxAlphabet * kMaxAlphabet];  // row-major sigma(q, s) over the real alphabet
   // sigma - 2 ge - sig_off (low bytes; exact where every one fits a byte): row-major by query letter, then by subject letter
   alignas(4) int8_t sig2[2 * kMaxAlphabet * kMaxAlphabet];
+  // what sig2 is lowered by: 0 unless the largest sigma - 2 ge exceeds a signed byte (last: ahead of the tables it moves them by
+  // 4 bytes, which took 200,003 peptide pairs from 1145 to 1181 us)
+  int32_t sig_off;
 };
 
 // Whether sig2 is exact and lowered by nothing: the byte profiles of the bands (band.h).
